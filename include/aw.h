@@ -199,9 +199,12 @@ aw_status aw_map_ensemble(const aw_ensemble *ens, int32_t n_ens,
                           const aw_tuning *tuning, void *stream);
 
 /* Rows of the resumable carry[AW_NCARRY][N], the propagation's own state in
- * its rotated frame (u = x + y, v = x - y, z; momenta and tangent alike): X,
- * P, tangent (scaled), X0 (original frame), P0, twice the J sum, tangent scale
- * exponent, steps done, left-the-window flag.  Only the library reads it. */
+ * its rotated frame (u = x + y, v = x - y, z; momenta and tangent alike): X (u,
+ * v and 2 z in units of pi/2048), P (p_u, p_v, sqrt 2 p_z), tangent (z
+ * components times sqrt 2, scaled), X0 (original frame), P0 (as P), twice the J
+ * sum, tangent scale exponent, steps done, flags (1: left the window; 2: the
+ * units above -- a carry without it, in radians and with z, p_z unscaled, is
+ * still read).  Only the library reads it. */
 #define AW_NCARRY 22
 
 /* Resumable form of aw_map_ensemble for one ensemble: runs global steps
@@ -436,9 +439,10 @@ void aw_graph_destroy(aw_graph *g);
 aw_status aw_timing_enable(int32_t on);
 aw_status aw_timing_read(double *ms, int64_t *launches);
 
-/* FP64 operations per map step of the propagation kernel as built, for the
- * roofline: counts of fma, mul and add/sub instructions (per orbit-step,
- * excluding the per-orbit prologue/epilogue); flops = 2 fma + mul + add. */
+/* FP64 operations of a map step in the rotated frame, for the roofline: counts
+ * of fma, mul and add/sub (per orbit-step, excluding the per-orbit
+ * prologue/epilogue); flops = 2 fma + mul + add.  The count of the unscaled
+ * form; the kernels' scaled units take fewer operations for the same step. */
 aw_status aw_step_op_counts(int32_t map_form, int32_t tangent, int64_t *fma, int64_t *mul,
                             int64_t *add);
 

@@ -212,7 +212,7 @@ def map_ensemble_steps(ens: Ensemble, carry: torch.Tensor, k_begin: int, k_end: 
                        ic: Optional[torch.Tensor] = None, orbit_out: Optional[torch.Tensor] = None,
                        state: Optional[torch.Tensor] = None, cls: Optional[torch.Tensor] = None,
                        tuning: Optional[Tuning] = None) -> None:
-    """Run global steps [k_begin, k_end) with the state carried in carry[21, N]."""
+    """Run global steps [k_begin, k_end) with the state carried in carry[22, N]."""
     N = ens.size
     _dev_f64(carry, (NCARRY, N), "carry")
     if orbit_out is not None:
@@ -505,7 +505,8 @@ def timing_read():
 
 
 def step_op_counts(map_form: str = "s6", tangent: bool = True):
-    """FP64 (fma, mul, add) instructions per map step of the kernel as built."""
+    """FP64 (fma, mul, add) operations of a map step, the unit of the roofline
+    (the unscaled rotated form; the kernels take fewer)."""
     f, m, a = ctypes.c_int64(), ctypes.c_int64(), ctypes.c_int64()
     _abi.check(_lib().aw_step_op_counts(FORMS[map_form], int(tangent), ctypes.byref(f), ctypes.byref(m),
                                         ctypes.byref(a)))

@@ -286,6 +286,11 @@ bool unique_weights(int form, double h, double kick[MAX_UNIQUE], double drift[MA
   return true;
 }
 
+// Factors of the scaled frame's weights, in extended precision so that each
+// weight is rounded once.
+constexpr long double NODES_PER_RAD = 2048.0L / 3.14159265358979323846264338327950288L;
+constexpr long double SQRT2 = 1.41421356237309504880168872420969808L;
+
 bool is_fin(double v) { return std::isfinite(v); }
 
 aw_status check_tuning(const aw_tuning *t, Tuning &out) {
@@ -390,8 +395,10 @@ FwdDesc make_desc(const aw_ensemble &e, const double *ic, const Tuning &t) {
   double tau[MAX_UNIQUE];
   (void)unique_weights(e.map_form, e.h, tau, d.drift);  // checked by check_ensemble
   for (int u = 0; u < MAX_UNIQUE; ++u) {
-    d.ka2[u] = 2.0 * tau[u] * e.eps;
-    d.ka4[u] = 4.0 * tau[u] * e.eps;
+    d.dnode[u] = (double)(d.drift[u] * NODES_PER_RAD);
+    d.dnodez[u] = (double)(d.drift[u] * (SQRT2 * NODES_PER_RAD));
+    d.ka[u] = tau[u] * e.eps;
+    d.kb[u] = (double)(SQRT2 * d.ka[u]);
   }
   d.eps = e.eps;
   d.th = (double)e.n_steps * e.h;

@@ -105,11 +105,6 @@ __device__ __forceinline__ SinCosT sincos_tab(double x, const double2 *__restric
   return o;
 }
 
-// FP64 operation counts of one sincos_tab.
-constexpr int SCT_FMA = 1 + 2 + 1 + 2 + 2;
-constexpr int SCT_MUL = 4;  // r*r, r*u, and one product per rotated output
-constexpr int SCT_ADD = 1;
-
 // The z factors of eq. 2's force and Hessian, cos^2 z and cos z sin z, from
 // the same table at the doubled angle: cos^2 z = (1 + cos 2z)/2 and
 // cos z sin z = sin(2z)/2.  The reduction is sincos_tab's, x = q pi/2048 + r;
@@ -146,9 +141,61 @@ __device__ __forceinline__ ZTerms zterms_tab(double z, const double2 *__restrict
   return o;
 }
 
-constexpr int ZT_FMA = 1 + 2 + 1 + 2 + 3;
-constexpr int ZT_MUL = 3;  // r*r, r*u, C*sh
-constexpr int ZT_ADD = 1;
+// ---------------------------------------------------------------------------
+// The propagation kernels hold their angles in units of the table's nodes,
+// a = 2048 x/pi (the drifts' weights carry the factor).  The reduction is then
+// exact and takes three additions: q = nearest integer to a (the low mantissa
+// word of a + 1.5*2^52 holds it), r = a - q, |r| <= 1/2.  The table entry
+// (S, C) of node q mod 4096 is turned by the angle r pi/2048 with three
+// shears,
+//   c1 = C - t S,  s = S + w c1,  c = c1 - t s,
+// t = tan(r pi/4096) and w = sin(r pi/2048), one coefficient each beyond the
+// leading one.  7 FMA, 3 MUL, 3 ADD in place of the radian form's 8, 4 and 1
+// plus the products that a doubled angle needed, and no reduction constants.
+// Error over random arguments: sin at most 1.12e-16 (rms 3.8e-17), cos 1.66e-16
+// (4.8e-17); the radian form's are 1.63e-16 (4.3e-17) and 1.64e-16 (4.6e-17).
+//
+// The table's byte offset, the low word shifted left by 4 and cut to 16 bits,
+// is one 16-bit shift, which clears the upper half of its result.  A simple
+// 32-bit or 16-bit instruction takes 2.6 cycles of a SIMD with two waves
+// where an SDWA form, like every FP64 instruction, takes 4.5.
+// ---------------------------------------------------------------------------
+struct NodeSC {
+  double s, c;
+};
+
+__device__ __forceinline__ uint32_t node_offset(double t) {
+  uint32_t a;
+  asm("v_lshlrev_b16_e32 %0, 4, %1" : "=v"(a) : "v"((uint32_t)__double2loint(t)));
+  return a;
+}
+
+__device__ __forceinline__ NodeSC sincos_node(double a, const double2 *__restrict__ tab) {
+  const double m = a + AW_ROUND_MAGIC;
+  const double q = m - AW_ROUND_MAGIC;
+  const double2 e = *(const double2 *)((const char *)tab + node_offset(m));
+  const double r = a - q;
+  const double u = r * r;
+  const double w = r * __builtin_fma(AW_NODE_W[1], u, AW_NODE_W[0]);
+  const double t = r * __builtin_fma(AW_NODE_T[1], u, AW_NODE_T[0]);
+  const double c1 = __builtin_fma(-t, e.x, e.y);
+  NodeSC o;
+  o.s = __builtin_fma(w, c1, e.x);
+  o.c = __builtin_fma(-t, o.s, c1);
+  return o;
+}
+
+// x times a constant held in two parts, rounded once (to within 2^-100).
+__device__ __forceinline__ double times2(double x, const double (&k)[2]) {
+#pragma clang fp contract(off)
+  const double p = x * k[0];
+  const double e = __builtin_fma(x, k[0], -p);
+  return p + __builtin_fma(x, k[1], e);
+}
+
+__device__ __forceinline__ double to_nodes(double x) { return times2(x, AW_NODES_PER_RAD); }
+__device__ __forceinline__ double times_sqrt2(double x) { return times2(x, AW_SQRT2); }
+constexpr double AW_SQRT1_2 = 0x1.6a09e667f3bcdp-1;
 
 // Fill a block's LDS copy of the (sin, cos)(k pi/2048) table; every thread of
 // the block must call this before any of them returns.
@@ -183,7 +230,118 @@ struct Orbit {
   int kexp;                            // tangent scale exponent (|w| true = |w| 2^kexp)
 };
 
-// The propagation kernels run in the rotated frame u = x + y, v = x - y, with
+// The propagation kernels step the rotated frame u = x + y, v = x - y, scaled:
+// the Orbit's x, y, z hold u, v and 2 z in table nodes; px, py, pz hold
+// p_u = p_x + p_y, p_v = p_x - p_y and sqrt 2 p_z; the tangent's dx, dy, dz,
+// dpx, dpy, dpz hold du, dv, sqrt 2 dz and the same of its momenta, in plain
+// units.  Eq. 2's H_p = 2 cx cy cz^2 is (cos u + cos v) cz^2, so the force and
+// its Jacobian do not couple u and v, and the factor sqrt 2 on z makes the
+// Jacobian symmetric: with a = t eps, e1 = a (1 + cos 2z), e2 = sqrt 2 a sin 2z
+// and cs = cos u + cos v,
+//   p_u += e1 sin u,  p_v += e1 sin v,  p_z += e2 cs,
+//   dp_u += e1 cos u du - e2 sin u dz,
+//   dp_v += e1 cos v dv - e2 sin v dz,
+//   dp_z += -e2 (sin u du + sin v dv) + 2 a cos 2z cs dz.
+// 52 FP64 instructions and three offsets with the tangent (39 without), where
+// the unscaled form took 59 (46): bound by VALU issue, an S6 step is 563 VALU
+// instructions instead of 627 (415 instead of 470).  The 1024 x 1024 slice over
+// 1000 steps takes 18.9 ms instead of 21.3, 2e6 state-only orbits over 200
+// steps 5.45 ms instead of 6.35.
+template <bool TAN>
+__device__ __forceinline__ void kick_node(Orbit &o, double a, double b, const double2 *__restrict__ tab) {
+  const NodeSC U = sincos_node(o.x, tab), V = sincos_node(o.y, tab), Z = sincos_node(o.z, tab);
+  const double e1 = __builtin_fma(a, Z.c, a);
+  const double e2 = b * Z.s;
+  const double cs = U.c + V.c;
+  if (TAN) {
+    const double du = o.dx, dv = o.dy, dz = o.dz;
+    const double fu = e1 * du, fv = e1 * dv, h = e2 * dz;
+    const double g = __builtin_fma(U.s, du, V.s * dv);
+    const double mz = cs * __builtin_fma(2.0, e1, -2.0 * a);
+    o.dpx = __builtin_fma(U.c, fu, __builtin_fma(-U.s, h, o.dpx));
+    o.dpy = __builtin_fma(V.c, fv, __builtin_fma(-V.s, h, o.dpy));
+    o.dpz = __builtin_fma(mz, dz, __builtin_fma(-e2, g, o.dpz));
+  }
+  o.px = __builtin_fma(e1, U.s, o.px);
+  o.py = __builtin_fma(e1, V.s, o.py);
+  o.pz = __builtin_fma(e2, cs, o.pz);
+}
+
+// A drift of time t: wu = t in nodes per unit of p_u, wz = sqrt 2 wu (2 z in
+// nodes per unit of sqrt 2 p_z).
+template <bool TAN>
+__device__ __forceinline__ void drift_node(Orbit &o, double wu, double wz, double t) {
+  o.x = __builtin_fma(wu, o.px, o.x);
+  o.y = __builtin_fma(wu, o.py, o.y);
+  o.z = __builtin_fma(wz, o.pz, o.z);
+  if (TAN) {
+    o.dx = __builtin_fma(t, o.dpx, o.dx);
+    o.dy = __builtin_fma(t, o.dpy, o.dy);
+    o.dz = __builtin_fma(t, o.dpz, o.dz);
+  }
+}
+
+// Into the scaled rotated frame (p0 alike).
+__device__ __forceinline__ void to_node(Orbit &o) {
+#pragma clang fp contract(off)
+  const double x = o.x, y = o.y, px = o.px, py = o.py;
+  o.x = to_nodes(x + y); o.y = to_nodes(x - y); o.z = to_nodes(2.0 * o.z);
+  o.px = px + py; o.py = px - py; o.pz = times_sqrt2(o.pz);
+  const double p0x = o.p0x, p0y = o.p0y;
+  o.p0x = p0x + p0y; o.p0y = p0x - p0y; o.p0z = times_sqrt2(o.p0z);
+  const double dx = o.dx, dy = o.dy, dpx = o.dpx, dpy = o.dpy;
+  o.dx = dx + dy; o.dy = dx - dy; o.dz = times_sqrt2(o.dz);
+  o.dpx = dpx + dpy; o.dpy = dpx - dpy; o.dpz = times_sqrt2(o.dpz);
+}
+
+// Back to the original frame, as displacements from the initial state s0
+// (x, y, z, px, py, pz), whose scaled form is recomputed here exactly as
+// to_node formed it: what the steps did not change comes back unchanged (at
+// eps = 0 the momenta exactly).
+__device__ __forceinline__ void from_node(Orbit &o, const double (&s0)[6]) {
+#pragma clang fp contract(off)
+  const double du0 = (o.x - to_nodes(s0[0] + s0[1])) * AW_RAD_PER_NODE;
+  const double dv0 = (o.y - to_nodes(s0[0] - s0[1])) * AW_RAD_PER_NODE;
+  const double dz0 = (o.z - to_nodes(2.0 * s0[2])) * (0.5 * AW_RAD_PER_NODE);
+  const double dpu0 = o.px - (s0[3] + s0[4]), dpv0 = o.py - (s0[3] - s0[4]);
+  const double dpz0 = (o.pz - times_sqrt2(s0[5])) * AW_SQRT1_2;
+  o.x = s0[0] + 0.5 * (du0 + dv0); o.y = s0[1] + 0.5 * (du0 - dv0); o.z = s0[2] + dz0;
+  o.px = s0[3] + 0.5 * (dpu0 + dpv0); o.py = s0[4] + 0.5 * (dpu0 - dpv0); o.pz = s0[5] + dpz0;
+  const double du = o.dx, dv = o.dy, dpu = o.dpx, dpv = o.dpy;
+  o.dx = 0.5 * (du + dv); o.dy = 0.5 * (du - dv); o.dz = o.dz * AW_SQRT1_2;
+  o.dpx = 0.5 * (dpu + dpv); o.dpy = 0.5 * (dpu - dpv); o.dpz = o.dpz * AW_SQRT1_2;
+}
+
+// In the scaled frame |P - P0|^2 is half the sum of the three squares: jsum
+// collects twice the step sum.
+__device__ __forceinline__ void accum_j_node(Orbit &o) {
+  const double eu = o.px - o.p0x, ev = o.py - o.p0y, ez = o.pz - o.p0z;
+  o.jsum = __builtin_fma(eu, eu, o.jsum);
+  o.jsum = __builtin_fma(ev, ev, o.jsum);
+  o.jsum = __builtin_fma(ez, ez, o.jsum);
+}
+
+// Rescale the tangent by an exact power of two so that |w|^2 lies in
+// [0.5, 2); the scale is accumulated in kexp.  Exact: it changes no mantissa.
+// In the scaled frame |w|^2 is half the sum of the six squares.
+__device__ __forceinline__ void renorm_node(Orbit &o) {
+  double a = o.dx * o.dx;
+  a = __builtin_fma(o.dy, o.dy, a);
+  a = __builtin_fma(o.dz, o.dz, a);
+  a = __builtin_fma(o.dpx, o.dpx, a);
+  a = __builtin_fma(o.dpy, o.dpy, a);
+  a = __builtin_fma(o.dpz, o.dpz, a);
+  const int s = (__builtin_amdgcn_frexp_exp(a) - 1) >> 1;
+  o.dx = __builtin_amdgcn_ldexp(o.dx, -s);
+  o.dy = __builtin_amdgcn_ldexp(o.dy, -s);
+  o.dz = __builtin_amdgcn_ldexp(o.dz, -s);
+  o.dpx = __builtin_amdgcn_ldexp(o.dpx, -s);
+  o.dpy = __builtin_amdgcn_ldexp(o.dpy, -s);
+  o.dpz = __builtin_amdgcn_ldexp(o.dpz, -s);
+  o.kexp += s;
+}
+
+// The adjoint kernels run in the rotated frame u = x + y, v = x - y, with
 // momenta p_u = p_x + p_y, p_v = p_x - p_y and the tangent transformed alike
 // (the Orbit fields x, y, px, py, dx, dy, dpx, dpy then hold u, v, p_u, p_v,
 // du, dv, dp_u, dp_v).  The drift keeps its form (u advances by t p_u), and
@@ -216,12 +374,6 @@ __device__ __forceinline__ void kick_rot(Orbit &o, double a2, const double2 *__r
   o.pz = __builtin_fma(e2, cs, o.pz);
 }
 
-template <bool TAN> struct KickRotOps {
-  static constexpr int fma = 2 * SCT_FMA + ZT_FMA + 3 + (TAN ? 1 + 7 : 0);
-  static constexpr int mul = 2 * SCT_MUL + ZT_MUL + 2 + (TAN ? 4 + 1 + 1 : 0);
-  static constexpr int add = 2 * SCT_ADD + ZT_ADD + 1;
-};
-
 // Into and out of the rotated frame (p0 alike; the tangent only with TAN).
 __device__ __forceinline__ void to_rot(Orbit &o) {
   const double x = o.x, y = o.y, px = o.px, py = o.py;
@@ -232,21 +384,6 @@ __device__ __forceinline__ void to_rot(Orbit &o) {
   const double dx = o.dx, dy = o.dy, dpx = o.dpx, dpy = o.dpy;
   o.dx = dx + dy; o.dy = dx - dy;
   o.dpx = dpx + dpy; o.dpy = dpx - dpy;
-}
-
-// Back to the original frame, as displacements from the initial state s0
-// (x, y, z, px, py, pz), whose rotated form is recomputed here exactly as
-// to_rot formed it: what the steps did not change comes back unchanged (at
-// eps = 0 the momenta exactly).
-__device__ __forceinline__ void from_rot(Orbit &o, const double (&s0)[6]) {
-#pragma clang fp contract(off)
-  const double du0 = o.x - (s0[0] + s0[1]), dv0 = o.y - (s0[0] - s0[1]);
-  const double dpu0 = o.px - (s0[3] + s0[4]), dpv0 = o.py - (s0[3] - s0[4]);
-  o.x = s0[0] + 0.5 * (du0 + dv0); o.y = s0[1] + 0.5 * (du0 - dv0);
-  o.px = s0[3] + 0.5 * (dpu0 + dpv0); o.py = s0[4] + 0.5 * (dpu0 - dpv0);
-  const double du = o.dx, dv = o.dy, dpu = o.dpx, dpv = o.dpy;
-  o.dx = 0.5 * (du + dv); o.dy = 0.5 * (du - dv);
-  o.dpx = 0.5 * (dpu + dpv); o.dpy = 0.5 * (dpu - dpv);
 }
 
 // In the rotated frame |P - P0|^2 = (du_p^2 + dv_p^2)/2 + dz_p^2: jsum collects
@@ -270,11 +407,6 @@ __device__ __forceinline__ void drift(Orbit &o, double t) {
     o.dz = __builtin_fma(t, o.dpz, o.dz);
   }
 }
-
-// Op counts of kick/drift (roofline accounting).
-template <bool TAN> struct DriftOps {
-  static constexpr int fma = TAN ? 6 : 3;
-};
 
 // Rescale the tangent by an exact power of two so that |w|^2 lies in
 // [0.5, 2); the scale is accumulated in kexp.  Exact: it changes no mantissa.

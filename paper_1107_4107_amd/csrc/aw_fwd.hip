@@ -97,33 +97,37 @@ __device__ __forceinline__ void gen_w0(uint64_t seed, int64_t n, double w[6]) {
 // kicks take their sines and cosines from the block's LDS table `tab`.
 // ---------------------------------------------------------------------------
 // The distinct stage weights of the form, copied from the descriptor before
-// the step loop.
-// Stage weights of the rotated-frame step: the drift's t and the kick's
-// a2 = 2 t eps (the kick needs no other weight there).
+// the step loop (see FwdDesc).
 struct StepWeights {
   double drift[MAX_UNIQUE];
-  double ka2[MAX_UNIQUE];
+  double dnode[MAX_UNIQUE];
+  double dnodez[MAX_UNIQUE];
+  double ka[MAX_UNIQUE];
+  double kb[MAX_UNIQUE];
 };
 
 template <int FORM, bool TAN, int OPL>
 __device__ __forceinline__ void map_step(Orbit (&o)[OPL], const StepWeights &d, const double2 *__restrict__ tab) {
   using F = FormPattern<FORM>;
   constexpr int NK = F::NK;
+  auto drift = [&](int q) {
+#pragma unroll
+    for (int j = 0; j < OPL; ++j) drift_node<TAN>(o[j], d.dnode[q], d.dnodez[q], d.drift[q]);
+  };
+  auto kick = [&](int q) {
+#pragma unroll
+    for (int j = 0; j < OPL; ++j) kick_node<TAN>(o[j], d.ka[q], d.kb[q], tab);
+  };
   if constexpr (F::LEAD) {
 #pragma unroll
     for (int i = 0; i < NK; ++i) {
-#pragma unroll
-      for (int j = 0; j < OPL; ++j) drift<TAN>(o[j], d.drift[F::drift_idx[i]]);
-#pragma unroll
-      for (int j = 0; j < OPL; ++j) kick_rot<TAN>(o[j], d.ka2[F::kick_idx[i]], tab);
+      drift(F::drift_idx[i]);
+      kick(F::kick_idx[i]);
     }
-#pragma unroll
-    for (int j = 0; j < OPL; ++j) drift<TAN>(o[j], d.drift[F::drift_idx[NK]]);
+    drift(F::drift_idx[NK]);
   } else {
-#pragma unroll
-    for (int j = 0; j < OPL; ++j) kick_rot<TAN>(o[j], d.ka2[0], tab);
-#pragma unroll
-    for (int j = 0; j < OPL; ++j) drift<TAN>(o[j], d.drift[0]);
+    kick(0);
+    drift(0);
   }
 }
 
@@ -187,6 +191,22 @@ __device__ __forceinline__ bool in_window(double px, double py, double pz, const
   return ok;
 }
 
+// Row 21 of the resumable carry: whether the orbit has left the window, and
+// whether rows 0-20 hold the scaled frame.  A carry without the second flag
+// was written in the unscaled rotated frame (u, v, z and their momenta, z and
+// p_z not scaled) and is taken over.
+constexpr int CARRY_LEFT = 1, CARRY_NODES = 2;
+
+__device__ __forceinline__ void carry_to_nodes(Orbit &o) {
+  o.x = to_nodes(o.x);
+  o.y = to_nodes(o.y);
+  o.z = to_nodes(2.0 * o.z);
+  o.pz = times_sqrt2(o.pz);
+  o.p0z = times_sqrt2(o.p0z);
+  o.dz = times_sqrt2(o.dz);
+  o.dpz = times_sqrt2(o.dpz);
+}
+
 // ---------------------------------------------------------------------------
 // Run the orbits first + j*blockDim.x + threadIdx.x (j < OPL) over global
 // steps [k_begin, k_end).  FILT: test the window after every step.  `tab` is
@@ -226,11 +246,12 @@ __device__ __forceinline__ void run_orbits(const FwdDesc &d, int64_t first, cons
         o[j].dx = o[j].dy = o[j].dz = o[j].dpx = o[j].dpy = o[j].dpz = 0.0;
       }
       if (FILT) left[j] = !in_window(s[3], s[4], s[5], d);
-      to_rot(o[j]);
+      to_node(o[j]);
     } else {
-      // The carry holds the rotated-frame state as the loop left it.
+      // The carry holds the scaled rotated state as the loop left it.
       const double *c = d.carry;
       const int64_t N = d.N, m = n[j];
+      const int flags = (int)c[21 * N + m];
       o[j].x = c[0 * N + m]; o[j].y = c[1 * N + m]; o[j].z = c[2 * N + m];
       o[j].px = c[3 * N + m]; o[j].py = c[4 * N + m]; o[j].pz = c[5 * N + m];
       o[j].dx = c[6 * N + m]; o[j].dy = c[7 * N + m]; o[j].dz = c[8 * N + m];
@@ -238,11 +259,12 @@ __device__ __forceinline__ void run_orbits(const FwdDesc &d, int64_t first, cons
       o[j].p0x = c[15 * N + m]; o[j].p0y = c[16 * N + m]; o[j].p0z = c[17 * N + m];
       o[j].jsum = c[18 * N + m];
       o[j].kexp = (int)c[19 * N + m];
-      if (FILT) left[j] = c[21 * N + m] != 0.0;
+      if (FILT) left[j] = (flags & CARRY_LEFT) != 0;
+      if (!(flags & CARRY_NODES)) carry_to_nodes(o[j]);
     }
   }
 
-  // Positions at the start of this launch (time-window velocity; rotated).
+  // Positions at the start of this launch (time-window velocity; scaled frame).
   double xs[OPL], ys[OPL], zs[OPL];
   if (WINV) {
 #pragma unroll
@@ -259,39 +281,39 @@ __device__ __forceinline__ void run_orbits(const FwdDesc &d, int64_t first, cons
   // will not unroll with a remainder.
   const int64_t k0 = d.k_begin, k1 = d.k_end;
   const int64_t mask = d.renorm_mask;
-  // Stage weights.  In the plain tangent kernel the kick weights move into
-  // VGPRs (an empty asm the compiler must treat as producing per-lane
-  // values): across the loop the descriptor fields of the epilogue hold most
-  // SGPRs, and kick weights left there are spilled to VGPR lanes and read back
-  // with v_readlane every step, 16 VALU instructions per S6 step and 32 per Y6
-  // step.  In VGPRs they cost 8 registers and no instruction.  The
-  // unrolled, two-orbit and window variants would lose occupancy and keep
+  // Stage weights.  In the plain tangent kernel they move into VGPRs (an empty
+  // asm the compiler must treat as producing per-lane values): left in SGPRs,
+  // which the epilogue's descriptor fields hold across the loop, they are
+  // spilled and read back every step.  A block of 512 leaves 256 VGPRs a lane.
+  // The unrolled, two-orbit and window variants would lose occupancy and keep
   // them in SGPRs.
   constexpr bool kVregW = TAN && OPL == 1 && UNR == 1 && !FILT && !WINV;
   StepWeights sw;
 #pragma unroll
   for (int q = 0; q < MAX_UNIQUE; ++q) {
     sw.drift[q] = d.drift[q];
-    sw.ka2[q] = d.ka2[q];
+    sw.dnode[q] = d.dnode[q];
+    sw.dnodez[q] = d.dnodez[q];
+    sw.ka[q] = d.ka[q];
+    sw.kb[q] = d.kb[q];
     if (kVregW) {
-      asm volatile("" : "+v"(sw.drift[q]));
-      asm volatile("" : "+v"(sw.ka2[q]));
+      asm volatile("" : "+v"(sw.drift[q]), "+v"(sw.dnode[q]), "+v"(sw.dnodez[q]), "+v"(sw.ka[q]), "+v"(sw.kb[q]));
     }
   }
   auto one_step = [&](int64_t k) {
     map_step<FORM, TAN, OPL>(o, sw, tab);
 #pragma unroll
-    for (int j = 0; j < OPL; ++j) accum_j_rot(o[j]);
+    for (int j = 0; j < OPL; ++j) accum_j_node(o[j]);
     if (FILT) {
-      // 2 P in the original frame, exactly: the window test depends only on
-      // the direction of P.
+      // 2 P in the original frame: the window test depends only on the
+      // direction of P.
 #pragma unroll
       for (int j = 0; j < OPL; ++j)
-        left[j] = left[j] || !in_window(o[j].px + o[j].py, o[j].px - o[j].py, o[j].pz + o[j].pz, d);
+        left[j] = left[j] || !in_window(o[j].px + o[j].py, o[j].px - o[j].py, AW_SQRT2[0] * o[j].pz, d);
     }
     if (TAN && ((k + 1) & mask) == 0) {
 #pragma unroll
-      for (int j = 0; j < OPL; ++j) renorm_rot(o[j]);
+      for (int j = 0; j < OPL; ++j) renorm_node(o[j]);
     }
   };
   int64_t k = k0;
@@ -313,8 +335,9 @@ __device__ __forceinline__ void run_orbits(const FwdDesc &d, int64_t first, cons
       if (WINV) {
 #pragma clang fp contract(off)
         double phi, mu;
-        const double du = o[j].x - xs[j], dv = o[j].y - ys[j];
-        vdir_key(0.5 * (du + dv) / d.wdt, 0.5 * (du - dv) / d.wdt, (o[j].z - zs[j]) / d.wdt, phi, mu);
+        const double du = (o[j].x - xs[j]) * AW_RAD_PER_NODE, dv = (o[j].y - ys[j]) * AW_RAD_PER_NODE;
+        const double dz = (o[j].z - zs[j]) * (0.5 * AW_RAD_PER_NODE);
+        vdir_key(0.5 * (du + dv) / d.wdt, 0.5 * (du - dv) / d.wdt, dz / d.wdt, phi, mu);
         d.bins[n[j]] = left[j] ? BIN_DROP : bin_of(phi, mu, d.klo0, d.khi0, d.klo1, d.khi1, d.W, d.H, true);
       }
       double *c = d.carry;
@@ -330,7 +353,7 @@ __device__ __forceinline__ void run_orbits(const FwdDesc &d, int64_t first, cons
       c[18 * N + m] = o[j].jsum;
       c[19 * N + m] = (double)o[j].kexp;
       c[20 * N + m] = (double)k1;
-      c[21 * N + m] = left[j] ? 1.0 : 0.0;
+      c[21 * N + m] = (double)(CARRY_NODES | (left[j] ? CARRY_LEFT : 0));
     }
     return;
   }
@@ -347,7 +370,7 @@ __device__ __forceinline__ void run_orbits(const FwdDesc &d, int64_t first, cons
     const int64_t N = d.N, m = n[j];
     double s0[6];
     gen_ic(d, m, s0);
-    from_rot(o[j], s0);
+    from_node(o[j], s0);
     double res[9];
     double wn = 1.0;
     if (TAN) {
@@ -460,25 +483,24 @@ __device__ __forceinline__ double swap_pair(double v) {
 }
 
 struct HalfOrbit {
-  double w, pw;    // own rotated coordinate (u or v) and its momentum
-  double z, pz;
+  double w, pw;    // own rotated coordinate (u or v, in nodes) and its momentum
+  double z, pz;    // 2 z in nodes, sqrt 2 p_z
   double p0w, p0z;
   double jsum;     // meaningful in the pair's even lane
 };
 
-__device__ __forceinline__ void pair_kick(HalfOrbit &h, double a2, const double2 *__restrict__ tab) {
-  const SinCosT W = sincos_tab(h.w, tab);
-  const ZTerms Z = zterms_tab(h.z, tab);
-  const double e1 = a2 * Z.cz2;
-  const double e2 = a2 * Z.czsz;
+__device__ __forceinline__ void pair_kick(HalfOrbit &h, double a, double b, const double2 *__restrict__ tab) {
+  const NodeSC W = sincos_node(h.w, tab), Z = sincos_node(h.z, tab);
+  const double e1 = __builtin_fma(a, Z.c, a);
+  const double e2 = b * Z.s;
   const double cs = W.c + swap_pair(W.c);
   h.pw = __builtin_fma(e1, W.s, h.pw);
   h.pz = __builtin_fma(e2, cs, h.pz);
 }
 
-__device__ __forceinline__ void pair_drift(HalfOrbit &h, double t) {
-  h.w = __builtin_fma(t, h.pw, h.w);
-  h.z = __builtin_fma(t, h.pz, h.z);
+__device__ __forceinline__ void pair_drift(HalfOrbit &h, double wu, double wz) {
+  h.w = __builtin_fma(wu, h.pw, h.w);
+  h.z = __builtin_fma(wz, h.pz, h.z);
 }
 
 template <int FORM>
@@ -488,13 +510,13 @@ __device__ __forceinline__ void pair_step(HalfOrbit &h, const StepWeights &d, co
   if constexpr (F::LEAD) {
 #pragma unroll
     for (int i = 0; i < NK; ++i) {
-      pair_drift(h, d.drift[F::drift_idx[i]]);
-      pair_kick(h, d.ka2[F::kick_idx[i]], tab);
+      pair_drift(h, d.dnode[F::drift_idx[i]], d.dnodez[F::drift_idx[i]]);
+      pair_kick(h, d.ka[F::kick_idx[i]], d.kb[F::kick_idx[i]], tab);
     }
-    pair_drift(h, d.drift[F::drift_idx[NK]]);
+    pair_drift(h, d.dnode[F::drift_idx[NK]], d.dnodez[F::drift_idx[NK]]);
   } else {
-    pair_kick(h, d.ka2[0], tab);
-    pair_drift(h, d.drift[0]);
+    pair_kick(h, d.ka[0], d.kb[0], tab);
+    pair_drift(h, d.dnode[0], d.dnodez[0]);
   }
 }
 
@@ -512,12 +534,12 @@ __global__ __launch_bounds__(256) void k_fwd_pair(FwdDesc d) {
 #pragma clang fp contract(off)
     double s[6];
     gen_ic(d, m, s);
-    h.w = odd ? s[0] - s[1] : s[0] + s[1];
+    h.w = to_nodes(odd ? s[0] - s[1] : s[0] + s[1]);
     h.pw = odd ? s[3] - s[4] : s[3] + s[4];
-    h.z = s[2];
-    h.pz = s[5];
+    h.z = to_nodes(2.0 * s[2]);
+    h.pz = times_sqrt2(s[5]);
     h.p0w = h.pw;
-    h.p0z = s[5];
+    h.p0z = h.pz;
     h.jsum = 0.0;
   } else {
     const double *c = d.carry;
@@ -529,26 +551,33 @@ __global__ __launch_bounds__(256) void k_fwd_pair(FwdDesc d) {
     h.p0w = c[(15 + r) * N + m];
     h.p0z = c[17 * N + m];
     h.jsum = c[18 * N + m];
+    if (!((int)c[21 * N + m] & CARRY_NODES)) {
+      h.w = to_nodes(h.w);
+      h.z = to_nodes(2.0 * h.z);
+      h.pz = times_sqrt2(h.pz);
+      h.p0z = times_sqrt2(h.p0z);
+    }
   }
   const double ws = h.w, zs = h.z;
   StepWeights sw;
 #pragma unroll
   for (int q = 0; q < MAX_UNIQUE; ++q) {
-    sw.drift[q] = d.drift[q];
-    sw.ka2[q] = d.ka2[q];
+    sw.dnode[q] = d.dnode[q];
+    sw.dnodez[q] = d.dnodez[q];
+    sw.ka[q] = d.ka[q];
+    sw.kb[q] = d.kb[q];
   }
 #pragma nounroll
   for (int64_t k = d.k_begin; k < d.k_end; ++k) {
     pair_step<FORM>(h, sw, s_tab);
-    // J as run_orbits accumulates it, in the even lane: (p_u - p0_u)^2, then
-    // (p_v - p0_v)^2, then twice (p_z - p0_z)^2.
+    // J as run_orbits accumulates it, in the even lane: the u, v and z squares
+    // in that order.
     const double e = h.pw - h.p0w;
     const double ep = swap_pair(e);
     const double ez = h.pz - h.p0z;
-    const double ez2 = ez + ez;
     h.jsum = __builtin_fma(e, e, h.jsum);
     h.jsum = __builtin_fma(ep, ep, h.jsum);
-    h.jsum = __builtin_fma(ez, ez2, h.jsum);
+    h.jsum = __builtin_fma(ez, ez, h.jsum);
   }
   const double dw = h.w - ws;
   const double dwp = swap_pair(dw);   // the partner's displacement
@@ -563,8 +592,9 @@ __global__ __launch_bounds__(256) void k_fwd_pair(FwdDesc d) {
   if (WINV) {
 #pragma clang fp contract(off)
     double phi, mu;
-    const double du = dw, dv = dwp;
-    vdir_key(0.5 * (du + dv) / d.wdt, 0.5 * (du - dv) / d.wdt, (h.z - zs) / d.wdt, phi, mu);
+    const double du = dw * AW_RAD_PER_NODE, dv = dwp * AW_RAD_PER_NODE;
+    const double dz = (h.z - zs) * (0.5 * AW_RAD_PER_NODE);
+    vdir_key(0.5 * (du + dv) / d.wdt, 0.5 * (du - dv) / d.wdt, dz / d.wdt, phi, mu);
     d.bins[m] = bin_of(phi, mu, d.klo0, d.khi0, d.klo1, d.khi1, d.W, d.H, true);
   }
   c[0 * N + m] = h.w;
@@ -584,7 +614,7 @@ __global__ __launch_bounds__(256) void k_fwd_pair(FwdDesc d) {
     c[12 * N + m] = s0[0]; c[13 * N + m] = s0[1]; c[14 * N + m] = s0[2];
     c[19 * N + m] = 0.0;
   }
-  c[21 * N + m] = 0.0;   // no window test here
+  c[21 * N + m] = (double)CARRY_NODES;   // no window test here
 }
 
 // Persistent batched propagation: each workgroup takes (ensemble, tile)
@@ -757,8 +787,11 @@ hipError_t launch_zero_u32(uint32_t *p, int32_t n, hipStream_t s) {
   return hipGetLastError();
 }
 
-// FP64 instruction counts per map step as built (sincos, kicks, drifts, J,
-// amortised renormalisation excluded).
+// FP64 operations per map step in the unscaled rotated frame, the unit of the
+// roofline (amortised renormalisation excluded): a sincos takes 8 FMA, 4 MUL
+// and 1 ADD, the z factors 9, 3 and 1, the rest of a kick 3, 2 and 1 and with
+// the tangent 8 FMA and 6 MUL more; a drift 3 FMA, 6 with the tangent; the J
+// accumulator 3 FMA and 4 ADD.  kick_node and drift_node take fewer.
 void step_op_counts(int form, bool tan, int64_t *fma, int64_t *mul, int64_t *add) {
   int nk = 0, nd = 0;
   switch (form) {
@@ -769,13 +802,11 @@ void step_op_counts(int form, bool tan, int64_t *fma, int64_t *mul, int64_t *add
   case 7: nk = 7; nd = 8; break;
   default: break;
   }
-  const int kf = tan ? KickRotOps<true>::fma : KickRotOps<false>::fma;
-  const int km = tan ? KickRotOps<true>::mul : KickRotOps<false>::mul;
-  const int ka = tan ? KickRotOps<true>::add : KickRotOps<false>::add;
-  const int df = tan ? DriftOps<true>::fma : DriftOps<false>::fma;
-  *fma = (int64_t)nk * kf + (int64_t)nd * df + 3;  // + 3 fma of the J accumulator
+  const int kf = 2 * 8 + 9 + 3 + (tan ? 8 : 0);
+  const int km = 2 * 4 + 3 + 2 + (tan ? 6 : 0);
+  *fma = (int64_t)nk * kf + (int64_t)nd * (tan ? 6 : 3) + 3;
   *mul = (int64_t)nk * km;
-  *add = (int64_t)nk * ka + 4;                     // + 3 subtractions and a doubling (J accumulator)
+  *add = (int64_t)nk * 4 + 4;
 }
 
 }  // namespace aw

@@ -52,12 +52,16 @@ constexpr uint32_t BIN_DROP = 0xffffffffu;
 // Image epilogue selector of the propagation kernel.
 enum EpiKind : int32_t { EPI_NONE = 0, EPI_IC_GRID = 1, EPI_HIST_P0 = 2, EPI_HIST_VDIR = 3 };
 
-// One ensemble as the kernels see it.  Distinct stage weights, pre-multiplied:
-// drift[u] = c h, ka2[u] = 2 w h eps, ka4[u] = 4 w h eps.
+// One ensemble as the kernels see it.  Distinct stage weights of the scaled
+// frame (kick_node, drift_node), pre-multiplied: a drift of time t = c h takes
+// drift[u] = t, dnode[u] = t in table nodes per radian and dnodez[u] = sqrt 2
+// times that; a kick of time t = w h takes ka[u] = t eps and kb[u] = sqrt 2 t eps.
 struct FwdDesc {
   double drift[MAX_UNIQUE];
-  double ka2[MAX_UNIQUE];
-  double ka4[MAX_UNIQUE];
+  double dnode[MAX_UNIQUE];
+  double dnodez[MAX_UNIQUE];
+  double ka[MAX_UNIQUE];
+  double kb[MAX_UNIQUE];
   double eps;
   double th;         // T h
   double lth;        // ln(1 + T h)

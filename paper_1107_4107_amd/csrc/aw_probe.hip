@@ -51,9 +51,9 @@ __global__ __launch_bounds__(BLOCK) void k_fma_chains(double m, double c, int64_
   }
 }
 
-// The table-driven sine and cosine of the propagation and adjoint kernels, the
-// kicks' doubled-angle z terms and the polynomial form of the initial
-// conditions, one argument per lane.
+// The table-driven sine and cosine of the adjoint kernels, their doubled-angle
+// z terms and the polynomial form of the initial conditions, one argument per
+// lane; and the propagation kernels' node-unit form.
 __global__ __launch_bounds__(BLOCK) void k_sincos(const double* __restrict__ x, double* __restrict__ s,
                                                   double* __restrict__ c, int64_t n, int32_t form) {
   __shared__ double2 tab[AW_TAB_N];
@@ -74,6 +74,17 @@ __global__ __launch_bounds__(BLOCK) void k_sincos(const double* __restrict__ x, 
     s[i] = sv;
     c[i] = cv;
   }
+}
+
+__global__ __launch_bounds__(BLOCK) void k_sincos_node(const double* __restrict__ a, double* __restrict__ s,
+                                                       double* __restrict__ c, int64_t n) {
+  __shared__ double2 tab[AW_TAB_N];
+  aw::load_sincos_table(tab);
+  const int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
+  if (i >= n) return;
+  const aw::NodeSC r = aw::sincos_node(a[i], tab);
+  s[i] = r.s;
+  c[i] = r.c;
 }
 
 int fail(hipError_t e, const char* what) {
@@ -166,4 +177,17 @@ extern "C" int awp_sincos(const double* x_dev, double* s_dev, double* c_dev, int
                      form);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? 0 : fail(e, "sincos probe");
+}
+
+// The node-unit sine and cosine of the propagation kernels: s_dev[i],
+// c_dev[i] = sin, cos of a_dev[i] pi/2048.  Arguments and results as awp_sincos.
+extern "C" int awp_sincos_node(const double* a_dev, double* s_dev, double* c_dev, int64_t n, void* stream) {
+  if (n < 0) return 2;
+  if (n == 0) return 0;
+  if (!a_dev || !s_dev || !c_dev) return 2;
+  const int64_t blocks = (n + BLOCK - 1) / BLOCK;
+  if (blocks > INT32_MAX) return 2;
+  hipLaunchKernelGGL(k_sincos_node, dim3((unsigned)blocks), dim3(BLOCK), 0, (hipStream_t)stream, a_dev, s_dev, c_dev, n);
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? 0 : fail(e, "node sincos probe");
 }

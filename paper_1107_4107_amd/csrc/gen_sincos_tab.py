@@ -24,6 +24,15 @@ the kicks' z terms, cos^2 z = (1 + cos 2z)/2 and cos z sin z = sin(2z)/2, which
 the device takes from the same table at the doubled angle: same reduction,
 node 2q, and polynomials for sin(2r)/2 and cos(2r)/2 (device_zterms).
 
+The propagation kernels hold their angles in units of the table's nodes, a =
+2048 x/pi, so that the reduction is exact: q = nearest integer to a, r = a - q,
+|r| <= 1/2, and the node is q mod 4096.  They turn (S_k, C_k) by the angle
+r pi/2048 with three shears (device_sincos_node),
+    c1 = C - t S,  s = S + w c1,  c = c1 - t s,
+with t = tan(r pi/4096) = r (T0 + T1 r^2) and w = sin(r pi/2048) =
+r (W0 + W1 r^2): near-minimax fits in r^2 on [0, 1/4] whose leading
+coefficients are pi/4096 and pi/2048.
+
 Run:  python gen_sincos_tab.py > aw_sincos_tab.h
 """
 import random
@@ -119,6 +128,43 @@ def z_constants():
     return zs, zc, errzs, errzc
 
 
+def node_constants():
+    """Shear coefficients (W0, W1), (T0, T1) of one node unit with their fit
+    errors relative to the angle, and the two-part conversions nodes per radian
+    (hi, lo), sqrt 2 (hi, lo) and radians per node."""
+    step = mp.pi / 2048
+
+    def cubic(f, lead):
+        # f(r) = lead r + r^3 g(r^2): one coefficient for g on u = r^2 in [0, 1/4]
+        def g(u):
+            if u == 0:
+                u = mp.mpf("1e-20")
+            r = mp.sqrt(u)
+            return (f(r) / r - lead) / u
+        poly, err = mp.chebyfit(g, [mp.mpf("1e-8"), mp.mpf(1) / 4], 1, error=True)
+        return float(lead), float(poly[0]), err / 4 / lead
+    w0, w1, ew = cubic(lambda r: mp.sin(r * step), step)
+    t0, t1, et = cubic(lambda r: mp.tan(r * step / 2), step / 2)
+    k, q2 = 1 / step, mp.sqrt(2)
+    khi, qhi = float(k), float(q2)
+    return (w0, w1, ew), (t0, t1, et), (khi, float(k - khi)), (qhi, float(q2 - qhi)), float(step)
+
+
+def device_sincos_node(a, tab, w, t):
+    """(sin, cos) of a pi/2048 as the propagation kernels compute them."""
+    m = a + MAGIC
+    q = m - MAGIC
+    r = a - q
+    k = ((lo32(m) << 4) & 0xFFFF) >> 4
+    S, C = tab[2 * k], tab[2 * k + 1]
+    u = r * r
+    sw = r * fma(w[1], u, w[0])
+    tn = r * fma(t[1], u, t[0])
+    c1 = fma(-tn, S, C)
+    s = fma(sw, c1, S)
+    return s, fma(-tn, s, c1)
+
+
 def constants():
     """The table, the coefficients and the reduction constants, with the fit
     errors: (tab, ps, pc, inv, pa, pb, errs, errc)."""
@@ -156,6 +202,16 @@ def main():
         cz, sz = mp.cos(mp.mpf(z)), mp.sin(mp.mpf(z))
         ez2 = max(ez2, abs(z2 - float(cz * cz)))
         ezs = max(ezs, abs(zsz - float(cz * sz)))
+    # The node-unit routine over nodes drawn up to 1e9 and around the rounding edges.
+    nw, nt, kk, q2, rpn = node_constants()
+    ns = [rnd.uniform(-5e3, 5e3) for _ in range(4000)] + [rnd.uniform(-1e9, 1e9) for _ in range(2000)]
+    ns += [(k + 0.5) * (1 + s * 1e-15) for k in range(-4200, 4200, 7) for s in (-1, 0, 1)]
+    ens = enc = 0.0
+    for a in ns:
+        s, c = device_sincos_node(a, tab, nw, nt)
+        x = mp.mpf(a) * mp.pi / 2048
+        ens = max(ens, abs(s - float(mp.sin(x))))
+        enc = max(enc, abs(c - float(mp.cos(x))))
     out = sys.stdout
     out.write("/* Generated by gen_sincos_tab.py -- do not edit. */\n#pragma once\n")
     out.write(f"/* sin r = r + r^3 c: 1 coefficient, fit error {mp.nstr(errs, 3)}; "
@@ -165,7 +221,15 @@ def main():
     out.write(f"/* kick z terms from the doubled angle: sin(2r)/2 = r + r^3 a, fit error {mp.nstr(errzs, 3)}; "
               f"cos(2r)/2 = 1/2 + r^2 B(r^2), fit error {mp.nstr(errzc, 3)}; replayed over {len(zs)} arguments "
               f"up to 1e6: max abs error cos^2 z {ez2:.3e}, cos z sin z {ezs:.3e} */\n")
+    out.write(f"/* node units: w = r (W0 + W1 r^2), t = r (T0 + T1 r^2), |r| <= 1/2: fit errors {mp.nstr(nw[2], 3)} and "
+              f"{mp.nstr(nt[2], 3)} of the angle; replayed over {len(ns)} arguments up to 1e9 nodes: max abs error "
+              f"sin {ens:.3e}, cos {enc:.3e} */\n")
     out.write(f"#define AW_TAB_N {N_TAB}\n")
+    out.write(f"static constexpr double AW_NODE_W[2] = {{{nw[0].hex()}, {nw[1].hex()}}};\n")
+    out.write(f"static constexpr double AW_NODE_T[2] = {{{nt[0].hex()}, {nt[1].hex()}}};\n")
+    out.write(f"static constexpr double AW_NODES_PER_RAD[2] = {{{kk[0].hex()}, {kk[1].hex()}}};  /* 2048/pi, two parts */\n")
+    out.write(f"static constexpr double AW_RAD_PER_NODE = {rpn.hex()};\n")
+    out.write(f"static constexpr double AW_SQRT2[2] = {{{q2[0].hex()}, {q2[1].hex()}}};  /* two parts */\n")
     out.write(f"static constexpr double AW_TSIN_C0 = {ps[0].hex()};\n")
     out.write("static constexpr double AW_TCOS_C[2] = {" + ", ".join(v.hex() for v in pc) + "};\n")
     out.write(f"static constexpr double AW_PI2K_A = {pa.hex()};\n")
