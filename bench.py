@@ -60,7 +60,7 @@ FP64_ACHIEVABLE_TFLOPS = 76.92
 KICKS_PER_STEP = {"stdmap": 1, "s2": 1, "s4": 3, "s6": 9, "y6": 7}
 KERNEL_SOURCES = ["paper_1107_4107_amd/csrc/aw_fwd.hip", "paper_1107_4107_amd/csrc/aw_device.hpp",
                   "paper_1107_4107_amd/csrc/aw_sincos_coef.h", "paper_1107_4107_amd/csrc/aw_sincos_tab.h",
-                  "paper_1107_4107_amd/csrc/aw_internal.hpp"]
+                  "paper_1107_4107_amd/csrc/aw_internal.hpp", "paper_1107_4107_amd/csrc/aw_step.hpp"]
 METRIC = "orbit map-steps/sec (with tangent map)"
 
 

@@ -17,10 +17,11 @@
 // and the source of J, (2 gJ / T)(P_k - P_0), enters Pbar at every step
 // boundary k >= 1.  The explicit P_0 dependence of J adds
 // -(2 gJ / T) sum_k (P_k - P_0) to the initial-momentum gradient.
-// All of it runs in the rotated frame of the forward kernels (u = x + y,
-// v = x - y, momenta alike), where the kick's Jacobian has 7 non-zero entries;
-// the checkpoints and step states hold rotated states, and the gradient is
-// taken back to (x, y) at the end.
+// All of it runs in the scaled rotated frame of the forward kernels
+// (kick_node), where the kick's Jacobian has 7 non-zero entries and is
+// symmetric; the checkpoints and step states hold scaled states, the adjoint
+// that of (u, v, sqrt 2 z) and their momenta, and the gradient is taken back to
+// (x, y, z) at the end.
 // Each lane only reads back what it wrote itself, so no synchronisation
 // between lanes is needed.
 //
@@ -35,24 +36,15 @@
 #include "aw_device.hpp"
 #include "aw_internal.hpp"
 #include "aw_launch.hpp"
+#include "aw_step.hpp"
 
 namespace aw {
 
 template <int FORM>
 __device__ __forceinline__ void adj_step_fwd(Orbit &o, const AdjDesc &d, const double2 *__restrict__ tab) {
-  using F = FormPattern<FORM>;
-  constexpr int NK = F::NK;
-  if constexpr (F::LEAD) {
-#pragma unroll
-    for (int i = 0; i < NK; ++i) {
-      drift<false>(o, d.drift[F::drift_idx[i]]);
-      kick_rot<false>(o, d.ka2[F::kick_idx[i]], tab);
-    }
-    drift<false>(o, d.drift[F::drift_idx[NK]]);
-  } else {
-    kick_rot<false>(o, d.ka2[0], tab);
-    drift<false>(o, d.drift[0]);
-  }
+  Orbit t[1] = {o};
+  map_step<FORM, false, 1>(t, d.w, tab);
+  o = t[0];
 }
 
 struct Adjoint {
@@ -60,48 +52,49 @@ struct Adjoint {
 };
 
 // Undo D(t) on the state and apply its transpose to the adjoint.
-__device__ __forceinline__ void rev_drift(Orbit &o, Adjoint &a, double t) {
-  o.x = __builtin_fma(-t, o.px, o.x);
-  o.y = __builtin_fma(-t, o.py, o.y);
-  o.z = __builtin_fma(-t, o.pz, o.z);
+__device__ __forceinline__ void rev_drift(Orbit &o, Adjoint &a, double wu, double wz, double t) {
+  o.x = __builtin_fma(-wu, o.px, o.x);
+  o.y = __builtin_fma(-wu, o.py, o.y);
+  o.z = __builtin_fma(-wz, o.pz, o.z);
   a.pxb = __builtin_fma(t, a.xb, a.pxb);
   a.pyb = __builtin_fma(t, a.yb, a.pyb);
   a.pzb = __builtin_fma(t, a.zb, a.pzb);
 }
 
-// Undo K(t) on the state and apply its transpose to the adjoint, in the
-// rotated frame of the forward kernels (u = x + y, v = x - y; the Adjoint's
-// xb, yb, pxb, pyb hold the adjoints of u, v, p_u, p_v).  a2 = 2 t eps,
-// w2 = 2 t.  With e1 = a2 cz^2, e2 = a2 cz sz, cs = cos u + cos v the kick is
-// F = (e1 sin u, e1 sin v, e2 cs) and its Jacobian
-//   [[e1 cos u, 0, -2 e2 sin u], [0, e1 cos v, -2 e2 sin v],
-//    [-e2 sin u, -e2 sin v, cs (2 e1 - a2)]],
-// whose transpose acts on Pbar; dF/deps = F / eps.  For eps != 0 (EPS0
-// false) a.eb collects eps epsbar = F . Pbar and the kernel divides by eps
-// once at the end; for eps = 0 (EPS0 true) F / eps is formed from w2 = 2 t.
+// Undo K(t) on the state and apply its transpose to the adjoint, in the scaled
+// frame of the forward kernels (the Adjoint's fields hold the adjoints of u, v,
+// sqrt 2 z and their momenta).  With a = t eps, e1 = a (1 + cos 2z),
+// e2 = sqrt 2 a sin 2z and cs = cos u + cos v the kick is
+// F = (e1 sin u, e1 sin v, e2 cs) and its symmetric Jacobian
+//   [[e1 cos u, 0, -e2 sin u], [0, e1 cos v, -e2 sin v],
+//    [-e2 sin u, -e2 sin v, 2 a cos 2z cs]]
+// acts on Pbar; dF/deps = F / eps.  For eps != 0 (EPS0 false) a.eb collects
+// eps epsbar = F . Pbar and the kernel divides by eps once at the end; for
+// eps = 0 (EPS0 true) F / eps is formed from the kick's time t, sqrt 2 t.
 // Sines and cosines from the same table as the forward kick, so the undone
-// kick matches it.
+// kick matches it.  54 FP64 instructions (62 in the unscaled frame).
 template <bool EPS0>
-__device__ __forceinline__ void rev_kick(Orbit &o, Adjoint &a, double a2, double w2,
+__device__ __forceinline__ void rev_kick(Orbit &o, Adjoint &a, double ka, double kb, double kt, double ktb,
                                          const double2 *__restrict__ tab) {
-  const SinCosT U = sincos_tab(o.x, tab), V = sincos_tab(o.y, tab);
-  const ZTerms Z = zterms_tab(o.z, tab);
-  const double e1 = a2 * Z.cz2, e2 = a2 * Z.czsz;
+  const NodeSC U = sincos_node(o.x, tab), V = sincos_node(o.y, tab), Z = sincos_node(o.z, tab);
+  const double e1 = __builtin_fma(ka, Z.c, ka);
+  const double e2 = kb * Z.s;
   const double cs = U.c + V.c;
   const double pub = a.pxb, pvb = a.pyb, pzb = a.pzb;
   const double q = __builtin_fma(U.s, pub, V.s * pvb);   // sin u pu_bar + sin v pv_bar
+  const double h = e2 * pzb;
   if constexpr (EPS0) {
-    a.eb = __builtin_fma(w2 * Z.cz2, q, a.eb);
-    a.eb = __builtin_fma((w2 * Z.czsz) * cs, pzb, a.eb);
+    a.eb = __builtin_fma(__builtin_fma(kt, Z.c, kt), q, a.eb);
+    a.eb = __builtin_fma((ktb * Z.s) * pzb, cs, a.eb);
   } else {
     a.eb = __builtin_fma(e1, q, a.eb);
-    a.eb = __builtin_fma(e2 * cs, pzb, a.eb);
+    a.eb = __builtin_fma(h, cs, a.eb);
   }
-  const double e2p = e2 * pzb;
-  a.xb = __builtin_fma(e1 * U.c, pub, __builtin_fma(-U.s, e2p, a.xb));
-  a.yb = __builtin_fma(e1 * V.c, pvb, __builtin_fma(-V.s, e2p, a.yb));
-  const double mz = cs * __builtin_fma(2.0, e1, -a2);
-  a.zb = __builtin_fma(mz, pzb, __builtin_fma(-2.0 * e2, q, a.zb));
+  const double fu = e1 * pub, fv = e1 * pvb;
+  a.xb = __builtin_fma(U.c, fu, __builtin_fma(-U.s, h, a.xb));
+  a.yb = __builtin_fma(V.c, fv, __builtin_fma(-V.s, h, a.yb));
+  const double mz = cs * __builtin_fma(2.0, e1, -2.0 * ka);
+  a.zb = __builtin_fma(mz, pzb, __builtin_fma(-e2, q, a.zb));
   // P before the kick.
   o.px = __builtin_fma(-e1, U.s, o.px);
   o.py = __builtin_fma(-e1, V.s, o.py);
@@ -112,17 +105,18 @@ template <int FORM, bool EPS0>
 __device__ __forceinline__ void adj_step_rev(Orbit &o, Adjoint &a, const AdjDesc &d, const double2 *__restrict__ tab) {
   using F = FormPattern<FORM>;
   constexpr int NK = F::NK;
+  auto drift = [&](int q) { rev_drift(o, a, d.w.dnode[q], d.w.dnodez[q], d.w.drift[q]); };
+  auto kick = [&](int q) { rev_kick<EPS0>(o, a, d.w.ka[q], d.w.kb[q], d.kt[q], d.ktb[q], tab); };
   if constexpr (F::LEAD) {
-    rev_drift(o, a, d.drift[F::drift_idx[NK]]);
+    drift(F::drift_idx[NK]);
 #pragma unroll
     for (int i = NK - 1; i >= 0; --i) {
-      const int u = F::kick_idx[i];
-      rev_kick<EPS0>(o, a, d.ka2[u], d.kw2[u], tab);
-      rev_drift(o, a, d.drift[F::drift_idx[i]]);
+      kick(F::kick_idx[i]);
+      drift(F::drift_idx[i]);
     }
   } else {
-    rev_drift(o, a, d.drift[0]);
-    rev_kick<EPS0>(o, a, d.ka2[0], d.kw2[0], tab);
+    drift(0);
+    kick(0);
   }
 }
 
@@ -146,7 +140,7 @@ __global__ __launch_bounds__(512) void k_adj_fwd(AdjDesc d) {
   load6(d.ic, d.N, n, o);
   o.p0x = o.px; o.p0y = o.py; o.p0z = o.pz;
   o.dx = o.dy = o.dz = o.dpx = o.dpy = o.dpz = 0.0;
-  to_rot(o);
+  to_node(o);
   o.jsum = 0.0;
   for (int64_t s = 0; s < d.n_seg; ++s) {
     store6(d.ckpts + s * 6 * d.N, d.N, n, o);
@@ -154,7 +148,7 @@ __global__ __launch_bounds__(512) void k_adj_fwd(AdjDesc d) {
     const int64_t g1 = g0 + d.ckpt < d.T ? g0 + d.ckpt : d.T;
     for (int64_t g = g0; g < g1; ++g) {
       adj_step_fwd<FORM>(o, d, s_tab);
-      accum_j_rot(o);
+      accum_j_node(o);
       if (d.fwd_steps && adj_kept(g, g1)) store6(d.steps + adj_slot(g, 0) * 6 * d.N, d.N, n, o);  // one segment
     }
   }
@@ -163,18 +157,18 @@ __global__ __launch_bounds__(512) void k_adj_fwd(AdjDesc d) {
 }
 
 // The initial-state gradient: the explicit P_0 share of J, then back from the
-// rotated frame (u = x + y, v = x - y, so d/dx = d/du + d/dv and
-// d/dy = d/du - d/dv; momenta alike).
-__device__ __forceinline__ void store_grad(const AdjDesc &d, int64_t n, const Adjoint &a, double ch, double c,
+// scaled frame (u = x + y, v = x - y, so d/dx = d/du + d/dv and
+// d/dy = d/du - d/dv; d/dz = sqrt 2 d/d(sqrt 2 z); momenta alike).
+__device__ __forceinline__ void store_grad(const AdjDesc &d, int64_t n, const Adjoint &a, double c,
                                            double su, double sv, double sz) {
   const int64_t N = d.N;
-  const double pub = __builtin_fma(-ch, su, a.pxb), pvb = __builtin_fma(-ch, sv, a.pyb);
+  const double pub = __builtin_fma(-c, su, a.pxb), pvb = __builtin_fma(-c, sv, a.pyb);
   d.gic[0 * N + n] = a.xb + a.yb;
   d.gic[1 * N + n] = a.xb - a.yb;
-  d.gic[2 * N + n] = a.zb;
+  d.gic[2 * N + n] = times_sqrt2(a.zb);
   d.gic[3 * N + n] = pub + pvb;
   d.gic[4 * N + n] = pub - pvb;
-  d.gic[5 * N + n] = __builtin_fma(-c, sz, a.pzb);
+  d.gic[5 * N + n] = times_sqrt2(__builtin_fma(-c, sz, a.pzb));
   d.geps[n] = a.eb;
 }
 
@@ -185,13 +179,12 @@ __global__ __launch_bounds__(512) void k_adj_bwd_rev(AdjDesc d) {
   const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (n >= d.N) return;
   const int64_t N = d.N;
-  // P_0 in the rotated frame, rounded as the forward pass formed it.
+  // P_0 in the scaled frame, rounded as the forward pass formed it.
   const double p0x = d.ic[3 * N + n] + d.ic[4 * N + n], p0y = d.ic[3 * N + n] - d.ic[4 * N + n];
-  const double p0z = d.ic[5 * N + n];
-  // J = (1/T) sum ((P_u - P0_u)^2 + (P_v - P0_v)^2) / 2 + (P_z - P0_z)^2: the
-  // source is c/2 on p_u and p_v and c on p_z.
-  const double c = 2.0 * (d.gJ ? d.gJ[n] : 1.0) / (double)d.T;
-  const double ch = 0.5 * c;
+  const double p0z = times_sqrt2(d.ic[5 * N + n]);
+  // J is half the step average of the three squared displacements: the source
+  // is c (P_k - P_0).
+  const double c = (d.gJ ? d.gJ[n] : 1.0) / (double)d.T;
   Adjoint a{0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   double sx = 0.0, sy = 0.0, sz = 0.0;  // sum_k (P_k - P_0)
   Orbit o;
@@ -205,15 +198,15 @@ __global__ __launch_bounds__(512) void k_adj_bwd_rev(AdjDesc d) {
     load6(d.ckpts + (s + 1) * 6 * N, N, n, o);        // exact state after step g1 - 1
     for (int64_t g = g1 - 1; g >= g0; --g) {
       const double ex = o.px - p0x, ey = o.py - p0y, ez = o.pz - p0z;
-      a.pxb = __builtin_fma(ch, ex, a.pxb);
-      a.pyb = __builtin_fma(ch, ey, a.pyb);
+      a.pxb = __builtin_fma(c, ex, a.pxb);
+      a.pyb = __builtin_fma(c, ey, a.pyb);
       a.pzb = __builtin_fma(c, ez, a.pzb);
       sx += ex; sy += ey; sz += ez;
       adj_step_rev<FORM, EPS0>(o, a, d, s_tab);              // state now at the start of step g
     }
   }
   if (!EPS0) a.eb /= d.eps;   // the kicks collected eps epsbar
-  store_grad(d, n, a, ch, c, sx, sy, sz);
+  store_grad(d, n, a, c, sx, sy, sz);
 }
 
 template <int FORM, bool EPS0>
@@ -223,13 +216,12 @@ __global__ __launch_bounds__(512) void k_adj_bwd(AdjDesc d) {
   const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (n >= d.N) return;
   const int64_t N = d.N;
-  // P_0 in the rotated frame, rounded as the forward pass formed it.
+  // P_0 in the scaled frame, rounded as the forward pass formed it.
   const double p0x = d.ic[3 * N + n] + d.ic[4 * N + n], p0y = d.ic[3 * N + n] - d.ic[4 * N + n];
-  const double p0z = d.ic[5 * N + n];
-  // J = (1/T) sum ((P_u - P0_u)^2 + (P_v - P0_v)^2) / 2 + (P_z - P0_z)^2: the
-  // source is c/2 on p_u and p_v and c on p_z.
-  const double c = 2.0 * (d.gJ ? d.gJ[n] : 1.0) / (double)d.T;
-  const double ch = 0.5 * c;
+  const double p0z = times_sqrt2(d.ic[5 * N + n]);
+  // J is half the step average of the three squared displacements: the source
+  // is c (P_k - P_0).
+  const double c = (d.gJ ? d.gJ[n] : 1.0) / (double)d.T;
   Adjoint a{0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   double sx = 0.0, sy = 0.0, sz = 0.0;  // sum_k (P_k - P_0)
   Orbit o;
@@ -250,15 +242,15 @@ __global__ __launch_bounds__(512) void k_adj_bwd(AdjDesc d) {
       // state after step g: kept, or rebuilt by the inverse of step g + 1
       if (adj_kept(g, g1)) load6(d.steps + adj_slot(g, g0) * 6 * N, N, n, o);
       const double ex = o.px - p0x, ey = o.py - p0y, ez = o.pz - p0z;
-      a.pxb = __builtin_fma(ch, ex, a.pxb);
-      a.pyb = __builtin_fma(ch, ey, a.pyb);
+      a.pxb = __builtin_fma(c, ex, a.pxb);
+      a.pyb = __builtin_fma(c, ey, a.pyb);
       a.pzb = __builtin_fma(c, ez, a.pzb);
       sx += ex; sy += ey; sz += ez;
       adj_step_rev<FORM, EPS0>(o, a, d, s_tab);
     }
   }
   if (!EPS0) a.eb /= d.eps;   // the kicks collected eps epsbar
-  store_grad(d, n, a, ch, c, sx, sy, sz);
+  store_grad(d, n, a, c, sx, sy, sz);
 }
 
 hipError_t launch_adj_forward(const AdjDesc &d, int form, const Tuning &t, hipStream_t s) {

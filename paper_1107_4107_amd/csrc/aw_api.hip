@@ -389,17 +389,23 @@ aw_status check_ensemble(const aw_ensemble *e, const double *ic, int idx) {
   return AW_OK;
 }
 
+// Stage weights of a checked ensemble (see StepWeights); tau[u]: the kicks'
+// times.
+void step_weights(const aw_ensemble &e, StepWeights &w, double tau[MAX_UNIQUE]) {
+  (void)unique_weights(e.map_form, e.h, tau, w.drift);  // checked by check_ensemble
+  for (int u = 0; u < MAX_UNIQUE; ++u) {
+    w.dnode[u] = (double)(w.drift[u] * NODES_PER_RAD);
+    w.dnodez[u] = (double)(w.drift[u] * (SQRT2 * NODES_PER_RAD));
+    w.ka[u] = tau[u] * e.eps;
+    w.kb[u] = (double)(SQRT2 * w.ka[u]);
+  }
+}
+
 FwdDesc make_desc(const aw_ensemble &e, const double *ic, const Tuning &t) {
   FwdDesc d;
   std::memset(&d, 0, sizeof d);
   double tau[MAX_UNIQUE];
-  (void)unique_weights(e.map_form, e.h, tau, d.drift);  // checked by check_ensemble
-  for (int u = 0; u < MAX_UNIQUE; ++u) {
-    d.dnode[u] = (double)(d.drift[u] * NODES_PER_RAD);
-    d.dnodez[u] = (double)(d.drift[u] * (SQRT2 * NODES_PER_RAD));
-    d.ka[u] = tau[u] * e.eps;
-    d.kb[u] = (double)(SQRT2 * d.ka[u]);
-  }
+  step_weights(e, d.w, tau);
   d.eps = e.eps;
   d.th = (double)e.n_steps * e.h;
   d.lth = std::log(1.0 + d.th);
@@ -1075,14 +1081,8 @@ static aw_status adj_setup(const aw_ensemble *ens, const double *ic_dev, const d
   if (ws_bytes < need || (N > 0 && !workspace_dev))
     return fail(AW_EWORKSPACE, "workspace of %zu bytes needed, %zu given", need, ws_bytes);
   std::memset(&d, 0, sizeof d);
-  double tau[MAX_UNIQUE];
-  (void)unique_weights(ens->map_form, ens->h, tau, d.drift);
-  for (int u = 0; u < MAX_UNIQUE; ++u) {
-    d.ka2[u] = 2.0 * tau[u] * ens->eps;
-    d.ka4[u] = 4.0 * tau[u] * ens->eps;
-    d.kw2[u] = 2.0 * tau[u];
-    d.kw4[u] = 4.0 * tau[u];
-  }
+  step_weights(*ens, d.w, d.kt);
+  for (int u = 0; u < MAX_UNIQUE; ++u) d.ktb[u] = (double)(SQRT2 * d.kt[u]);
   d.eps = ens->eps;
   d.T = ens->n_steps;
   d.N = N;
@@ -1181,14 +1181,8 @@ static aw_status ftle_setup(const aw_ensemble *ens, const double *ic_dev, const 
   if (ws_bytes < need || (N > 0 && !workspace_dev))
     return fail(AW_EWORKSPACE, "workspace of %zu bytes needed, %zu given", need, ws_bytes);
   std::memset(&d, 0, sizeof d);
-  double tau[MAX_UNIQUE];
-  (void)unique_weights(ens->map_form, ens->h, tau, d.drift);
-  for (int u = 0; u < MAX_UNIQUE; ++u) {
-    d.ka2[u] = 2.0 * tau[u] * ens->eps;
-    d.ka4[u] = 4.0 * tau[u] * ens->eps;
-    d.kw2[u] = 2.0 * tau[u];
-    d.kw4[u] = 4.0 * tau[u];
-  }
+  step_weights(*ens, d.w, d.kt);
+  for (int u = 0; u < MAX_UNIQUE; ++u) d.ktb[u] = (double)(SQRT2 * d.kt[u]);
   d.eps = ens->eps;
   d.T = ens->n_steps;
   d.N = N;

@@ -15,11 +15,11 @@
 //                epsbar += -t grad Hp(X) . Pbar - t (Hess Hp(X) dX) . dPbar
 // where T3 is the third-derivative tensor of Hp (symmetric), contracted
 // with dX and dPbar.  The end condition is dL/dw_T = w_T / |w_T|^2.
-// The kernels step in the rotated frame of the forward kernels (u = x + y,
-// v = x - y, momenta and tangent alike): there the kick's Jacobian has 7
-// non-zero entries and is not symmetric (the frame is not orthonormal), the
-// norm of w carries the weights (1/2, 1/2, 1, 1/2, 1/2, 1), and the gradient
-// is taken back to (x, y) at the end.
+// The kernels step in the scaled rotated frame of the forward kernels
+// (kick_node; tangent and adjoint in (u, v, sqrt 2 z) and their momenta): there
+// the kick's Jacobian has 7 non-zero entries and is symmetric, |w|^2 is half
+// the sum of the six squares, and the gradient is taken back to (x, y, z) at
+// the end.
 //
 // The tangent is rescaled by exact powers of two after every 8th step
 // (global step count), as in the forward kernel.  A rescale w <- 2^-k w is
@@ -49,6 +49,7 @@
 #include "aw_device.hpp"
 #include "aw_internal.hpp"
 #include "aw_launch.hpp"
+#include "aw_step.hpp"
 
 namespace aw {
 
@@ -60,19 +61,9 @@ static_assert(((RESCALE_MASK + 1) % ADJ_SUB) == 0, "every rescale step must be a
 
 template <int FORM>
 __device__ __forceinline__ void tan_step(Orbit &o, const AdjDesc &d, const double2 *__restrict__ tab) {
-  using F = FormPattern<FORM>;
-  constexpr int NK = F::NK;
-  if constexpr (F::LEAD) {
-#pragma unroll
-    for (int i = 0; i < NK; ++i) {
-      drift<true>(o, d.drift[F::drift_idx[i]]);
-      kick_rot<true>(o, d.ka2[F::kick_idx[i]], tab);
-    }
-    drift<true>(o, d.drift[F::drift_idx[NK]]);
-  } else {
-    kick_rot<true>(o, d.ka2[0], tab);
-    drift<true>(o, d.drift[0]);
-  }
+  Orbit t[1] = {o};
+  map_step<FORM, true, 1>(t, d.w, tab);
+  o = t[0];
 }
 
 struct Adjoint2 {
@@ -82,10 +73,10 @@ struct Adjoint2 {
 };
 
 // Undo D(t) and apply its transpose.
-__device__ __forceinline__ void rev_drift2(Orbit &o, Adjoint2 &a, double t) {
-  o.x = __builtin_fma(-t, o.px, o.x);
-  o.y = __builtin_fma(-t, o.py, o.y);
-  o.z = __builtin_fma(-t, o.pz, o.z);
+__device__ __forceinline__ void rev_drift2(Orbit &o, Adjoint2 &a, double wu, double wz, double t) {
+  o.x = __builtin_fma(-wu, o.px, o.x);
+  o.y = __builtin_fma(-wu, o.py, o.y);
+  o.z = __builtin_fma(-wz, o.pz, o.z);
   o.dx = __builtin_fma(-t, o.dpx, o.dx);
   o.dy = __builtin_fma(-t, o.dpy, o.dy);
   o.dz = __builtin_fma(-t, o.dpz, o.dz);
@@ -97,100 +88,81 @@ __device__ __forceinline__ void rev_drift2(Orbit &o, Adjoint2 &a, double t) {
   a.dpzb = __builtin_fma(t, a.dzb, a.dpzb);
 }
 
-// Undo K(t) and apply its transpose, in the rotated frame of the steps
-// (u = x + y, v = x - y; the Adjoint2's x, y, px, py fields hold u, v, p_u,
-// p_v and their tangents).  a2 = 2 t eps, w2 = 2 t.  With e1 = a2 cz^2,
-// e2 = a2 cz sz, g = 2 e1 - a2 (= de2/dz; de1/dz = -2 e2) and
-// cs = cos u + cos v, the kick is F = (e1 sin u, e1 sin v, e2 cs) with Jacobian
-//   M = [[e1 cos u, 0, -2 e2 sin u], [0, e1 cos v, -2 e2 sin v],
-//        [-e2 sin u, -e2 sin v, cs g]],
+// Undo K(t) and apply its transpose, in the scaled frame (the Adjoint2's x, y,
+// z, px, py, pz fields hold the adjoints of (u, v, sqrt 2 z) and their momenta
+// and of their tangents).  With a = t eps, e1 = a (1 + cos 2z),
+// e2 = sqrt 2 a sin 2z, g = 2 a cos 2z and cs = cos u + cos v -- in
+// w = sqrt 2 z: de1/dw = -e2, de2/dw = g, dg/dw = -2 e2 -- the kick is
+// F = (e1 sin u, e1 sin v, e2 cs) with the symmetric Jacobian
+//   M = [[e1 cos u, 0, -e2 sin u], [0, e1 cos v, -e2 sin v],
+//        [-e2 sin u, -e2 sin v, g cs]],
 // and the tangent kick dP += M dX.  Its transpose gives
-//   Xbar  += M^T Pbar + S,   S_k = sum_ij dPbar_i (dM_ij/dX_k) dX_j,
-//   dXbar += M^T dPbar,      epsbar += (F . Pbar + (M dX) . dPbar) / eps,
-// where, with Bu = e2 cos u du + g sin u dz, Bv = e2 cos v dv + g sin v dz,
-//   S_u = -dPbar_u (e1 sin u du + 2 e2 cos u dz) - dPbar_z Bu,
-//   S_v = -dPbar_v (e1 sin v dv + 2 e2 cos v dz) - dPbar_z Bv,
-//   S_z = -2 dPbar_u Bu - 2 dPbar_v Bv
-//         - dPbar_z (g sin u du + g sin v dv + 4 e2 cs dz).
-// F and M carry the factor eps.  For eps != 0 (EPS0 false) a.eb collects
-// eps epsbar, F . Pbar + (M dX) . dPbar with the M dX the undo needs anyway,
-// and the kernel divides by eps once at the end.  For eps = 0 (EPS0 true)
-// F / eps and M / eps are formed from w2 = 2 t directly.
+//   Xbar  += M Pbar + S,   S_k = sum_ij dPbar_i (dM_ij/dX_k) dX_j,
+//   dXbar += M dPbar,      epsbar += (F . Pbar + (M dX) . dPbar) / eps.
+// With the symmetric products of tangent and adjoint tangent
+//   auu = dPbar_u du, avv alike, azz = dPbar_z dz,
+//   auz = dPbar_u dz + dPbar_z du, avz alike,
+// and q = sin u Pbar_u + sin v Pbar_v, kc = cos u auu + cos v avv,
+// ks = sin u auz + sin v avz, A = cs Pbar_z - ks, the terms collect to
+//   Xbar_u += cos u (e1 Pbar_u - e2 auz) - sin u (e2 Pbar_z + g azz + e1 auu),
+//   Xbar_z += g A - e2 (q + kc + 2 cs azz),
+//   eps epsbar += e1 (q + kc) + e2 A + g cs azz.
+// 98 FP64 instructions where the unscaled, unsymmetric frame took 112.
+// F and M carry the factor eps.  For eps != 0 (EPS0 false) a.eb collects eps
+// epsbar and the kernel divides by eps once at the end.  For eps = 0 (EPS0
+// true) the same sums are taken with the kick's time t in the place of a.
 // Sines and cosines from the same table as the forward kick.
 template <bool EPS0>
-__device__ __forceinline__ void rev_kick2(Orbit &o, Adjoint2 &a, double a2, double w2,
+__device__ __forceinline__ void rev_kick2(Orbit &o, Adjoint2 &a, double ka, double kb, double kt, double ktb,
                                           const double2 *__restrict__ tab) {
-  const SinCosT U = sincos_tab(o.x, tab), V = sincos_tab(o.y, tab);
-  const ZTerms Z = zterms_tab(o.z, tab);
-  const double e1 = a2 * Z.cz2, e2 = a2 * Z.czsz, g = __builtin_fma(2.0, e1, -a2);
+  const NodeSC U = sincos_node(o.x, tab), V = sincos_node(o.y, tab), Z = sincos_node(o.z, tab);
+  const double e1 = __builtin_fma(ka, Z.c, ka);
+  const double e2 = kb * Z.s;
+  const double g = __builtin_fma(2.0, e1, -2.0 * ka);
   const double cs = U.c + V.c;
-  // F, the kick's increment of P.
-  const double fu = e1 * U.s, fv = e1 * V.s, fz = e2 * cs;
   const double du = o.dx, dv = o.dy, dz = o.dz;
   const double pub = a.pxb, pvb = a.pyb, pzb = a.pzb;
   const double dpub = a.dpxb, dpvb = a.dpyb, dpzb = a.dpzb;
-  // M; its (u, z) and (v, z) entries are 2 mzu and 2 mzv, and every product
-  // with them is formed as mzu (2 dz) and the like, exact rescalings by 2.
-  const double muu = e1 * U.c, mvv = e1 * V.c;
-  const double mzu = -e2 * U.s, mzv = -e2 * V.s, mzz = cs * g;
-  const double dz2 = dz + dz;
-  // M dX: the tangent kick of the forward step.
-  const double mdu = __builtin_fma(muu, du, mzu * dz2);
-  const double mdv = __builtin_fma(mvv, dv, mzv * dz2);
-  const double mdz = __builtin_fma(mzu, du, __builtin_fma(mzv, dv, mzz * dz));
+  const double mzz = cs * g;
+
+  const double auu = dpub * du, avv = dpvb * dv, azz = dpzb * dz;
+  const double auz = __builtin_fma(dpub, dz, dpzb * du);
+  const double avz = __builtin_fma(dpvb, dz, dpzb * dv);
+  const double q = __builtin_fma(U.s, pub, V.s * pvb);
+  const double kc = __builtin_fma(U.c, auu, V.c * avv);
+  const double ks = __builtin_fma(U.s, auz, V.s * avz);
+  const double A = __builtin_fma(cs, pzb, -ks);
+  const double csz = cs * azz;
+  const double qk = q + kc;
 
   if constexpr (EPS0) {
-    // epsbar from F / eps and M / eps.
-    const double f1 = w2 * Z.cz2, f2 = w2 * Z.czsz, gf = __builtin_fma(2.0, f1, -w2);
-    const double wuu = f1 * U.c, wvv = f1 * V.c, wuz = -2.0 * f2 * U.s, wvz = -2.0 * f2 * V.s;
-    const double wzu = -f2 * U.s, wzv = -f2 * V.s, wzz = cs * gf;
-    double eb = a.eb;
-    eb = __builtin_fma(f1, __builtin_fma(U.s, pub, V.s * pvb), eb);
-    eb = __builtin_fma(f2 * cs, pzb, eb);
-    eb = __builtin_fma(__builtin_fma(wuu, du, wuz * dz), dpub, eb);
-    eb = __builtin_fma(__builtin_fma(wvv, dv, wvz * dz), dpvb, eb);
-    eb = __builtin_fma(__builtin_fma(wzu, du, __builtin_fma(wzv, dv, wzz * dz)), dpzb, eb);
-    a.eb = eb;
+    const double f1 = __builtin_fma(kt, Z.c, kt), f2 = ktb * Z.s, gf = __builtin_fma(2.0, f1, -2.0 * kt);
+    a.eb = __builtin_fma(f1, qk, a.eb);
+    a.eb = __builtin_fma(f2, A, a.eb);
+    a.eb = __builtin_fma(gf, csz, a.eb);
   } else {
-    // eps epsbar: F . Pbar + (M dX) . dPbar.
-    double eb = a.eb;
-    eb = __builtin_fma(fu, pub, eb);
-    eb = __builtin_fma(fv, pvb, eb);
-    eb = __builtin_fma(fz, pzb, eb);
-    eb = __builtin_fma(mdu, dpub, eb);
-    eb = __builtin_fma(mdv, dpvb, eb);
-    eb = __builtin_fma(mdz, dpzb, eb);
-    a.eb = eb;
+    a.eb = __builtin_fma(e1, qk, a.eb);
+    a.eb = __builtin_fma(e2, A, a.eb);
+    a.eb = __builtin_fma(g, csz, a.eb);
   }
 
-  // Xbar += M^T Pbar + S.
-  const double e2cu = e2 * U.c, e2cv = e2 * V.c, gsu = g * U.s, gsv = g * V.s;
-  const double Au = __builtin_fma(fu, du, e2cu * dz2);
-  const double Av = __builtin_fma(fv, dv, e2cv * dz2);
-  const double Bu = __builtin_fma(e2cu, du, gsu * dz);
-  const double Bv = __builtin_fma(e2cv, dv, gsv * dz);
-  const double Cz = __builtin_fma(gsu, du, __builtin_fma(gsv, dv, fz * (dz2 + dz2)));
-  double xb = a.xb, yb = a.yb, zb = a.zb;
-  xb = __builtin_fma(muu, pub, __builtin_fma(mzu, pzb, xb));
-  yb = __builtin_fma(mvv, pvb, __builtin_fma(mzv, pzb, yb));
-  xb = __builtin_fma(-dpub, Au, __builtin_fma(-dpzb, Bu, xb));
-  yb = __builtin_fma(-dpvb, Av, __builtin_fma(-dpzb, Bv, yb));
-  // The z row: the terms with a factor 2 summed first, then doubled.
-  const double zh = __builtin_fma(mzu, pub, __builtin_fma(mzv, pvb, __builtin_fma(-dpub, Bu, -(dpvb * Bv))));
-  zb = __builtin_fma(2.0, zh, __builtin_fma(mzz, pzb, __builtin_fma(-dpzb, Cz, zb)));
-  a.xb = xb;
-  a.yb = yb;
-  a.zb = zb;
+  // Xbar += M Pbar + S.
+  const double hb = __builtin_fma(e2, pzb, g * azz);
+  a.xb = __builtin_fma(U.c, __builtin_fma(-e2, auz, e1 * pub), __builtin_fma(-U.s, __builtin_fma(e1, auu, hb), a.xb));
+  a.yb = __builtin_fma(V.c, __builtin_fma(-e2, avz, e1 * pvb), __builtin_fma(-V.s, __builtin_fma(e1, avv, hb), a.yb));
+  a.zb = __builtin_fma(g, A, __builtin_fma(-e2, __builtin_fma(2.0, csz, qk), a.zb));
 
-  // dXbar += M^T dPbar.
-  a.dxb = __builtin_fma(muu, dpub, __builtin_fma(mzu, dpzb, a.dxb));
-  a.dyb = __builtin_fma(mvv, dpvb, __builtin_fma(mzv, dpzb, a.dyb));
-  a.dzb = __builtin_fma(2.0, __builtin_fma(mzu, dpub, mzv * dpvb), __builtin_fma(mzz, dpzb, a.dzb));
+  // dXbar += M dPbar.
+  const double hd = e2 * dpzb;
+  a.dxb = __builtin_fma(U.c, e1 * dpub, __builtin_fma(-U.s, hd, a.dxb));
+  a.dyb = __builtin_fma(V.c, e1 * dpvb, __builtin_fma(-V.s, hd, a.dyb));
+  a.dzb = __builtin_fma(mzz, dpzb, __builtin_fma(-e2, __builtin_fma(U.s, dpub, V.s * dpvb), a.dzb));
 
   // Undo the kick: dP -= M dX, P -= F.
-  o.dpx -= mdu;
-  o.dpy -= mdv;
-  o.dpz -= mdz;
+  const double h = e2 * dz;
+  o.dpx = __builtin_fma(-U.c, e1 * du, __builtin_fma(U.s, h, o.dpx));
+  o.dpy = __builtin_fma(-V.c, e1 * dv, __builtin_fma(V.s, h, o.dpy));
+  o.dpz = __builtin_fma(-mzz, dz, __builtin_fma(e2, __builtin_fma(U.s, du, V.s * dv), o.dpz));
   o.px = __builtin_fma(-e1, U.s, o.px);
   o.py = __builtin_fma(-e1, V.s, o.py);
   o.pz = __builtin_fma(-e2, cs, o.pz);
@@ -200,17 +172,18 @@ template <int FORM, bool EPS0>
 __device__ __forceinline__ void rev_tan_step(Orbit &o, Adjoint2 &a, const AdjDesc &d, const double2 *__restrict__ tab) {
   using F = FormPattern<FORM>;
   constexpr int NK = F::NK;
+  auto drift = [&](int q) { rev_drift2(o, a, d.w.dnode[q], d.w.dnodez[q], d.w.drift[q]); };
+  auto kick = [&](int q) { rev_kick2<EPS0>(o, a, d.w.ka[q], d.w.kb[q], d.kt[q], d.ktb[q], tab); };
   if constexpr (F::LEAD) {
-    rev_drift2(o, a, d.drift[F::drift_idx[NK]]);
+    drift(F::drift_idx[NK]);
 #pragma unroll
     for (int i = NK - 1; i >= 0; --i) {
-      const int u = F::kick_idx[i];
-      rev_kick2<EPS0>(o, a, d.ka2[u], d.kw2[u], tab);
-      rev_drift2(o, a, d.drift[F::drift_idx[i]]);
+      kick(F::kick_idx[i]);
+      drift(F::drift_idx[i]);
     }
   } else {
-    rev_drift2(o, a, d.drift[0]);
-    rev_kick2<EPS0>(o, a, d.ka2[0], d.kw2[0], tab);
+    drift(0);
+    kick(0);
   }
 }
 
@@ -228,54 +201,42 @@ __device__ __forceinline__ void store12(double *p, int64_t N, int64_t n, const O
   p[9 * N + n] = o.dpx; p[10 * N + n] = o.dpy; p[11 * N + n] = o.dpz;
 }
 
-// The tangent's norm in the rotated frame of the steps:
-// |w|^2 = (du^2 + dv^2 + dp_u^2 + dp_v^2)/2 + dz^2 + dp_z^2.
-__device__ __forceinline__ double tan_norm2_rot(const Orbit &o) {
+// The sum of the tangent's six squares: 2 |w|^2 in the scaled frame.
+__device__ __forceinline__ double tan_sum2(const Orbit &o) {
   double a = o.dx * o.dx;
   a = __builtin_fma(o.dy, o.dy, a);
+  a = __builtin_fma(o.dz, o.dz, a);
   a = __builtin_fma(o.dpx, o.dpx, a);
   a = __builtin_fma(o.dpy, o.dpy, a);
-  const double n2 = __builtin_fma(o.dz, o.dz, o.dpz * o.dpz);
-  return __builtin_fma(0.5, a, n2);
+  return __builtin_fma(o.dpz, o.dpz, a);
 }
 
-// dL/dw_T = G w_T / |w_T|^2 in the rotated frame, G = diag(1/2, 1/2, 1, 1/2, 1/2, 1),
-// scaled by the upstream gradient gl.
+// dL/dw_T in the scaled frame: w_T over the sum of its squares, scaled by the
+// upstream gradient gl.
 __device__ __forceinline__ void end_condition(const Orbit &o, Adjoint2 &a, double gl) {
-  const double c = gl / tan_norm2_rot(o);
-  const double h = 0.5 * c;
-  a.dxb = h * o.dx; a.dyb = h * o.dy; a.dzb = c * o.dz;
-  a.dpxb = h * o.dpx; a.dpyb = h * o.dpy; a.dpzb = c * o.dpz;
+  const double c = gl / tan_sum2(o);
+  a.dxb = c * o.dx; a.dyb = c * o.dy; a.dzb = c * o.dz;
+  a.dpxb = c * o.dpx; a.dpyb = c * o.dpy; a.dpzb = c * o.dpz;
 }
 
-// The initial-state gradient, back from the rotated frame (d/dx = d/du + d/dv,
-// d/dy = d/du - d/dv; momenta alike).
+// The initial-state gradient, back from the scaled frame (d/dx = d/du + d/dv,
+// d/dy = d/du - d/dv, d/dz = sqrt 2 d/d(sqrt 2 z); momenta alike).
 __device__ __forceinline__ void store_grad2(const FtleDesc &d, int64_t n, const Adjoint2 &a) {
   const int64_t N = d.N;
   d.gic[0 * N + n] = a.xb + a.yb;
   d.gic[1 * N + n] = a.xb - a.yb;
-  d.gic[2 * N + n] = a.zb;
+  d.gic[2 * N + n] = times_sqrt2(a.zb);
   d.gic[3 * N + n] = a.pxb + a.pyb;
   d.gic[4 * N + n] = a.pxb - a.pyb;
-  d.gic[5 * N + n] = a.pzb;
+  d.gic[5 * N + n] = times_sqrt2(a.pzb);
   d.geps[n] = a.eb;
-}
-
-__device__ __forceinline__ double tan_norm2(const Orbit &o) {
-  double n2 = o.dx * o.dx;
-  n2 = __builtin_fma(o.dy, o.dy, n2);
-  n2 = __builtin_fma(o.dz, o.dz, n2);
-  n2 = __builtin_fma(o.dpx, o.dpx, n2);
-  n2 = __builtin_fma(o.dpy, o.dpy, n2);
-  n2 = __builtin_fma(o.dpz, o.dpz, n2);
-  return n2;
 }
 
 // Power-of-two exponent the forward rescale applies to this tangent.
 __device__ __forceinline__ int rescale_exponent(const Orbit &o) {
   Orbit t = o;
   t.kexp = 0;
-  renorm_rot(t);
+  renorm_node(t);
   return t.kexp;
 }
 
@@ -294,8 +255,8 @@ __global__ __launch_bounds__(512) void k_ftle_fwd(FtleDesc d) {
   o.p0x = o.px; o.p0y = o.py; o.p0z = o.pz;
   o.jsum = 0.0;
   o.kexp = 0;
-  const double n0 = tan_norm2(o);
-  to_rot(o);
+  const double n0 = tan_sum2(o);   // |w_0|^2, before the frame
+  to_node(o);
   for (int64_t s = 0; s < d.n_seg; ++s) {
     store12(d.ckpts + s * 12 * N, N, n, o);
     const int64_t g0 = s * d.ckpt;
@@ -305,14 +266,14 @@ __global__ __launch_bounds__(512) void k_ftle_fwd(FtleDesc d) {
       if (d.fwd_steps && adj_kept(g, g1)) store12(d.steps + adj_slot(g, 0) * 12 * N, N, n, o);  // one segment
       if (((g + 1) & RESCALE_MASK) == 0) {
         const int k0 = o.kexp;
-        renorm_rot(o);
+        renorm_node(o);
         d.exps[((g + 1) / (RESCALE_MASK + 1) - 1) * N + n] = (int16_t)(o.kexp - k0);
       }
     }
   }
   store12(d.ckpts + d.n_seg * 12 * N, N, n, o);   // the final state (after any last rescale)
   if (d.L) {
-    const double n2 = tan_norm2_rot(o);
+    const double n2 = 0.5 * tan_sum2(o);
     const int e = __builtin_amdgcn_frexp_exp(n2);
     const double mant = __builtin_amdgcn_frexp_mant(n2);
     d.L[n] = 0.5 * ((double)(2 * o.kexp + e) * LN2_D + log(mant)) - 0.5 * log(n0);
@@ -340,7 +301,7 @@ __global__ __launch_bounds__(512) void k_ftle_bwd(FtleDesc d) {
       for (int64_t g = g0; g < g1; ++g) {
         tan_step<FORM>(o, d, s_tab);
         if (adj_kept(g, g1)) store12(d.steps + adj_slot(g, g0) * 12 * N, N, n, o);
-        if (((g + 1) & RESCALE_MASK) == 0) renorm_rot(o);
+        if (((g + 1) & RESCALE_MASK) == 0) renorm_node(o);
       }
     }
     for (int64_t g = g1 - 1; g >= g0; --g) {

@@ -15,6 +15,7 @@
 #include "aw_device.hpp"
 #include "aw_internal.hpp"
 #include "aw_launch.hpp"
+#include "aw_step.hpp"
 
 namespace aw {
 
@@ -89,46 +90,6 @@ __device__ __forceinline__ void gen_w0(uint64_t seed, int64_t n, double w[6]) {
   const double nu = sqrt(n2);
 #pragma unroll
   for (int k = 0; k < 6; ++k) w[k] = u[k] / nu;
-}
-
-// ---------------------------------------------------------------------------
-// One map step: NK kicks, each preceded by a drift, and a closing drift
-// (symmetric compositions), or kick-then-drift (coupled standard map).  The
-// kicks take their sines and cosines from the block's LDS table `tab`.
-// ---------------------------------------------------------------------------
-// The distinct stage weights of the form, copied from the descriptor before
-// the step loop (see FwdDesc).
-struct StepWeights {
-  double drift[MAX_UNIQUE];
-  double dnode[MAX_UNIQUE];
-  double dnodez[MAX_UNIQUE];
-  double ka[MAX_UNIQUE];
-  double kb[MAX_UNIQUE];
-};
-
-template <int FORM, bool TAN, int OPL>
-__device__ __forceinline__ void map_step(Orbit (&o)[OPL], const StepWeights &d, const double2 *__restrict__ tab) {
-  using F = FormPattern<FORM>;
-  constexpr int NK = F::NK;
-  auto drift = [&](int q) {
-#pragma unroll
-    for (int j = 0; j < OPL; ++j) drift_node<TAN>(o[j], d.dnode[q], d.dnodez[q], d.drift[q]);
-  };
-  auto kick = [&](int q) {
-#pragma unroll
-    for (int j = 0; j < OPL; ++j) kick_node<TAN>(o[j], d.ka[q], d.kb[q], tab);
-  };
-  if constexpr (F::LEAD) {
-#pragma unroll
-    for (int i = 0; i < NK; ++i) {
-      drift(F::drift_idx[i]);
-      kick(F::kick_idx[i]);
-    }
-    drift(F::drift_idx[NK]);
-  } else {
-    kick(0);
-    drift(0);
-  }
 }
 
 // Select row r of the nine per-orbit results by masking bit patterns.  A
@@ -288,17 +249,11 @@ __device__ __forceinline__ void run_orbits(const FwdDesc &d, int64_t first, cons
   // The unrolled, two-orbit and window variants would lose occupancy and keep
   // them in SGPRs.
   constexpr bool kVregW = TAN && OPL == 1 && UNR == 1 && !FILT && !WINV;
-  StepWeights sw;
+  StepWeights sw = d.w;
+  if (kVregW) {
 #pragma unroll
-  for (int q = 0; q < MAX_UNIQUE; ++q) {
-    sw.drift[q] = d.drift[q];
-    sw.dnode[q] = d.dnode[q];
-    sw.dnodez[q] = d.dnodez[q];
-    sw.ka[q] = d.ka[q];
-    sw.kb[q] = d.kb[q];
-    if (kVregW) {
+    for (int q = 0; q < MAX_UNIQUE; ++q)
       asm volatile("" : "+v"(sw.drift[q]), "+v"(sw.dnode[q]), "+v"(sw.dnodez[q]), "+v"(sw.ka[q]), "+v"(sw.kb[q]));
-    }
   }
   auto one_step = [&](int64_t k) {
     map_step<FORM, TAN, OPL>(o, sw, tab);
@@ -559,14 +514,7 @@ __global__ __launch_bounds__(256) void k_fwd_pair(FwdDesc d) {
     }
   }
   const double ws = h.w, zs = h.z;
-  StepWeights sw;
-#pragma unroll
-  for (int q = 0; q < MAX_UNIQUE; ++q) {
-    sw.dnode[q] = d.dnode[q];
-    sw.dnodez[q] = d.dnodez[q];
-    sw.ka[q] = d.ka[q];
-    sw.kb[q] = d.kb[q];
-  }
+  const StepWeights sw = d.w;
 #pragma nounroll
   for (int64_t k = d.k_begin; k < d.k_end; ++k) {
     pair_step<FORM>(h, sw, s_tab);

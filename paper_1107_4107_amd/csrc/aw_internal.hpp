@@ -52,16 +52,21 @@ constexpr uint32_t BIN_DROP = 0xffffffffu;
 // Image epilogue selector of the propagation kernel.
 enum EpiKind : int32_t { EPI_NONE = 0, EPI_IC_GRID = 1, EPI_HIST_P0 = 2, EPI_HIST_VDIR = 3 };
 
-// One ensemble as the kernels see it.  Distinct stage weights of the scaled
-// frame (kick_node, drift_node), pre-multiplied: a drift of time t = c h takes
-// drift[u] = t, dnode[u] = t in table nodes per radian and dnodez[u] = sqrt 2
-// times that; a kick of time t = w h takes ka[u] = t eps and kb[u] = sqrt 2 t eps.
-struct FwdDesc {
+// Distinct stage weights of a form in the kernels' scaled frame (kick_node,
+// drift_node), pre-multiplied: a drift of time t = c h takes drift[u] = t,
+// dnode[u] = t in table nodes per radian and dnodez[u] = sqrt 2 times that; a
+// kick of time t = w h takes ka[u] = t eps and kb[u] = sqrt 2 t eps.
+struct StepWeights {
   double drift[MAX_UNIQUE];
   double dnode[MAX_UNIQUE];
   double dnodez[MAX_UNIQUE];
   double ka[MAX_UNIQUE];
   double kb[MAX_UNIQUE];
+};
+
+// One ensemble as the kernels see it.
+struct FwdDesc {
+  StepWeights w;
   double eps;
   double th;         // T h
   double lth;        // ln(1 + T h)
@@ -138,11 +143,9 @@ __host__ __device__ inline int64_t adj_slots_max(int64_t ck) { return (ck + ADJ_
 
 // Adjoint descriptor.
 struct AdjDesc {
-  double drift[MAX_UNIQUE];
-  double ka2[MAX_UNIQUE];
-  double ka4[MAX_UNIQUE];
-  double kw2[MAX_UNIQUE];  // 2 w h (for d/deps)
-  double kw4[MAX_UNIQUE];  // 4 w h
+  StepWeights w;
+  double kt[MAX_UNIQUE];   // w h and sqrt 2 w h: the kick weights without eps
+  double ktb[MAX_UNIQUE];  // (for d/deps at eps = 0)
   double eps;
   int64_t T;
   int64_t N;

@@ -51,9 +51,20 @@ __global__ __launch_bounds__(BLOCK) void k_fma_chains(double m, double c, int64_
   }
 }
 
-// The table-driven sine and cosine of the adjoint kernels, their doubled-angle
-// z terms and the polynomial form of the initial conditions, one argument per
-// lane; and the propagation kernels' node-unit form.
+// The step loops' table lookup and rotation for an argument in radians (a
+// two-part reduction by pi/2048 in front; the kernels' own angles are in
+// nodes), cos x sin x and cos^2 x from the doubled angle as the kick forms its
+// z factors, and the polynomial form of the initial conditions, one argument
+// per lane; and the kernels' node-unit form itself.
+__device__ __forceinline__ double radian_reduce(double x, uint32_t& lo) {
+  const double m = __builtin_fma(x, AW_NODES_PER_RAD[0], AW_ROUND_MAGIC);
+  const double q = m - AW_ROUND_MAGIC;
+  double r = __builtin_fma(-q, AW_PI2K_A, x);
+  r = __builtin_fma(-q, AW_PI2K_B, r);
+  lo = (uint32_t)__double2loint(m);
+  return r;
+}
+
 __global__ __launch_bounds__(BLOCK) void k_sincos(const double* __restrict__ x, double* __restrict__ s,
                                                   double* __restrict__ c, int64_t n, int32_t form) {
   __shared__ double2 tab[AW_TAB_N];
@@ -61,13 +72,17 @@ __global__ __launch_bounds__(BLOCK) void k_sincos(const double* __restrict__ x, 
   const int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
   if (i >= n) return;
   if (form == 0) {
-    const aw::SinCosT r = aw::sincos_tab(x[i], tab);
-    s[i] = r.s;
-    c[i] = r.c;
+    uint32_t lo;
+    const double r = radian_reduce(x[i], lo);
+    const aw::NodeSC v = aw::turn_node(tab[lo & (AW_TAB_N - 1)], r * AW_NODES_PER_RAD[0]);
+    s[i] = v.s;
+    c[i] = v.c;
   } else if (form == 2) {
-    const aw::ZTerms r = aw::zterms_tab(x[i], tab);
-    s[i] = r.czsz;
-    c[i] = r.cz2;
+    uint32_t lo;
+    const double r = radian_reduce(x[i], lo);
+    const aw::NodeSC v = aw::turn_node(tab[(2 * lo) & (AW_TAB_N - 1)], (r + r) * AW_NODES_PER_RAD[0]);
+    s[i] = 0.5 * v.s;
+    c[i] = __builtin_fma(0.5, v.c, 0.5);
   } else {
     double sv, cv;
     aw::sincos_full(x[i], sv, cv);
@@ -160,9 +175,9 @@ extern "C" int awp_fma_peak(int32_t waves_per_simd, int64_t trips, double* out) 
 }
 
 // Writes s_dev[i], c_dev[i] = sin, cos of x_dev[i] (device arrays of n
-// doubles) as the kernels compute them: form 0 = the table-driven routine of
-// the step loops, 1 = the polynomial routine of the initial conditions and
-// the energy; form 2 writes the kicks' z terms instead, s = cos x sin x and
+// doubles) as the kernels compute them: form 0 = the table and rotation of the
+// step loops, 1 = the polynomial routine of the initial conditions and
+// the energy; form 2 writes the kick's z factors instead, s = cos x sin x and
 // c = cos^2 x, from the table at the doubled angle.  Enqueued on `stream`
 // (NULL = default).  Returns 0, 1 on a HIP error (printed), 2 on bad
 // arguments.
