@@ -340,9 +340,11 @@ aw_status aw_vdir_keys(int64_t N, const double *V_dev, double *phi_dev, double *
  * Requires a caller workspace of aw_indicator_grad_workspace() bytes: the
  * n_seg = ceil(T / ckpt_every) checkpoints, the final state and the kept step
  * states of one segment (at most floor((ck + 2)/4) + 1 with ck =
- * min(ckpt_every, T)), 6 doubles per orbit each.  With ckpt_every >= T (one
- * segment) the forward pass keeps the step states itself and the backward
- * pass sweeps them without a recompute: about T*N*12 bytes of workspace.
+ * min(ckpt_every, T)), 6 doubles per orbit each.  The forward pass keeps the
+ * step states of the last segment itself, and of as many segments before it
+ * as a larger workspace (ws_bytes) has room for: the backward pass sweeps
+ * those without a recompute.  With ckpt_every >= T (one segment) nothing is
+ * recomputed: about T*N*12 bytes of workspace.
  * The result is bitwise the same for every ckpt_every that is a multiple of 4
  * and for ckpt_every >= T (the same states are kept); other intervals keep
  * more states and agree to rounding. */
@@ -391,8 +393,9 @@ aw_status aw_indicator_grad_reversible(const aw_ensemble *ens, const double *ic_
  * Requires a caller workspace of aw_ftle_grad_workspace() bytes: 12 doubles
  * per orbit per checkpoint, for the final state and per kept step of a
  * segment, then one 16-bit rescale exponent per orbit per 8 steps.  As for
- * aw_indicator_grad, ckpt_every >= T keeps the step states in the forward pass
- * and skips the recompute (about T*N*24 bytes); the result is bitwise the same
+ * aw_indicator_grad, the forward pass keeps the step states of the last
+ * segment and of those a larger workspace holds, and ckpt_every >= T skips the
+ * recompute (about T*N*24 bytes); the result is bitwise the same
  * for ckpt_every a multiple of 4 and for ckpt_every >= T. */
 aw_status aw_ftle_grad_workspace(const aw_ensemble *ens, int64_t ckpt_every, size_t *bytes);
 aw_status aw_ftle_grad(const aw_ensemble *ens, const double *ic_dev, const double *w0_dev,

@@ -335,6 +335,30 @@ def grad_workspace_bytes(ens: Ensemble, ckpt_every: int, reversible: bool = Fals
     return int(nb.value)
 
 
+# An adjoint call that allocates its own workspace gives it room for the step
+# states of every segment, so that nothing is recomputed, up to this size (1.4%
+# of the card's memory); beyond it the last segments that fit are kept.
+KEEP_BYTES = 4 << 30
+
+
+def _adjoint_workspace(ens: Ensemble, ckpt_every: int, need: int, rows: int, reversible: bool, dev) -> torch.Tensor:
+    """A workspace of at least `need` bytes; rows: doubles per orbit and state."""
+    N, T = ens.size, int(ens.n_steps)
+    ck = min(int(ckpt_every), T)
+    n_seg = -(-T // ck)
+    want = need
+    if not reversible and n_seg > 1 and N > 0:
+        exps = 2 * N * (T // 8) if rows == 12 else 0
+        seg = need - exps - 8 * rows * N * (n_seg + 1)      # the step states of one segment
+        want += seg * max(0, min(n_seg - 1, (KEEP_BYTES - need) // seg))
+    if want > need:
+        try:
+            return torch.empty((want,), dtype=torch.uint8, device=dev)
+        except torch.OutOfMemoryError:
+            pass
+    return torch.empty((max(need, 8),), dtype=torch.uint8, device=dev)
+
+
 def indicator_grad(ens: Ensemble, ic: torch.Tensor, grad_J: Optional[torch.Tensor] = None,
                    ckpt_every: int = 100, tuning: Optional[Tuning] = None,
                    workspace: Optional[torch.Tensor] = None, reversible: bool = False):
@@ -349,7 +373,7 @@ def indicator_grad(ens: Ensemble, ic: torch.Tensor, grad_J: Optional[torch.Tenso
         _dev_f64(grad_J, (N,), "grad_J")
     nb = grad_workspace_bytes(ens, ckpt_every, reversible)
     if workspace is None or workspace.numel() * workspace.element_size() < nb:
-        workspace = torch.empty((max(nb, 8),), dtype=torch.uint8, device=ic.device)
+        workspace = _adjoint_workspace(ens, ckpt_every, nb, 6, reversible, ic.device)
     J = torch.empty((N,), dtype=torch.float64, device=ic.device)
     gic = torch.empty((6, N), dtype=torch.float64, device=ic.device)
     geps = torch.empty((N,), dtype=torch.float64, device=ic.device)
@@ -416,7 +440,7 @@ def ftle_grad(ens: Ensemble, ic: torch.Tensor, w0: Optional[torch.Tensor] = None
         _dev_f64(grad_L, (N,), "grad_L")
     nb = ftle_grad_workspace_bytes(ens, ckpt_every, reversible)
     if workspace is None or workspace.numel() * workspace.element_size() < nb:
-        workspace = torch.empty((max(nb, 8),), dtype=torch.uint8, device=ic.device)
+        workspace = _adjoint_workspace(ens, ckpt_every, nb, 12, reversible, ic.device)
     L = torch.empty((N,), dtype=torch.float64, device=ic.device)
     gic = torch.empty((6, N), dtype=torch.float64, device=ic.device)
     geps = torch.empty((N,), dtype=torch.float64, device=ic.device)

@@ -3,11 +3,12 @@
 // state and eps, for the maps of aw_fwd.hip.
 //
 // Forward kernel: one lane per orbit runs the map (no tangent), accumulates J
-// and stores the state at the start of every segment of `ckpt` steps.
-// Backward kernel: one lane per orbit walks the segments from the last one;
-// for each it recomputes the segment from its checkpoint, keeping the end
-// state of every ADJ_SUB-th step (and of the segment's last step), then sweeps
-// the steps backwards.  The stages are undone in reverse order by inverting
+// and stores the state at the start of every segment of `ckpt` steps.  In the
+// last segments, as many as the workspace has room for, it also keeps the end
+// state of every ADJ_SUB-th step (and of the segment's last step).
+// Backward kernel: one lane per orbit walks the segments from the last one; a
+// segment whose states were not kept it recomputes from its checkpoint, keeping
+// the same ones, then it sweeps the steps backwards.  The stages are undone in reverse order by inverting
 // them exactly in exact arithmetic (drift: X -= t P; kick: P += t eps grad
 // Hp(X)), starting from the kept state at the end of each group of ADJ_SUB
 // steps and carrying the rebuilt state through the group, while the adjoint
@@ -146,10 +147,12 @@ __global__ __launch_bounds__(512) void k_adj_fwd(AdjDesc d) {
     store6(d.ckpts + s * 6 * d.N, d.N, n, o);
     const int64_t g0 = s * d.ckpt;
     const int64_t g1 = g0 + d.ckpt < d.T ? g0 + d.ckpt : d.T;
+    const bool keep = s >= d.keep_from;
+    double *steps = d.steps + adj_steps_at(d, s) * 6 * d.N;
     for (int64_t g = g0; g < g1; ++g) {
       adj_step_fwd<FORM>(o, d, s_tab);
       accum_j_node(o);
-      if (d.fwd_steps && adj_kept(g, g1)) store6(d.steps + adj_slot(g, 0) * 6 * d.N, d.N, n, o);  // one segment
+      if (keep && adj_kept(g, g1)) store6(steps + adj_slot(g, g0) * 6 * d.N, d.N, n, o);
     }
   }
   store6(d.ckpts + d.n_seg * 6 * d.N, d.N, n, o);   // the final state
@@ -231,16 +234,17 @@ __global__ __launch_bounds__(512) void k_adj_bwd(AdjDesc d) {
   for (int64_t s = d.n_seg - 1; s >= 0; --s) {
     const int64_t g0 = s * d.ckpt;
     const int64_t g1 = g0 + d.ckpt < d.T ? g0 + d.ckpt : d.T;
-    if (!d.fwd_steps) {  // else the forward pass has kept the step states already
+    double *steps = d.steps + adj_steps_at(d, s) * 6 * N;
+    if (s < d.keep_from) {  // else the forward pass has kept the step states already
       load6(d.ckpts + s * 6 * N, N, n, o);
       for (int64_t g = g0; g < g1; ++g) {
         adj_step_fwd<FORM>(o, d, s_tab);
-        if (adj_kept(g, g1)) store6(d.steps + adj_slot(g, g0) * 6 * N, N, n, o);
+        if (adj_kept(g, g1)) store6(steps + adj_slot(g, g0) * 6 * N, N, n, o);
       }
     }
     for (int64_t g = g1 - 1; g >= g0; --g) {
       // state after step g: kept, or rebuilt by the inverse of step g + 1
-      if (adj_kept(g, g1)) load6(d.steps + adj_slot(g, g0) * 6 * N, N, n, o);
+      if (adj_kept(g, g1)) load6(steps + adj_slot(g, g0) * 6 * N, N, n, o);
       const double ex = o.px - p0x, ey = o.py - p0y, ez = o.pz - p0z;
       a.pxb = __builtin_fma(c, ex, a.pxb);
       a.pyb = __builtin_fma(c, ey, a.pyb);

@@ -1063,6 +1063,27 @@ aw_status aw_indicator_grad_reversible_workspace(const aw_ensemble *ens, int64_t
   return AW_OK;
 }
 
+// Where the kept step states of a checked adjoint call lie (`rows` doubles per
+// orbit and state): behind the checkpoints, for as many of the last segments
+// as a workspace of `bytes` holds, at least one.  Returns their number.  The
+// same states are kept however many segments the forward pass keeps, so the
+// result does not depend on it.
+static int64_t keep_segments(AdjDesc &d, int rows, size_t bytes, bool reversible) {
+  d.seg_slots = adj_slots_max(d.ckpt);
+  if (reversible) {
+    d.steps = nullptr;
+    d.keep_from = d.n_seg;
+    return 0;
+  }
+  const size_t row = sizeof(double) * (size_t)rows * (size_t)d.N;
+  d.steps = d.ckpts + (size_t)(d.n_seg + 1) * (size_t)rows * (size_t)d.N;
+  const size_t room = row ? bytes / row : 0;                       // states in all
+  const size_t segs = room > (size_t)d.n_seg + 1 ? (room - (size_t)d.n_seg - 1) / (size_t)d.seg_slots : 0;
+  const int64_t kept = std::max<int64_t>(1, (int64_t)std::min<size_t>(segs, (size_t)d.n_seg));
+  d.keep_from = d.n_seg - kept;
+  return kept;
+}
+
 // Validation and descriptor of the adjoint of J (both sweeps).
 static aw_status adj_setup(const aw_ensemble *ens, const double *ic_dev, const double *grad_J_dev, int64_t ckpt_every,
                     double *J_out_dev, double *grad_ic_dev, double *grad_eps_dev, void *workspace_dev,
@@ -1094,7 +1115,7 @@ static aw_status adj_setup(const aw_ensemble *ens, const double *ic_dev, const d
   d.gic = grad_ic_dev;
   d.geps = grad_eps_dev;
   d.ckpts = (double *)workspace_dev;
-  d.steps = reversible ? nullptr : d.ckpts + (size_t)(d.n_seg + 1) * 6 * (size_t)N;
+  keep_segments(d, 6, ws_bytes, reversible);
   return AW_OK;
 }
 
@@ -1106,7 +1127,6 @@ aw_status aw_indicator_grad(const aw_ensemble *ens, const double *ic_dev, const 
   aw_status st = adj_setup(ens, ic_dev, grad_J_dev, ckpt_every, J_out_dev, grad_ic_dev, grad_eps_dev, workspace_dev,
                            ws_bytes, tuning, "aw_indicator_grad", false, d, t);
   if (st != AW_OK) return st;
-  d.fwd_steps = d.n_seg == 1 ? 1 : 0;
   hipStream_t s = (hipStream_t)stream;
   hipError_t e = launch_adj_forward(d, ens->map_form, t, s);
   if (e != hipSuccess) return hip_fail(e, "adjoint forward launch");
@@ -1195,13 +1215,10 @@ static aw_status ftle_setup(const aw_ensemble *ens, const double *ic_dev, const 
   d.gic = grad_ic_dev;
   d.geps = grad_eps_dev;
   d.ckpts = (double *)workspace_dev;
-  if (reversible) {
-    d.steps = nullptr;
-    d.exps = (int16_t *)(d.ckpts + (size_t)(d.n_seg + 1) * 12 * (size_t)N);
-  } else {
-    d.steps = d.ckpts + (size_t)(d.n_seg + 1) * 12 * (size_t)N;
-    d.exps = (int16_t *)(d.steps + (size_t)adj_slots_max(d.ckpt) * 12 * (size_t)N);
-  }
+  // the kept step states, then the rescale exponents
+  const size_t exps = sizeof(int16_t) * (size_t)N * (size_t)(d.T / 8);
+  const int64_t kept = keep_segments(d, 12, ws_bytes - std::min(ws_bytes, exps), reversible);
+  d.exps = (int16_t *)(d.ckpts + (size_t)(d.n_seg + 1 + kept * d.seg_slots) * 12 * (size_t)N);
   return AW_OK;
 }
 
@@ -1213,7 +1230,6 @@ aw_status aw_ftle_grad(const aw_ensemble *ens, const double *ic_dev, const doubl
   aw_status st = ftle_setup(ens, ic_dev, w0_dev, grad_L_dev, ckpt_every, L_out_dev, grad_ic_dev, grad_eps_dev,
                             workspace_dev, ws_bytes, tuning, "aw_ftle_grad", false, d, t);
   if (st != AW_OK) return st;
-  d.fwd_steps = d.n_seg == 1 ? 1 : 0;
   hipStream_t s = (hipStream_t)stream;
   hipError_t e = launch_ftle_forward(d, ens->map_form, t, s);
   if (e != hipSuccess) return hip_fail(e, "FTLE-gradient forward launch");

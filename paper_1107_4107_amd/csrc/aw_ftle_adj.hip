@@ -28,11 +28,13 @@
 // tangent, so it matches the forward pass exactly.
 //
 // Forward kernel: one lane per orbit runs the map with its tangent, stores
-// (s, w) at the start of every segment of `ckpt` steps and writes L.
-// Backward kernel: one lane per orbit walks the segments from the last; for
-// each it recomputes the segment from its checkpoint, keeping (s, w) at the
-// end of every ADJ_SUB-th step and of the segment's last step (before any
-// rescale), then sweeps the steps backwards, undoing each stage by its exact
+// (s, w) at the start of every segment of `ckpt` steps and writes L.  In the
+// last segments, as many as the workspace has room for, it also keeps (s, w)
+// at the end of every ADJ_SUB-th step and of the segment's last step (before
+// any rescale).
+// Backward kernel: one lane per orbit walks the segments from the last; a
+// segment whose states were not kept it recomputes from its checkpoint, keeping
+// the same ones, then it sweeps the steps backwards, undoing each stage by its exact
 // inverse (drift: X -= t P, dX -= t dP; kick: P -= the kick's increment,
 // dP -= M dX) from the kept state at the end of each group of steps, while the
 // adjoint above is propagated.  Each lane only reads back what it wrote itself.
@@ -261,9 +263,11 @@ __global__ __launch_bounds__(512) void k_ftle_fwd(FtleDesc d) {
     store12(d.ckpts + s * 12 * N, N, n, o);
     const int64_t g0 = s * d.ckpt;
     const int64_t g1 = g0 + d.ckpt < d.T ? g0 + d.ckpt : d.T;
+    const bool keep = s >= d.keep_from;
+    double *steps = d.steps + adj_steps_at(d, s) * 12 * N;
     for (int64_t g = g0; g < g1; ++g) {
       tan_step<FORM>(o, d, s_tab);
-      if (d.fwd_steps && adj_kept(g, g1)) store12(d.steps + adj_slot(g, 0) * 12 * N, N, n, o);  // one segment
+      if (keep && adj_kept(g, g1)) store12(steps + adj_slot(g, g0) * 12 * N, N, n, o);
       if (((g + 1) & RESCALE_MASK) == 0) {
         const int k0 = o.kexp;
         renorm_node(o);
@@ -296,18 +300,19 @@ __global__ __launch_bounds__(512) void k_ftle_bwd(FtleDesc d) {
   for (int64_t s = d.n_seg - 1; s >= 0; --s) {
     const int64_t g0 = s * d.ckpt;
     const int64_t g1 = g0 + d.ckpt < d.T ? g0 + d.ckpt : d.T;
-    if (!d.fwd_steps) {  // else the forward pass has kept the step states already
+    double *steps = d.steps + adj_steps_at(d, s) * 12 * N;
+    if (s < d.keep_from) {  // else the forward pass has kept the step states already
       load12(d.ckpts + s * 12 * N, N, n, o);
       for (int64_t g = g0; g < g1; ++g) {
         tan_step<FORM>(o, d, s_tab);
-        if (adj_kept(g, g1)) store12(d.steps + adj_slot(g, g0) * 12 * N, N, n, o);
+        if (adj_kept(g, g1)) store12(steps + adj_slot(g, g0) * 12 * N, N, n, o);
         if (((g + 1) & RESCALE_MASK) == 0) renorm_node(o);
       }
     }
     for (int64_t g = g1 - 1; g >= g0; --g) {
       // end of step g, before any rescale: kept (every rescale step is kept,
       // since ADJ_SUB divides 8), or rebuilt by the inverse of step g + 1
-      if (adj_kept(g, g1)) load12(d.steps + adj_slot(g, g0) * 12 * N, N, n, o);
+      if (adj_kept(g, g1)) load12(steps + adj_slot(g, g0) * 12 * N, N, n, o);
       if (g == d.T - 1) {
         // dL/dw_T = w_T / |w_T|^2 (scaled by the upstream gradient).
         end_condition(o, a, gl);

@@ -157,9 +157,17 @@ struct AdjDesc {
   double *gic;            // [6][N]
   double *geps;           // [N]
   double *ckpts;          // [n_seg + 1][6][N] (the last slot: the final state)
-  double *steps;          // [adj_slots_max(ckpt)][6][N] (kept step states of a segment)
-  int32_t fwd_steps;      // 1: one segment, and the forward pass stores the step
-                          // states itself, so that the store sweep skips its recompute
+  double *steps;          // [n_seg - keep_from][seg_slots][6][N] (kept step states; see adj_steps_at)
+  int64_t keep_from;      // the forward pass keeps the step states of segments >= keep_from itself, so
+                          // that the store sweep recomputes only the earlier ones
+  int64_t seg_slots;      // adj_slots_max(ckpt)
 };
+
+// First slot of segment s in the buffer of kept step states.  The segments the
+// forward pass keeps lie one after the other; a recomputed segment takes the
+// place of the first of them, which the sweep is done with by then.
+__host__ __device__ inline int64_t adj_steps_at(const AdjDesc &d, int64_t s) {
+  return s > d.keep_from ? (s - d.keep_from) * d.seg_slots : 0;
+}
 
 }  // namespace aw
