@@ -77,7 +77,10 @@ __device__ __forceinline__ void rev_drift(Orbit &o, Adjoint &a, double wu, doubl
 template <bool EPS0>
 __device__ __forceinline__ void rev_kick(Orbit &o, Adjoint &a, double ka, double kb, double kt, double ktb,
                                          const double2 *__restrict__ tab) {
-  const NodeSC U = sincos_node(o.x, tab), V = sincos_node(o.y, tab), Z = sincos_node(o.z, tab);
+  NodeSC sc[3];
+  const double ang[3] = {o.x, o.y, o.z};
+  sincos_nodes<3>(ang, sc, tab);
+  const NodeSC U = sc[0], V = sc[1], Z = sc[2];
   const double e1 = __builtin_fma(ka, Z.c, ka);
   const double e2 = kb * Z.s;
   const double cs = U.c + V.c;

@@ -101,11 +101,36 @@ __device__ __forceinline__ NodeSC turn_node(double2 e, double r) {
   return o;
 }
 
-__device__ __forceinline__ NodeSC sincos_node(double a, const double2 *__restrict__ tab) {
-  const double m = a + AW_ROUND_MAGIC;
-  const double q = m - AW_ROUND_MAGIC;
-  const double2 e = *(const double2 *)((const char *)tab + node_offset(m));
-  return turn_node(e, a - q);
+// The sines and cosines of K angles, in three phases that the instruction
+// scheduler may not mix: every angle's table read, then the remainders and
+// coefficients while the reads are on their way, then the shears of all angles
+// in step.  Left to itself it serialises the angles to save registers, which
+// costs a wave that has its SIMD to itself the read's latency per angle and 8.7
+// cycles per dependent instruction instead of 5.3 per independent one.  4096
+// orbits x 900 steps: 1.22 -> 1.01 ms; four waves per SIMD gain 2-7%.
+template <int K>
+__device__ __forceinline__ void sincos_nodes(const double (&a)[K], NodeSC (&o)[K], const double2 *__restrict__ tab) {
+  double m[K], r[K], w[K], t[K];
+  double2 e[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) m[k] = a[k] + AW_ROUND_MAGIC;
+#pragma unroll
+  for (int k = 0; k < K; ++k) e[k] = *(const double2 *)((const char *)tab + node_offset(m[k]));
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    r[k] = a[k] - (m[k] - AW_ROUND_MAGIC);
+    const double u = r[k] * r[k];
+    w[k] = r[k] * __builtin_fma(AW_NODE_W[1], u, AW_NODE_W[0]);
+    t[k] = r[k] * __builtin_fma(AW_NODE_T[1], u, AW_NODE_T[0]);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int k = 0; k < K; ++k) o[k].c = __builtin_fma(-t[k], e[k].x, e[k].y);
+#pragma unroll
+  for (int k = 0; k < K; ++k) o[k].s = __builtin_fma(w[k], o[k].c, e[k].x);
+#pragma unroll
+  for (int k = 0; k < K; ++k) o[k].c = __builtin_fma(-t[k], o[k].s, o[k].c);
 }
 
 // x times a constant held in two parts, rounded once (to within 2^-100).
@@ -172,7 +197,10 @@ struct Orbit {
 // steps 5.45 ms instead of 6.35.
 template <bool TAN>
 __device__ __forceinline__ void kick_node(Orbit &o, double a, double b, const double2 *__restrict__ tab) {
-  const NodeSC U = sincos_node(o.x, tab), V = sincos_node(o.y, tab), Z = sincos_node(o.z, tab);
+  NodeSC sc[3];
+  const double ang[3] = {o.x, o.y, o.z};
+  sincos_nodes<3>(ang, sc, tab);
+  const NodeSC U = sc[0], V = sc[1], Z = sc[2];
   const double e1 = __builtin_fma(a, Z.c, a);
   const double e2 = b * Z.s;
   const double cs = U.c + V.c;

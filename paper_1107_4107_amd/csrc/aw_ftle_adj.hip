@@ -117,7 +117,10 @@ __device__ __forceinline__ void rev_drift2(Orbit &o, Adjoint2 &a, double wu, dou
 template <bool EPS0>
 __device__ __forceinline__ void rev_kick2(Orbit &o, Adjoint2 &a, double ka, double kb, double kt, double ktb,
                                           const double2 *__restrict__ tab) {
-  const NodeSC U = sincos_node(o.x, tab), V = sincos_node(o.y, tab), Z = sincos_node(o.z, tab);
+  NodeSC sc[3];
+  const double ang[3] = {o.x, o.y, o.z};
+  sincos_nodes<3>(ang, sc, tab);
+  const NodeSC U = sc[0], V = sc[1], Z = sc[2];
   const double e1 = __builtin_fma(ka, Z.c, ka);
   const double e2 = kb * Z.s;
   const double g = __builtin_fma(2.0, e1, -2.0 * ka);

@@ -445,7 +445,10 @@ struct HalfOrbit {
 };
 
 __device__ __forceinline__ void pair_kick(HalfOrbit &h, double a, double b, const double2 *__restrict__ tab) {
-  const NodeSC W = sincos_node(h.w, tab), Z = sincos_node(h.z, tab);
+  NodeSC sc[2];
+  const double ang[2] = {h.w, h.z};
+  sincos_nodes<2>(ang, sc, tab);
+  const NodeSC W = sc[0], Z = sc[1];
   const double e1 = __builtin_fma(a, Z.c, a);
   const double e2 = b * Z.s;
   const double cs = W.c + swap_pair(W.c);

@@ -97,9 +97,11 @@ __global__ __launch_bounds__(BLOCK) void k_sincos_node(const double* __restrict_
   aw::load_sincos_table(tab);
   const int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
   if (i >= n) return;
-  const aw::NodeSC r = aw::sincos_node(a[i], tab);
-  s[i] = r.s;
-  c[i] = r.c;
+  const double x[1] = {a[i]};
+  aw::NodeSC r[1];
+  aw::sincos_nodes<1>(x, r, tab);
+  s[i] = r[0].s;
+  c[i] = r[0].c;
 }
 
 int fail(hipError_t e, const char* what) {
