@@ -154,11 +154,13 @@ typedef struct {
 /* Launch shape.  NULL or zero fields = defaults (automatic block, one orbit
  * per lane, step loop not unrolled, renormalisation every 8 steps).  block in
  * {0, 64, 128, 256, 512}: the kernels hold a 64 KB sine/cosine table per
- * block, so blocks of 512 lanes are needed for a full CU; 0 picks 512 when
- * the ensemble gives every CU at least one such block, else the largest of
- * 256, 128 and 64 that still does.  The window-test and time-window
- * propagation and the batched persistent launch run a block above 256 (or
- * automatic) as 256.  orbits_per_lane in {1, 2}; unroll in {1, 2};
+ * block, so blocks of 512 lanes are needed for a full CU.  The propagation runs
+ * every wave on a tile of its own; 0 picks blocks of 512 there, with as many
+ * waves at work as there are tiles.  The adjoints run one orbit per lane of a
+ * block; 0 picks 512 when the ensemble gives every CU at least one such block,
+ * else the largest of 256, 128 and 64 that still does.  orbits_per_lane in
+ * {1, 2}; unroll in {1, 2}; the window-test and time-window propagation run
+ * one orbit per lane, not unrolled.
  * renorm_every in {1, 2, 4, 8, 16}.  persistent_wgs: workgroups of the batched
  * persistent launch (0 = auto).  lanes_per_orbit in {0, 1, 2}: tangent-free
  * launches that end before n_steps (aw_map_ensemble_steps) or bin time windows
@@ -186,8 +188,8 @@ aw_status aw_generate_ic(const aw_ensemble *ens, const double *ic_in_dev,
 
 /* Propagate ensembles for their n_steps and write per-orbit outputs.
  * n_ens >= 1 descriptors; with n_ens > 1 every ensemble must share map_form
- * and flags, and all of them run in ONE persistent launch whose workgroups
- * take (ensemble, tile) items, longest first, from a device queue.
+ * and flags, and all of them run in ONE persistent launch whose waves take
+ * tiles of the ensembles, the longest runs first, from a device queue.
  *   ic_dev[e]        EXPLICIT: [6][N_e], else ignored (the array may be NULL)
  *   orbit_out_dev[e] [AW_NOUT][N_e] or NULL
  *   state_out_dev[e] [12][N_e] (X, P, unit tangent) or NULL

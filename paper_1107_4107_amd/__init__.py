@@ -122,8 +122,8 @@ class Ensemble:
 
 @dataclass
 class Tuning:
-    """Launch shape (aw_tuning); zeros mean library defaults (block 0: chosen
-    from the ensemble size, 512 for large ensembles)."""
+    """Launch shape (aw_tuning); zeros mean library defaults (block 0: 512 lanes
+    for the propagation, chosen from the ensemble size for the adjoints)."""
     block: int = 0
     orbits_per_lane: int = 1
     unroll: int = 1

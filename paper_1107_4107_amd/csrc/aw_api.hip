@@ -52,17 +52,17 @@ struct Layout {
   size_t chunk_first = 0, part_first = 0, chunk_tile = 0;  // accumulation chunks
   size_t part_counts = 0, part_sums = 0;                   // partial tiles
   size_t sorted_local = 0, sorted_val = 0;                 // the largest single reduction
-  size_t descs = 0, items = 0, head = 0;                   // tables of a batched launch
+  size_t descs = 0, ends = 0, head = 0;                    // tables of a batched launch
   size_t total = 0;
 };
 
 // hist: histogram images over n_all orbits in all, of which one reduction
 // sorts at most n_max items into n_tiles tiles; vals: the items carry values;
 // vals_here: the items' values are kept in the area (written by the
-// propagation), not read from the caller; n_descs, n_items: tables of a
-// batched launch (0 for none).
+// propagation), not read from the caller; n_descs: ensembles of a batched
+// launch (0 for none).
 constexpr Layout layout_of(bool hist, bool vals, bool vals_here, int64_t n_all, int64_t n_max, int64_t n_tiles,
-                           size_t n_descs, size_t n_items) {
+                           size_t n_descs) {
   Layout l{};
   size_t o = 0;
   if (hist) {
@@ -104,10 +104,10 @@ constexpr Layout layout_of(bool hist, bool vals, bool vals_here, int64_t n_all, 
   if (n_descs > 0) {
     l.descs = o;
     o += align_up(sizeof(FwdDesc) * n_descs);
-    l.items = o;
-    o += align_up(sizeof(WorkItem) * (n_items ? n_items : 1));
+    l.ends = o;
+    o += align_up(sizeof(int64_t) * n_descs);
     l.head = o;
-    o += align_up(sizeof(uint32_t));
+    o += align_up(sizeof(unsigned long long));
   }
   l.total = o;
   return l;
@@ -442,10 +442,15 @@ FwdDesc make_desc(const aw_ensemble &e, const double *ic, const Tuning &t) {
   d.filter = (e.flags & AW_F_WINDOW) ? 1 : 0;
   if (d.filter) {
     const double w = e.window[1] - e.window[0];
-    d.e0x = std::cos(e.window[0]);
-    d.e0y = std::sin(e.window[0]);
-    d.e1x = std::cos(e.window[1]);
-    d.e1y = std::sin(e.window[1]);
+    // 2 p_x = p_u + p_v, 2 p_y = p_u - p_v
+    const double e0x = std::cos(e.window[0]), e0y = std::sin(e.window[0]);
+    const double e1x = std::cos(e.window[1]), e1y = std::sin(e.window[1]);
+    d.c0u = e0x - e0y;
+    d.c0v = -(e0x + e0y);
+    d.c1u = e1y - e1x;
+    d.c1v = e1y + e1x;
+    d.mu2_lo = e.window[2] * std::fabs(e.window[2]);
+    d.mu2_hi = e.window[3] * std::fabs(e.window[3]);
     d.win_phi = (e.window[0] == -M_PI && e.window[1] == M_PI) ? 0 : (w <= M_PI ? 1 : 2);
     d.win_mu = (e.window[2] == -1.0 && e.window[3] == 1.0) ? 0 : 1;
   }
@@ -464,40 +469,35 @@ aw_status launch_one(const FwdDesc &d, const Tuning &t, int form, bool tan, hipS
   return AW_OK;
 }
 
-// Batched persistent launch of descs (host copies) over n ensembles.
+// Tables of a batched launch, as they lie in the area: the descriptors sorted
+// by their step counts, longest first (a tile's cost), and the running number
+// of tiles.
 struct BatchTables {
-  std::vector<WorkItem> items;
-  int form = 6;
-  bool tan = true;
+  std::vector<FwdDesc> descs;
+  std::vector<int64_t> ends;
+  int64_t tiles() const { return ends.back(); }
 };
 
-BatchTables make_items(const std::vector<FwdDesc> &descs, const Tuning &t) {
+BatchTables make_tables(const std::vector<FwdDesc> &descs, const Tuning &t) {
   BatchTables b;
-  const int64_t per = (int64_t)block_256(t) * t.opl;
-  for (size_t e = 0; e < descs.size(); ++e)
-    for (int64_t f = 0; f < descs[e].N; f += per) b.items.push_back(WorkItem{(int32_t)e, 0, f});
-  // Longest processing time first: a tile's cost is its step count.
-  std::stable_sort(b.items.begin(), b.items.end(), [&](const WorkItem &a, const WorkItem &c) {
-    return descs[a.ens].T > descs[c.ens].T;
-  });
+  b.descs = descs;
+  std::stable_sort(b.descs.begin(), b.descs.end(), [](const FwdDesc &x, const FwdDesc &y) { return x.T > y.T; });
+  const int64_t per = 64 * (int64_t)t.opl;
+  int64_t n = 0;
+  for (const FwdDesc &d : b.descs) b.ends.push_back(n += (d.N + per - 1) / per);
   return b;
 }
 
 int persistent_wgs(int form, bool tan, const Tuning &t) {
   if (t.pwgs > 0) return t.pwgs;
-  int dev = 0, ncu = 0;
-  (void)hipGetDevice(&dev);
-  if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu <= 0)
-    ncu = 256;
-  return ncu * persistent_blocks_per_cu(form, tan, t);
+  return n_cus() * persistent_blocks_per_cu(form, tan, t);
 }
 
-// Copy the batch tables into the area (at l.descs and l.items) through one of
+// Copy the batch tables into the area (at l.descs and l.ends) through one of
 // the stream's pinned staging buffers: one whose earlier copies have finished,
 // or a new one -- the host never waits for the device here.
-aw_status upload_tables(StreamScratch &sc, const Layout &l, const std::vector<FwdDesc> &descs,
-                        const std::vector<WorkItem> &items, hipStream_t s) {
-  const size_t bd = descs.size() * sizeof(FwdDesc), bi = items.size() * sizeof(WorkItem);
+aw_status upload_tables(StreamScratch &sc, const Layout &l, const BatchTables &b, hipStream_t s) {
+  const size_t bd = b.descs.size() * sizeof(FwdDesc), bi = b.ends.size() * sizeof(int64_t);
   hipError_t e;
   Stage *st = nullptr;
   for (Stage &c : sc.stages) {
@@ -520,23 +520,32 @@ aw_status upload_tables(StreamScratch &sc, const Layout &l, const std::vector<Fw
     sc.stages.push_back(c);
     st = &sc.stages.back();
   }
-  std::memcpy(st->p, descs.data(), bd);
-  std::memcpy((char *)st->p + bd, items.data(), bi);
+  std::memcpy(st->p, b.descs.data(), bd);
+  std::memcpy((char *)st->p + bd, b.ends.data(), bi);
   char *base = (char *)sc.area;
   if ((e = hipMemcpyAsync(base + l.descs, st->p, bd, hipMemcpyHostToDevice, s)) != hipSuccess ||
-      (e = hipMemcpyAsync(base + l.items, (char *)st->p + bd, bi, hipMemcpyHostToDevice, s)) != hipSuccess)
+      (e = hipMemcpyAsync(base + l.ends, (char *)st->p + bd, bi, hipMemcpyHostToDevice, s)) != hipSuccess)
     return hip_fail(e, "batch table upload");
   if ((e = hipEventRecord(st->done, s)) != hipSuccess) return hip_fail(e, "hipEventRecord");
   return AW_OK;
 }
 
-aw_status launch_batched_tables(const FwdDesc *descs_dev, const WorkItem *items_dev, int32_t n_items,
-                                uint32_t *head, const Tuning &t, int form, bool tan, hipStream_t s) {
-  const int nwg = std::max(1, std::min<int>(persistent_wgs(form, tan, t), n_items));
+// The batched launch of tables that lie (or arrive, earlier on the stream) in
+// the area at `base`.  timed: record it for aw_timing_read.
+aw_status launch_batched_tables(const BatchTables &b, const Layout &l, char *base, const Tuning &t, int form, bool tan,
+                                hipStream_t s, bool timed) {
+  const int64_t nw = block_512(t) >> 6;
+  const int nwg = (int)std::min<int64_t>(persistent_wgs(form, tan, t), (b.tiles() + nw - 1) / nw);
+  auto launch = [&] {
+    return launch_fwd_batched((const FwdDesc *)(base + l.descs), (const int64_t *)(base + l.ends),
+                              (int32_t)b.descs.size(), (unsigned long long *)(base + l.head), t, form, tan, nwg, s);
+  };
   hipError_t err;
-  {
+  if (timed) {
     TimedLaunch tl(s);
-    err = launch_fwd_batched(descs_dev, items_dev, n_items, head, t, form, tan, nwg, s);
+    err = launch();
+  } else {
+    err = launch();
   }
   if (err != hipSuccess) return hip_fail(err, "persistent launch");
   return AW_OK;
@@ -617,13 +626,13 @@ aw_status apply_image(const aw_image_spec *sp, const aw_ensemble &e, int idx, Fw
   return AW_OK;
 }
 
-// One image call: validated descriptors, work items and scratch layout.
+// One image call: validated descriptors, batch tables and scratch layout.
 // batched: one persistent launch over every ensemble, their histogram items
 // side by side in the area; otherwise the ensembles run one after the other,
 // each reusing the same part of the area (stream order keeps them apart).
 struct ImageCall {
-  std::vector<FwdDesc> descs;
-  std::vector<WorkItem> items;
+  std::vector<FwdDesc> descs;  // in the caller's order
+  BatchTables tables;          // (batched only)
   std::vector<int64_t> off;  // first item of each ensemble in the bins array
   Layout lay;
   bool hist = false, vals = false, batched = false;
@@ -652,20 +661,21 @@ aw_status prepare_image(const aw_ensemble *ens, int32_t n_ens, const aw_image_sp
     n_max = std::max<int64_t>(n_max, c.descs[e].N);
   }
   if (c.hist) c.n_tiles = hist_plan(n_max, spec->W, spec->H).n_tiles;
-  if (c.batched) c.items = make_items(c.descs, t).items;
   const int64_t n_all = c.batched ? c.off[n_ens] : n_max;
-  c.lay = layout_of(c.hist, c.vals, true, n_all, n_max, c.n_tiles, c.batched ? c.descs.size() : 0,
-                    c.batched ? c.items.size() : 0);
+  c.lay = layout_of(c.hist, c.vals, true, n_all, n_max, c.n_tiles, c.batched ? c.descs.size() : 0);
   return AW_OK;
 }
 
-// Point the descriptors' histogram items into the area at `base`.
-void place_image(ImageCall &c, char *base) {
-  if (!c.hist) return;
-  for (size_t e = 0; e < c.descs.size(); ++e) {
-    c.descs[e].bins = (uint32_t *)(base + c.lay.bins) + c.off[e];
-    c.descs[e].vals = c.vals ? (double *)(base + c.lay.vals) + c.off[e] : nullptr;
+// Point the descriptors' histogram items into the area at `base`, and make the
+// batch tables of the descriptors as they then are.
+void place_image(ImageCall &c, char *base, const Tuning &t) {
+  if (c.hist) {
+    for (size_t e = 0; e < c.descs.size(); ++e) {
+      c.descs[e].bins = (uint32_t *)(base + c.lay.bins) + c.off[e];
+      c.descs[e].vals = c.vals ? (double *)(base + c.lay.vals) + c.off[e] : nullptr;
+    }
   }
+  if (c.batched) c.tables = make_tables(c.descs, t);
 }
 
 // Histogram reduction of ensemble e's items into its image.
@@ -681,7 +691,7 @@ hipError_t reduce_image(const ImageCall &c, char *base, int e, const aw_image_sp
 }
 
 // Enqueue a prepared and placed image call.  A batched call needs its tables
-// at lay.descs / lay.items of the area already (or on their way, earlier on
+// at lay.descs / lay.ends of the area already (or on their way, earlier on
 // the stream).  timed: record the propagation launches for aw_timing_read
 // (never inside a graph capture).
 aw_status enqueue_image(const ImageCall &c, char *base, const aw_image_spec *spec, double *const *image,
@@ -707,21 +717,7 @@ aw_status enqueue_image(const ImageCall &c, char *base, const aw_image_spec *spe
     }
     return AW_OK;
   }
-  for (int e = 0; e < n_ens; ++e)
-    if ((st = zero_counter(c.descs[e])) != AW_OK) return st;
-  if (!c.items.empty()) {
-    const FwdDesc *dd = (const FwdDesc *)(base + c.lay.descs);
-    const WorkItem *di = (const WorkItem *)(base + c.lay.items);
-    uint32_t *head = (uint32_t *)(base + c.lay.head);
-    if (timed) {
-      st = launch_batched_tables(dd, di, (int32_t)c.items.size(), head, t, c.form, c.tan, s);
-    } else {
-      const int nwg = std::max(1, std::min<int>(persistent_wgs(c.form, c.tan, t), (int)c.items.size()));
-      herr = launch_fwd_batched(dd, di, (int32_t)c.items.size(), head, t, c.form, c.tan, nwg, s);
-      st = herr == hipSuccess ? AW_OK : hip_fail(herr, "persistent launch");
-    }
-    if (st != AW_OK) return st;
-  }
+  if ((st = launch_batched_tables(c.tables, c.lay, base, t, c.form, c.tan, s, timed)) != AW_OK) return st;
   if (c.hist)
     for (int e = 0; e < n_ens; ++e)
       if ((herr = reduce_image(c, base, e, spec, image, counts, s)) != hipSuccess)
@@ -740,8 +736,8 @@ aw_status image_run(const aw_ensemble *ens, int32_t n_ens, const aw_image_spec *
   StreamScratch &sc = stream_scratch(s);
   if ((st = reserve_area(sc, c.lay.total)) != AW_OK) return st;
   char *base = (char *)sc.area;
-  place_image(c, base);
-  if (c.batched && !c.items.empty() && (st = upload_tables(sc, c.lay, c.descs, c.items, s)) != AW_OK) return st;
+  place_image(c, base, t);
+  if (c.batched && (st = upload_tables(sc, c.lay, c.tables, s)) != AW_OK) return st;
   return enqueue_image(c, base, spec, image, counts, t, s, true);
 }
 
@@ -822,9 +818,7 @@ aw_status aw_image_workspace(const aw_ensemble *ens, int32_t n_ens, const aw_ima
       *bytes = 0;
       return AW_OK;
     }
-    std::vector<FwdDesc> descs(n_ens);
-    for (int e = 0; e < n_ens; ++e) descs[e] = make_desc(ens[e], nullptr, Tuning{});
-    *bytes = layout_of(false, false, false, 0, 0, 0, descs.size(), make_items(descs, Tuning{}).items.size()).total;
+    *bytes = layout_of(false, false, false, 0, 0, 0, (size_t)n_ens).total;
     return AW_OK;
   }
   std::vector<double> dummy(n_ens, 0.0);
@@ -874,16 +868,14 @@ aw_status aw_map_ensemble(const aw_ensemble *ens, int32_t n_ens, const double *c
   const int form = ens[0].map_form;
   const bool tan = tangent_on(ens[0]);
   if (n_ens == 1) return launch_one(descs[0], t, form, tan, s);
-  BatchTables b = make_items(descs, t);
-  if (b.items.empty()) return AW_OK;
-  const Layout l = layout_of(false, false, false, 0, 0, 0, descs.size(), b.items.size());
+  const BatchTables b = make_tables(descs, t);
+  if (b.tiles() == 0) return AW_OK;
+  const Layout l = layout_of(false, false, false, 0, 0, 0, descs.size());
   std::lock_guard<std::mutex> lk(g_mu);
   StreamScratch &sc = stream_scratch(s);
   if ((st = reserve_area(sc, l.total)) != AW_OK) return st;
-  if ((st = upload_tables(sc, l, descs, b.items, s)) != AW_OK) return st;
-  char *base = (char *)sc.area;
-  return launch_batched_tables((const FwdDesc *)(base + l.descs), (const WorkItem *)(base + l.items),
-                               (int32_t)b.items.size(), (uint32_t *)(base + l.head), t, form, tan, s);
+  if ((st = upload_tables(sc, l, b, s)) != AW_OK) return st;
+  return launch_batched_tables(b, l, (char *)sc.area, t, form, tan, s, true);
 }
 
 aw_status aw_map_ensemble_steps(const aw_ensemble *ens, const double *ic_dev, double *carry_dev, int64_t k_begin,
@@ -946,7 +938,7 @@ aw_status aw_window_density(const aw_ensemble *ens, const double *ic_dev, double
   d.carry = carry_dev;
   hipStream_t s = (hipStream_t)stream;
   const HistPlan p = hist_plan(d.N, spec->W, spec->H);
-  const Layout l = layout_of(true, false, false, d.N, d.N, p.n_tiles, 0, 0);
+  const Layout l = layout_of(true, false, false, d.N, d.N, p.n_tiles, 0);
   std::lock_guard<std::mutex> lk(g_mu);
   StreamScratch &sc = stream_scratch(s);
   if ((st = reserve_area(sc, l.total)) != AW_OK) return st;
@@ -1003,7 +995,7 @@ aw_status aw_histogram2d(int64_t N, const double *a_dev, const double *b_dev, co
   aw_status st = hist2d_check(N, a_dev, b_dev, lo0, hi0, lo1, hi1, W, H, counts_dev, p);
   if (st != AW_OK) return st;
   hipStream_t s = (hipStream_t)stream;
-  const Layout l = layout_of(true, v_dev != nullptr, false, N, N, p.n_tiles, 0, 0);
+  const Layout l = layout_of(true, v_dev != nullptr, false, N, N, p.n_tiles, 0);
   std::lock_guard<std::mutex> lk(g_mu);
   StreamScratch &sc = stream_scratch(s);
   if ((st = reserve_area(sc, l.total)) != AW_OK) return st;
@@ -1018,7 +1010,7 @@ aw_status aw_histogram2d_noalloc(int64_t N, const double *a_dev, const double *b
   HistPlan p;
   aw_status st = hist2d_check(N, a_dev, b_dev, lo0, hi0, lo1, hi1, W, H, counts_dev, p);
   if (st != AW_OK) return st;
-  const Layout l = layout_of(true, v_dev != nullptr, false, N, N, p.n_tiles, 0, 0);
+  const Layout l = layout_of(true, v_dev != nullptr, false, N, N, p.n_tiles, 0);
   if (l.total > (size_t)AW_NOALLOC_SCRATCH_BYTES)
     return fail(AW_EWORKSPACE, "aw_histogram2d_noalloc: %lld items into %d x %d bins need %zu bytes of scratch, "
                                "more than its fixed %zu", (long long)N, W, H, l.total,
@@ -1290,11 +1282,11 @@ aw_status aw_graph_create(const aw_ensemble *ens, int32_t n_ens, const aw_image_
     return cleanup(fail(AW_ENOMEM, "graph scratch of %zu bytes: %s", c.lay.total, hipGetErrorString(e)));
   g->dev_allocs.push_back(area);
   char *base = (char *)area;
-  place_image(c, base);
-  if (c.batched && !c.items.empty()) {
-    if ((e = hipMemcpy(base + c.lay.descs, c.descs.data(), c.descs.size() * sizeof(FwdDesc),
+  place_image(c, base, t);
+  if (c.batched) {
+    if ((e = hipMemcpy(base + c.lay.descs, c.tables.descs.data(), c.tables.descs.size() * sizeof(FwdDesc),
                        hipMemcpyHostToDevice)) != hipSuccess ||
-        (e = hipMemcpy(base + c.lay.items, c.items.data(), c.items.size() * sizeof(WorkItem),
+        (e = hipMemcpy(base + c.lay.ends, c.tables.ends.data(), c.tables.ends.size() * sizeof(int64_t),
                        hipMemcpyHostToDevice)) != hipSuccess)
       return cleanup(hip_fail(e, "graph table upload"));
   }

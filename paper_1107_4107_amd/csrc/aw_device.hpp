@@ -108,7 +108,11 @@ __device__ __forceinline__ NodeSC turn_node(double2 e, double r) {
 // costs a wave that has its SIMD to itself the read's latency per angle and 8.7
 // cycles per dependent instruction instead of 5.3 per independent one.  4096
 // orbits x 900 steps: 1.22 -> 1.01 ms; four waves per SIMD gain 2-7%.
-template <int K>
+// ALIGN puts the remainders, a run of 8-byte instructions, at a multiple of 8
+// bytes: a wave that has its SIMD to itself takes 6% longer per step where the
+// step loop happens to start 4 bytes off (1.17 against 1.10 us per S6 step with
+// the tangent).  Without the tangent the padding costs as much as it gains.
+template <int K, bool ALIGN = false>
 __device__ __forceinline__ void sincos_nodes(const double (&a)[K], NodeSC (&o)[K], const double2 *__restrict__ tab) {
   double m[K], r[K], w[K], t[K];
   double2 e[K];
@@ -117,6 +121,7 @@ __device__ __forceinline__ void sincos_nodes(const double (&a)[K], NodeSC (&o)[K
 #pragma unroll
   for (int k = 0; k < K; ++k) e[k] = *(const double2 *)((const char *)tab + node_offset(m[k]));
   __builtin_amdgcn_sched_barrier(0);
+  if (ALIGN) asm volatile(".p2align 3");
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     r[k] = a[k] - (m[k] - AW_ROUND_MAGIC);
@@ -199,7 +204,7 @@ template <bool TAN>
 __device__ __forceinline__ void kick_node(Orbit &o, double a, double b, const double2 *__restrict__ tab) {
   NodeSC sc[3];
   const double ang[3] = {o.x, o.y, o.z};
-  sincos_nodes<3>(ang, sc, tab);
+  sincos_nodes<3, TAN>(ang, sc, tab);
   const NodeSC U = sc[0], V = sc[1], Z = sc[2];
   const double e1 = __builtin_fma(a, Z.c, a);
   const double e2 = b * Z.s;

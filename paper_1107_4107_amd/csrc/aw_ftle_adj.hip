@@ -119,7 +119,7 @@ __device__ __forceinline__ void rev_kick2(Orbit &o, Adjoint2 &a, double ka, doub
                                           const double2 *__restrict__ tab) {
   NodeSC sc[3];
   const double ang[3] = {o.x, o.y, o.z};
-  sincos_nodes<3>(ang, sc, tab);
+  sincos_nodes<3, true>(ang, sc, tab);
   const NodeSC U = sc[0], V = sc[1], Z = sc[2];
   const double e1 = __builtin_fma(ka, Z.c, ka);
   const double e2 = kb * Z.s;

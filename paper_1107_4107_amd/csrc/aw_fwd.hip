@@ -133,21 +133,26 @@ __device__ __forceinline__ void vdir_key(double vx, double vy, double vz, double
 constexpr double LN2 = 0x1.62e42fefa39efp-1;
 
 // Is the direction of P inside the closed window phi in [phi_lo, phi_hi],
-// mu = pz/|P| in [mu_lo, mu_hi]?  The phi test uses half-plane (cross
+// mu = pz/|P| in [mu_lo, mu_hi]?  On the scaled momenta (p_u, p_v, sqrt 2 p_z),
+// whose squares add up to 2 |P|^2.  The phi test uses half-plane (cross
 // product) tests against the edge directions e0, e1 instead of atan2: for a
 // window of width w <= pi, phi is inside iff e0 x d >= 0 and d x e1 >= 0; for
-// w > pi, iff d is not strictly inside the complementary sector.
-__device__ __forceinline__ bool in_window(double px, double py, double pz, const FwdDesc &d) {
+// w > pi, iff d is not strictly inside the complementary sector.  The mu test
+// compares p |p| against mu |mu| times the sum of squares, which needs no
+// square root: the whole test is 10 FP64 instructions where the rotated-back
+// momentum, its norm and their products took about 100.
+__device__ __forceinline__ bool in_window(double pu, double pv, double pz, const FwdDesc &d) {
 #pragma clang fp contract(off)
   bool ok = true;
   if (d.win_phi != 0) {
-    const double c0 = d.e0x * py - d.e0y * px;   // e0 x d
-    const double c1 = px * d.e1y - py * d.e1x;   // d x e1
+    const double c0 = __builtin_fma(pu, d.c0u, pv * d.c0v);   // 2 e0 x d
+    const double c1 = __builtin_fma(pu, d.c1u, pv * d.c1v);   // 2 d x e1
     ok = d.win_phi == 1 ? (c0 >= 0.0 && c1 >= 0.0) : !(c0 < 0.0 && c1 < 0.0);
   }
   if (d.win_mu != 0) {
-    const double r = sqrt(px * px + py * py + pz * pz);
-    ok = ok && pz >= d.win[2] * r && pz <= d.win[3] * r;
+    const double r2 = __builtin_fma(pu, pu, __builtin_fma(pv, pv, pz * pz));
+    const double q = pz * fabs(pz);
+    ok = ok && q >= d.mu2_lo * r2 && q <= d.mu2_hi * r2;
   }
   return ok;
 }
@@ -168,120 +173,30 @@ __device__ __forceinline__ void carry_to_nodes(Orbit &o) {
   o.dpz = times_sqrt2(o.dpz);
 }
 
-// ---------------------------------------------------------------------------
-// Run the orbits first + j*blockDim.x + threadIdx.x (j < OPL) over global
-// steps [k_begin, k_end).  FILT: test the window after every step.  `tab` is
-// the block's LDS copy of the sine/cosine table (filled by the caller).
-// ---------------------------------------------------------------------------
-template <int FORM, bool TAN, int OPL, int UNR, bool FILT = false, bool WINV = false>
-__device__ __forceinline__ void run_orbits(const FwdDesc &d, int64_t first, const double2 *__restrict__ tab) {
-  int64_t n[OPL];
-  bool act[OPL];
-#pragma unroll
-  for (int j = 0; j < OPL; ++j) {
-    const int64_t m = first + (int64_t)j * blockDim.x + threadIdx.x;
-    act[j] = m < d.N;
-    n[j] = act[j] ? m : d.N - 1;  // inactive slots repeat a valid orbit, never stored
-  }
-  if (!act[0]) return;
+// The descriptor a kernel was launched with, read where it lies in the kernel
+// arguments (it is the first one), and any descriptor read anew: what follows
+// the step loop loads its fields again instead of holding them in scalar
+// registers across the loop, where they would push the stage weights out into
+// vector lanes (24 v_readlane and 8 v_writelane per step with the window test).
+typedef const __attribute__((address_space(4))) FwdDesc *ConstDesc;
 
-  Orbit o[OPL];
-  bool left[OPL];
-#pragma unroll
-  for (int j = 0; j < OPL; ++j) {
-    left[j] = false;
-    if (d.k_begin == 0) {
-      double s[6];
-      gen_ic(d, n[j], s);
-      o[j].x = s[0]; o[j].y = s[1]; o[j].z = s[2];
-      o[j].px = s[3]; o[j].py = s[4]; o[j].pz = s[5];
-      o[j].p0x = s[3]; o[j].p0y = s[4]; o[j].p0z = s[5];
-      o[j].jsum = 0.0;
-      o[j].kexp = 0;
-      if (TAN) {
-        double w[6];
-        gen_w0(d.seed_tan, n[j], w);
-        o[j].dx = w[0]; o[j].dy = w[1]; o[j].dz = w[2];
-        o[j].dpx = w[3]; o[j].dpy = w[4]; o[j].dpz = w[5];
-      } else {
-        o[j].dx = o[j].dy = o[j].dz = o[j].dpx = o[j].dpy = o[j].dpz = 0.0;
-      }
-      if (FILT) left[j] = !in_window(s[3], s[4], s[5], d);
-      to_node(o[j]);
-    } else {
-      // The carry holds the scaled rotated state as the loop left it.
-      const double *c = d.carry;
-      const int64_t N = d.N, m = n[j];
-      const int flags = (int)c[21 * N + m];
-      o[j].x = c[0 * N + m]; o[j].y = c[1 * N + m]; o[j].z = c[2 * N + m];
-      o[j].px = c[3 * N + m]; o[j].py = c[4 * N + m]; o[j].pz = c[5 * N + m];
-      o[j].dx = c[6 * N + m]; o[j].dy = c[7 * N + m]; o[j].dz = c[8 * N + m];
-      o[j].dpx = c[9 * N + m]; o[j].dpy = c[10 * N + m]; o[j].dpz = c[11 * N + m];
-      o[j].p0x = c[15 * N + m]; o[j].p0y = c[16 * N + m]; o[j].p0z = c[17 * N + m];
-      o[j].jsum = c[18 * N + m];
-      o[j].kexp = (int)c[19 * N + m];
-      if (FILT) left[j] = (flags & CARRY_LEFT) != 0;
-      if (!(flags & CARRY_NODES)) carry_to_nodes(o[j]);
-    }
-  }
+__device__ __forceinline__ const FwdDesc &launched_desc() {
+  return *(const FwdDesc *)(ConstDesc)__builtin_amdgcn_kernarg_segment_ptr();
+}
 
-  // Positions at the start of this launch (time-window velocity; scaled frame).
-  double xs[OPL], ys[OPL], zs[OPL];
-  if (WINV) {
-#pragma unroll
-    for (int j = 0; j < OPL; ++j) {
-      xs[j] = o[j].x;
-      ys[j] = o[j].y;
-      zs[j] = o[j].z;
-    }
-  }
+__device__ __forceinline__ const FwdDesc &reread(const FwdDesc &d) {
+  uint64_t p = (uint64_t)(uintptr_t)&d;
+  asm volatile("" : "+s"(p));
+  return *(const FwdDesc *)(ConstDesc)p;
+}
 
-  // Hot loop.  The trip count and the renormalisation test are uniform.
-  // UNR = 2 runs steps in pairs plus a one-step tail, written out: the table
-  // offset is inline assembly, which the compiler treats as convergent and
-  // will not unroll with a remainder.
-  const int64_t k0 = d.k_begin, k1 = d.k_end;
-  const int64_t mask = d.renorm_mask;
-  // Stage weights.  In the plain tangent kernel they move into VGPRs (an empty
-  // asm the compiler must treat as producing per-lane values): left in SGPRs,
-  // which the epilogue's descriptor fields hold across the loop, they are
-  // spilled and read back every step.  A block of 512 leaves 256 VGPRs a lane.
-  // The unrolled, two-orbit and window variants would lose occupancy and keep
-  // them in SGPRs.
-  constexpr bool kVregW = TAN && OPL == 1 && UNR == 1 && !FILT && !WINV;
-  StepWeights sw = d.w;
-  if (kVregW) {
-#pragma unroll
-    for (int q = 0; q < MAX_UNIQUE; ++q)
-      asm volatile("" : "+v"(sw.drift[q]), "+v"(sw.dnode[q]), "+v"(sw.dnodez[q]), "+v"(sw.ka[q]), "+v"(sw.kb[q]));
-  }
-  auto one_step = [&](int64_t k) {
-    map_step<FORM, TAN, OPL>(o, sw, tab);
-#pragma unroll
-    for (int j = 0; j < OPL; ++j) accum_j_node(o[j]);
-    if (FILT) {
-      // 2 P in the original frame: the window test depends only on the
-      // direction of P.
-#pragma unroll
-      for (int j = 0; j < OPL; ++j)
-        left[j] = left[j] || !in_window(o[j].px + o[j].py, o[j].px - o[j].py, AW_SQRT2[0] * o[j].pz, d);
-    }
-    if (TAN && ((k + 1) & mask) == 0) {
-#pragma unroll
-      for (int j = 0; j < OPL; ++j) renorm_node(o[j]);
-    }
-  };
-  int64_t k = k0;
-  if (UNR == 2) {
-#pragma nounroll
-    for (; k + 1 < k1; k += 2) {
-      one_step(k);
-      one_step(k + 1);
-    }
-  }
-#pragma nounroll
-  for (; k < k1; ++k) one_step(k);
-
+// After the step loop: the resumable carry of an intermediate launch (or a
+// time window), or the outputs of the final one.
+template <bool TAN, int OPL, bool WINV>
+__device__ __forceinline__ void finish_orbits(const FwdDesc &d, Orbit (&o)[OPL], const int64_t (&n)[OPL],
+                                              const bool (&act)[OPL], const bool (&left)[OPL],
+                                              const double (&xs)[OPL], const double (&ys)[OPL],
+                                              const double (&zs)[OPL], int64_t k0, int64_t k1) {
   if (k1 < d.T || WINV) {
     // Intermediate launch (or a time window): store the resumable carry.
 #pragma unroll
@@ -297,13 +212,15 @@ __device__ __forceinline__ void run_orbits(const FwdDesc &d, int64_t first, cons
       }
       double *c = d.carry;
       const int64_t N = d.N, m = n[j];
-      double s0[6];
-      gen_ic(d, m, s0);
+      if (k0 == 0) {  // what the steps do not change
+        double s0[6];
+        gen_ic(d, m, s0);
+        c[12 * N + m] = s0[0]; c[13 * N + m] = s0[1]; c[14 * N + m] = s0[2];
+      }
       c[0 * N + m] = o[j].x; c[1 * N + m] = o[j].y; c[2 * N + m] = o[j].z;
       c[3 * N + m] = o[j].px; c[4 * N + m] = o[j].py; c[5 * N + m] = o[j].pz;
       c[6 * N + m] = o[j].dx; c[7 * N + m] = o[j].dy; c[8 * N + m] = o[j].dz;
       c[9 * N + m] = o[j].dpx; c[10 * N + m] = o[j].dpy; c[11 * N + m] = o[j].dpz;
-      c[12 * N + m] = s0[0]; c[13 * N + m] = s0[1]; c[14 * N + m] = s0[2];
       c[15 * N + m] = o[j].p0x; c[16 * N + m] = o[j].p0y; c[17 * N + m] = o[j].p0z;
       c[18 * N + m] = o[j].jsum;
       c[19 * N + m] = (double)o[j].kexp;
@@ -399,19 +316,144 @@ __device__ __forceinline__ void run_orbits(const FwdDesc &d, int64_t first, cons
   }
 }
 
-// Blocks of up to 512 lanes: with the 64 KB table two blocks share a CU, and
-// at four waves per SIMD it takes blocks of 512 to fill it.  The one-orbit
-// tangent kernels of the sixth-order maps take 129 VGPRs, one block per CU:
-// two waves per SIMD already saturate the VALU issue, and holding them to 128
-// would cost the single-wave schedule its parallelism (a sixth longer on
-// small ensembles).  The window-test and time-window variants hold about twice the
-// registers and keep 256.
+// ---------------------------------------------------------------------------
+// Run one wave's tile of 64 OPL orbits, (tile OPL + j) 64 + lane for j < OPL,
+// over global steps [k_begin, k_end).  FILT: test the window after every step.
+// `tab` is the block's LDS copy of the sine/cosine table (filled by the caller).
+// ---------------------------------------------------------------------------
 template <int FORM, bool TAN, int OPL, int UNR, bool FILT = false, bool WINV = false>
-__global__ __launch_bounds__((FILT || WINV) ? 256 : 512) void k_fwd(FwdDesc d) {
+__device__ __forceinline__ void run_orbits(const FwdDesc &d, int64_t tile, const double2 *__restrict__ tab) {
+  int64_t n[OPL];
+  bool act[OPL];
+#pragma unroll
+  for (int j = 0; j < OPL; ++j) {
+    const int64_t m = (tile * OPL + j) * 64 + (int)__lane_id();
+    act[j] = m < d.N;
+    n[j] = act[j] ? m : d.N - 1;  // inactive slots repeat a valid orbit, never stored
+  }
+  if (tile * 64 * OPL >= d.N || !act[0]) return;
+
+  Orbit o[OPL];
+  bool left[OPL];
+#pragma unroll
+  for (int j = 0; j < OPL; ++j) {
+    left[j] = false;
+    if (d.k_begin == 0) {
+      double s[6];
+      gen_ic(d, n[j], s);
+      o[j].x = s[0]; o[j].y = s[1]; o[j].z = s[2];
+      o[j].px = s[3]; o[j].py = s[4]; o[j].pz = s[5];
+      o[j].p0x = s[3]; o[j].p0y = s[4]; o[j].p0z = s[5];
+      o[j].jsum = 0.0;
+      o[j].kexp = 0;
+      if (TAN) {
+        double w[6];
+        gen_w0(d.seed_tan, n[j], w);
+        o[j].dx = w[0]; o[j].dy = w[1]; o[j].dz = w[2];
+        o[j].dpx = w[3]; o[j].dpy = w[4]; o[j].dpz = w[5];
+      } else {
+        o[j].dx = o[j].dy = o[j].dz = o[j].dpx = o[j].dpy = o[j].dpz = 0.0;
+      }
+      to_node(o[j]);
+      if (FILT) left[j] = !in_window(o[j].px, o[j].py, o[j].pz, d);
+    } else {
+      // The carry holds the scaled rotated state as the loop left it.
+      const double *c = d.carry;
+      const int64_t N = d.N, m = n[j];
+      const int flags = (int)c[21 * N + m];
+      o[j].x = c[0 * N + m]; o[j].y = c[1 * N + m]; o[j].z = c[2 * N + m];
+      o[j].px = c[3 * N + m]; o[j].py = c[4 * N + m]; o[j].pz = c[5 * N + m];
+      o[j].dx = c[6 * N + m]; o[j].dy = c[7 * N + m]; o[j].dz = c[8 * N + m];
+      o[j].dpx = c[9 * N + m]; o[j].dpy = c[10 * N + m]; o[j].dpz = c[11 * N + m];
+      o[j].p0x = c[15 * N + m]; o[j].p0y = c[16 * N + m]; o[j].p0z = c[17 * N + m];
+      o[j].jsum = c[18 * N + m];
+      o[j].kexp = (int)c[19 * N + m];
+      if (FILT) left[j] = (flags & CARRY_LEFT) != 0;
+      if (!(flags & CARRY_NODES)) carry_to_nodes(o[j]);
+    }
+  }
+
+  // Positions at the start of this launch (time-window velocity; scaled frame).
+  double xs[OPL], ys[OPL], zs[OPL];
+  if (WINV) {
+#pragma unroll
+    for (int j = 0; j < OPL; ++j) {
+      xs[j] = o[j].x;
+      ys[j] = o[j].y;
+      zs[j] = o[j].z;
+    }
+  }
+
+  // Hot loop.  The trip count and the renormalisation test are uniform.
+  // UNR = 2 runs steps in pairs plus a one-step tail, written out: the table
+  // offset is inline assembly, which the compiler treats as convergent and
+  // will not unroll with a remainder.
+  const int64_t k0 = d.k_begin, k1 = d.k_end;
+  const int64_t mask = d.renorm_mask;
+  // Stage weights.  In the plain tangent kernel they move into VGPRs (an empty
+  // asm the compiler must treat as producing per-lane values): left in SGPRs,
+  // which the epilogue's descriptor fields hold across the loop, they are
+  // spilled and read back every step.  A block of 512 leaves 256 VGPRs a lane.
+  // The unrolled, two-orbit and window variants would lose occupancy and keep
+  // them in SGPRs.
+  constexpr bool kVregW = TAN && OPL == 1 && UNR == 1 && !FILT && !WINV;
+  StepWeights sw = d.w;
+  if (kVregW) {
+#pragma unroll
+    for (int q = 0; q < MAX_UNIQUE; ++q)
+      asm volatile("" : "+v"(sw.drift[q]), "+v"(sw.dnode[q]), "+v"(sw.dnodez[q]), "+v"(sw.ka[q]), "+v"(sw.kb[q]));
+  }
+  auto one_step = [&](int64_t k) {
+    map_step<FORM, TAN, OPL>(o, sw, tab);
+#pragma unroll
+    for (int j = 0; j < OPL; ++j) accum_j_node(o[j]);
+    if (FILT) {
+#pragma unroll
+      for (int j = 0; j < OPL; ++j) left[j] = left[j] || !in_window(o[j].px, o[j].py, o[j].pz, d);
+    }
+    if (TAN && ((k + 1) & mask) == 0) {
+#pragma unroll
+      for (int j = 0; j < OPL; ++j) renorm_node(o[j]);
+    }
+  };
+  int64_t k = k0;
+  if (UNR == 2) {
+#pragma nounroll
+    for (; k + 1 < k1; k += 2) {
+      one_step(k);
+      one_step(k + 1);
+    }
+  }
+#pragma nounroll
+  for (; k < k1; ++k) one_step(k);
+
+  finish_orbits<TAN, OPL, WINV>(reread(d), o, n, act, left, xs, ys, zs, k0, k1);
+}
+
+// A wave runs one tile of 64 OPL orbits; a block's waves share only the 64 KB
+// table.  The first full_blocks blocks, whole rounds of what the chip holds at
+// once, run nw consecutive tiles each.  The tiles of the last, partial round
+// are dealt one to a block in turn over as many blocks as there are CUs (or
+// slots), so that they spread over the CUs' SIMDs instead of filling a few CUs
+// while the others idle.
+__device__ __forceinline__ int64_t tile_of_wave(int64_t full_blocks) {
+  const int64_t nw = blockDim.x >> 6, b = blockIdx.x;
+  const int64_t wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  return b < full_blocks ? b * nw + wave : full_blocks * nw + wave * (gridDim.x - full_blocks) + (b - full_blocks);
+}
+
+// Without the tangent two blocks of 512 share a CU at up to 128 VGPRs, four
+// waves per SIMD; with it, or with two orbits per lane, a wave may take 256, one
+// block and two waves per SIMD, which issue 97% of the slots.  300007 orbits in
+// chunks of 100 steps took 2.05 ms with the last round in whole blocks and take
+// 1.79 now, 1e6 orbits x 400 steps 7.45 and 7.21 ms.
+constexpr bool two_blocks(bool tan, int opl) { return !tan && opl == 1; }
+
+template <int FORM, bool TAN, int OPL, int UNR, bool FILT = false, bool WINV = false>
+__global__ __launch_bounds__(512, two_blocks(TAN, OPL) ? 4 : 2) void k_fwd(FwdDesc, int64_t full_blocks) {
   __shared__ double2 s_tab[AW_TAB_N];
   load_sincos_table(s_tab);
-  const int64_t first = (int64_t)blockIdx.x * blockDim.x * OPL;
-  run_orbits<FORM, TAN, OPL, UNR, FILT, WINV>(d, first, s_tab);
+  run_orbits<FORM, TAN, OPL, UNR, FILT, WINV>(launched_desc(), tile_of_wave(full_blocks), s_tab);
 }
 
 // ---------------------------------------------------------------------------
@@ -447,7 +489,7 @@ struct HalfOrbit {
 __device__ __forceinline__ void pair_kick(HalfOrbit &h, double a, double b, const double2 *__restrict__ tab) {
   NodeSC sc[2];
   const double ang[2] = {h.w, h.z};
-  sincos_nodes<2>(ang, sc, tab);
+  sincos_nodes<2, true>(ang, sc, tab);
   const NodeSC W = sc[0], Z = sc[1];
   const double e1 = __builtin_fma(a, Z.c, a);
   const double e2 = b * Z.s;
@@ -479,10 +521,12 @@ __device__ __forceinline__ void pair_step(HalfOrbit &h, const StepWeights &d, co
 }
 
 template <int FORM, bool WINV>
-__global__ __launch_bounds__(256) void k_fwd_pair(FwdDesc d) {
+__global__ __launch_bounds__(512, 2) void k_fwd_pair(FwdDesc d, int64_t full_blocks) {
   __shared__ double2 s_tab[AW_TAB_N];
   load_sincos_table(s_tab);
-  const int64_t m0 = (int64_t)blockIdx.x * (blockDim.x >> 1) + (threadIdx.x >> 1);
+  const int64_t tile = tile_of_wave(full_blocks);   // of 32 orbits
+  if (tile * 32 >= d.N) return;
+  const int64_t m0 = tile * 32 + ((int)__lane_id() >> 1);
   const bool act = m0 < d.N;
   const int64_t m = act ? m0 : d.N - 1;   // past the end: repeat a valid orbit, never stored
   const bool odd = (threadIdx.x & 1u) != 0;
@@ -568,28 +612,46 @@ __global__ __launch_bounds__(256) void k_fwd_pair(FwdDesc d) {
   c[21 * N + m] = (double)CARRY_NODES;   // no window test here
 }
 
-// Persistent batched propagation: each workgroup takes (ensemble, tile)
-// items from a device counter until the list, sorted longest-first, is empty.
-// Two orbits per lane take about 266 VGPRs in the rotated frame; held to 256
-// (two waves per SIMD instead of one, the spills outside the step loop) the
-// batch runs a fifth faster.
+// Persistent batched propagation: every wave takes the next tile of 64 OPL
+// orbits from a device counter until the tiles of all ensembles, the longest
+// runs first, are done.  descs[e] are sorted by their step counts, and
+// ends[e] is the number of tiles of descs[0..e]; the tile's ensemble is found
+// by bisection.  Waves share nothing but the table: a tile of the longest run
+// keeps one wave and not the whole block from the next tile.
+// Two orbits per lane take about 266 VGPRs; held to 256 (two waves per SIMD
+// instead of one, the spills outside the step loop) the batch runs a fifth
+// faster.
 template <int FORM, bool TAN, int OPL>
-__global__ __launch_bounds__(256, OPL > 1 ? 2 : 1) void k_fwd_persist(const FwdDesc *__restrict__ descs,
-                                                     const WorkItem *__restrict__ items,
-                                                     int32_t n_items, uint32_t *head) {
+__global__ __launch_bounds__(512, (TAN || OPL > 1) ? 2 : 4) void k_fwd_persist(const FwdDesc *__restrict__ descs,
+                                                                               const int64_t *__restrict__ ends,
+                                                                               int32_t n_descs,
+                                                                               unsigned long long *head) {
   __shared__ double2 s_tab[AW_TAB_N];
-  __shared__ int32_t s_item;
   load_sincos_table(s_tab);
+  const int64_t n_tiles = ends[n_descs - 1];
   for (;;) {
-    if (threadIdx.x == 0) s_item = (int32_t)atomicAdd(head, 1u);
-    __syncthreads();
-    const int32_t it = __builtin_amdgcn_readfirstlane(s_item);
-    __syncthreads();
-    if (it >= n_items) break;
-    const int32_t e = __builtin_amdgcn_readfirstlane(items[it].ens);
-    const int64_t first = items[it].first;
-    run_orbits<FORM, TAN, OPL, 1>(descs[e], first, s_tab);
+    unsigned long long t0 = 0;
+    if (__lane_id() == 0) t0 = atomicAdd(head, 1ull);
+    const int64_t t = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(t0 >> 32)) << 32) |
+                                (uint32_t)__builtin_amdgcn_readfirstlane((int)t0));
+    if (t >= n_tiles) break;
+    int32_t lo = 0, hi = n_descs - 1;   // the first e with ends[e] > t
+    while (lo < hi) {
+      const int32_t mid = (lo + hi) >> 1;
+      if (ends[mid] > t) hi = mid;
+      else lo = mid + 1;
+    }
+    const int32_t e = __builtin_amdgcn_readfirstlane(lo);
+    run_orbits<FORM, TAN, OPL, 1>(descs[e], t - (e > 0 ? ends[e - 1] : 0), s_tab);
   }
+}
+
+// Clears what a batched launch counts in: the queue's head and, for IC-grid
+// images, every ensemble's counter of class-1 orbits.
+__global__ void k_batch_clear(const FwdDesc *__restrict__ descs, int32_t n_descs, unsigned long long *head) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i == 0) *head = 0ull;
+  if (i < n_descs && descs[i].epi == EPI_IC_GRID && descs[i].n_class) *descs[i].n_class = 0u;
 }
 
 __global__ void k_zero_u32(uint32_t *p, int32_t n) {
@@ -616,15 +678,39 @@ __global__ void k_gen_ic(FwdDesc d, double *ic, double *w0) {
 // ---------------------------------------------------------------------------
 // Host-side launchers.
 // ---------------------------------------------------------------------------
-int block_for(const Tuning &t, int64_t n) {
-  if (t.block) return t.block;
+int n_cus() {
   int dev = 0, ncu = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu <= 0)
     ncu = 256;
+  return ncu;
+}
+
+int block_for(const Tuning &t, int64_t n) {
+  if (t.block) return t.block;
+  const int ncu = n_cus();
   int b = 512;
   while (b > 64 && (int64_t)b * ncu > n) b >>= 1;
   return b;
+}
+
+// The grid for n_tiles tiles, one per wave, in blocks of `lanes` lanes: whole
+// rounds of the blocks the chip holds at once, then the rest (see
+// tile_of_wave) four to a CU, one per SIMD, while there are CUs, then one more
+// per SIMD, then over every slot.  A CU holds two blocks (the table), or one of
+// 512 lanes where a wave may take 256 VGPRs.  Four waves on a CU run 6-8%
+// faster than four waves on four CUs: the clock falls with the CUs in use.
+struct TileGrid {
+  int64_t full_blocks;
+  unsigned blocks;
+};
+
+static TileGrid tile_grid(int64_t n_tiles, int lanes, bool two_of_512) {
+  const int64_t ncu = n_cus(), nw = lanes >> 6, per = std::min<int64_t>(nw, 4);
+  const int64_t slots = lanes < 512 || two_of_512 ? 2 * ncu : ncu;
+  const int64_t full = n_tiles / (slots * nw) * slots, rest = n_tiles - full * nw;
+  const int64_t tail = rest <= ncu * nw ? std::min(ncu, (rest + per - 1) / per) : slots;
+  return {full, (unsigned)(full + tail)};
 }
 
 // Two lanes per orbit: tangent-free intermediate or time-window launches
@@ -633,41 +719,32 @@ int block_for(const Tuning &t, int64_t n) {
 static bool use_pair(const FwdDesc &d, const Tuning &t, bool tan) {
   if (tan || d.filter || !(d.window_v || d.k_end < d.T) || d.N <= 0) return false;
   if (t.lpo) return t.lpo == 2;
-  int dev = 0, ncu = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu <= 0)
-    ncu = 256;
-  return d.N < (int64_t)ncu * 4 * 64;
+  return d.N < (int64_t)n_cus() * 4 * 64;
 }
 
 template <int FORM, bool TAN>
 static hipError_t fwd_dispatch_opl(const FwdDesc &d, const Tuning &t, hipStream_t s) {
+  if (d.N <= 0) return hipSuccess;
   if (use_pair(d, t, TAN)) {
-    // 128 orbits (four waves) per block: with the 64 KB table two blocks share
-    // a CU, so a block must bring a wave for each of the CU's four SIMDs.
-    const dim3 grid((unsigned)((d.N + 127) / 128));
-    if (d.window_v) hipLaunchKernelGGL((k_fwd_pair<FORM, true>), grid, dim3(256), 0, s, d);
-    else hipLaunchKernelGGL((k_fwd_pair<FORM, false>), grid, dim3(256), 0, s, d);
+    const TileGrid g = tile_grid((d.N + 31) / 32, 512, false);
+    if (d.window_v) hipLaunchKernelGGL((k_fwd_pair<FORM, true>), dim3(g.blocks), dim3(512), 0, s, d, g.full_blocks);
+    else hipLaunchKernelGGL((k_fwd_pair<FORM, false>), dim3(g.blocks), dim3(512), 0, s, d, g.full_blocks);
     return hipGetLastError();
   }
-  const int lanes = block_for(t, (d.N + t.opl - 1) / t.opl);
-  const int64_t per_block = (int64_t)lanes * t.opl;
-  const int64_t blocks = (d.N + per_block - 1) / per_block;
-  if (blocks <= 0) return hipSuccess;
-  dim3 grid((unsigned)blocks), block((unsigned)lanes);
-  if (d.filter || d.window_v) {
-    // The window test and the time-window velocity run with one orbit per
-    // lane, no unrolling and at most 256 lanes per block.
-    const int wb = std::min(block_for(t, d.N), 256);
-    const dim3 wgrid((unsigned)((d.N + wb - 1) / wb));
-    block = dim3((unsigned)wb);
-    if (d.filter && d.window_v) hipLaunchKernelGGL((k_fwd<FORM, TAN, 1, 1, true, true>), wgrid, block, 0, s, d);
-    else if (d.filter) hipLaunchKernelGGL((k_fwd<FORM, TAN, 1, 1, true, false>), wgrid, block, 0, s, d);
-    else hipLaunchKernelGGL((k_fwd<FORM, TAN, 1, 1, false, true>), wgrid, block, 0, s, d);
-  } else if (t.opl == 1 && t.unroll == 1) hipLaunchKernelGGL((k_fwd<FORM, TAN, 1, 1>), grid, block, 0, s, d);
-  else if (t.opl == 1) hipLaunchKernelGGL((k_fwd<FORM, TAN, 1, 2>), grid, block, 0, s, d);
-  else if (t.unroll == 1) hipLaunchKernelGGL((k_fwd<FORM, TAN, 2, 1>), grid, block, 0, s, d);
-  else hipLaunchKernelGGL((k_fwd<FORM, TAN, 2, 2>), grid, block, 0, s, d);
+  // The window test and the time-window velocity run with one orbit per lane
+  // and no unrolling.
+  const int opl = d.filter || d.window_v ? 1 : t.opl;
+  const int lanes = block_512(t);
+  const TileGrid g = tile_grid((d.N + 64 * opl - 1) / (64 * opl), lanes, two_blocks(TAN, opl));
+  const dim3 grid(g.blocks), block((unsigned)lanes);
+  const int64_t fb = g.full_blocks;
+  if (d.filter && d.window_v) hipLaunchKernelGGL((k_fwd<FORM, TAN, 1, 1, true, true>), grid, block, 0, s, d, fb);
+  else if (d.filter) hipLaunchKernelGGL((k_fwd<FORM, TAN, 1, 1, true, false>), grid, block, 0, s, d, fb);
+  else if (d.window_v) hipLaunchKernelGGL((k_fwd<FORM, TAN, 1, 1, false, true>), grid, block, 0, s, d, fb);
+  else if (opl == 1 && t.unroll == 1) hipLaunchKernelGGL((k_fwd<FORM, TAN, 1, 1>), grid, block, 0, s, d, fb);
+  else if (opl == 1) hipLaunchKernelGGL((k_fwd<FORM, TAN, 1, 2>), grid, block, 0, s, d, fb);
+  else if (t.unroll == 1) hipLaunchKernelGGL((k_fwd<FORM, TAN, 2, 1>), grid, block, 0, s, d, fb);
+  else hipLaunchKernelGGL((k_fwd<FORM, TAN, 2, 2>), grid, block, 0, s, d, fb);
   return hipGetLastError();
 }
 
@@ -683,31 +760,26 @@ hipError_t launch_fwd(const FwdDesc &d, const Tuning &t, int form, bool tan, hip
 }
 
 template <int FORM, bool TAN>
-static hipError_t persist_dispatch(const FwdDesc *descs, const WorkItem *items, int32_t n_items,
-                                   uint32_t *head, const Tuning &t, int n_wg, hipStream_t s) {
-  hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, s, head, 1);
-  dim3 grid((unsigned)n_wg), block((unsigned)block_256(t));
-  if (t.opl == 1) hipLaunchKernelGGL((k_fwd_persist<FORM, TAN, 1>), grid, block, 0, s, descs, items, n_items, head);
-  else hipLaunchKernelGGL((k_fwd_persist<FORM, TAN, 2>), grid, block, 0, s, descs, items, n_items, head);
+static hipError_t persist_dispatch(const FwdDesc *descs, const int64_t *ends, int32_t n_descs,
+                                   unsigned long long *head, const Tuning &t, int n_wg, hipStream_t s) {
+  const dim3 grid((unsigned)n_wg), block((unsigned)block_512(t));
+  if (t.opl == 1) hipLaunchKernelGGL((k_fwd_persist<FORM, TAN, 1>), grid, block, 0, s, descs, ends, n_descs, head);
+  else hipLaunchKernelGGL((k_fwd_persist<FORM, TAN, 2>), grid, block, 0, s, descs, ends, n_descs, head);
   return hipGetLastError();
 }
 
-hipError_t launch_fwd_batched(const FwdDesc *descs_dev, const WorkItem *items_dev, int32_t n_items,
-                              uint32_t *head_dev, const Tuning &t, int form, bool tan, int n_wg,
-                              hipStream_t s) {
+hipError_t launch_fwd_batched(const FwdDesc *descs, const int64_t *ends, int32_t n_descs, unsigned long long *head,
+                              const Tuning &t, int form, bool tan, int n_wg, hipStream_t s) {
+  hipLaunchKernelGGL(k_batch_clear, dim3((unsigned)((n_descs + 255) / 256)), dim3(256), 0, s, descs, n_descs, head);
+  if (n_wg <= 0) return hipGetLastError();
+#define AW_PERSIST(F)                                                                      \
+  case F: return tan ? persist_dispatch<F, true>(descs, ends, n_descs, head, t, n_wg, s)   \
+                     : persist_dispatch<F, false>(descs, ends, n_descs, head, t, n_wg, s);
   switch (form) {
-  case 1: return tan ? persist_dispatch<1, true>(descs_dev, items_dev, n_items, head_dev, t, n_wg, s)
-                     : persist_dispatch<1, false>(descs_dev, items_dev, n_items, head_dev, t, n_wg, s);
-  case 2: return tan ? persist_dispatch<2, true>(descs_dev, items_dev, n_items, head_dev, t, n_wg, s)
-                     : persist_dispatch<2, false>(descs_dev, items_dev, n_items, head_dev, t, n_wg, s);
-  case 4: return tan ? persist_dispatch<4, true>(descs_dev, items_dev, n_items, head_dev, t, n_wg, s)
-                     : persist_dispatch<4, false>(descs_dev, items_dev, n_items, head_dev, t, n_wg, s);
-  case 6: return tan ? persist_dispatch<6, true>(descs_dev, items_dev, n_items, head_dev, t, n_wg, s)
-                     : persist_dispatch<6, false>(descs_dev, items_dev, n_items, head_dev, t, n_wg, s);
-  case 7: return tan ? persist_dispatch<7, true>(descs_dev, items_dev, n_items, head_dev, t, n_wg, s)
-                     : persist_dispatch<7, false>(descs_dev, items_dev, n_items, head_dev, t, n_wg, s);
+    AW_PERSIST(1) AW_PERSIST(2) AW_PERSIST(4) AW_PERSIST(6) AW_PERSIST(7)
   default: return hipErrorInvalidValue;
   }
+#undef AW_PERSIST
 }
 
 int persistent_blocks_per_cu(int form, bool tan, const Tuning &t) {
@@ -715,10 +787,10 @@ int persistent_blocks_per_cu(int form, bool tan, const Tuning &t) {
   hipError_t e = hipErrorInvalidValue;
 #define AW_OCC(F)                                                                                 \
   if (form == F) {                                                                                \
-    if (tan) e = t.opl == 1 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_fwd_persist<F, true, 1>, block_256(t), 0) \
-                            : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_fwd_persist<F, true, 2>, block_256(t), 0); \
-    else e = t.opl == 1 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_fwd_persist<F, false, 1>, block_256(t), 0) \
-                        : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_fwd_persist<F, false, 2>, block_256(t), 0); \
+    if (tan) e = t.opl == 1 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_fwd_persist<F, true, 1>, block_512(t), 0) \
+                            : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_fwd_persist<F, true, 2>, block_512(t), 0); \
+    else e = t.opl == 1 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_fwd_persist<F, false, 1>, block_512(t), 0) \
+                        : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_fwd_persist<F, false, 2>, block_512(t), 0); \
   }
   AW_OCC(1) AW_OCC(2) AW_OCC(4) AW_OCC(6) AW_OCC(7)
 #undef AW_OCC

@@ -18,26 +18,25 @@ struct Tuning {
   int lpo = 0;    // lanes per orbit of tangent-free intermediate launches: 0 auto, 1 or 2
 };
 
-// Lanes per block for a launch over n orbits (or lanes).  A block set in the
+int n_cus();  // compute units of the current device
+
+// Lanes per block of the adjoint kernels for n orbits.  A block set in the
 // tuning is used as is.  Automatic: 512 when every CU gets at least one block
 // of 512 (a block holds the 64 KB sine/cosine table, so two blocks share a CU,
-// and it takes two of 512 lanes to fill it at four waves per SIMD; a kernel
-// above 128 VGPRs fits one, whose two waves per SIMD still saturate the
-// issue); below
-// that the largest of 256 and 128 that still gives every CU a block, else 64,
-// so that small ensembles spread over as much of the chip as they can.  No
+// and it takes two of 512 lanes to fill it at four waves per SIMD); below that
+// the largest of 256 and 128 that still gives every CU a block, else 64, so
+// that small ensembles spread over as much of the chip as they can.  No
 // result depends on the block.
 int block_for(const Tuning &t, int64_t n);
 
-// Kernels bounded at 256 lanes per block (the window-test and time-window
-// propagation and the batched persistent kernel, whose register counts leave
-// room for no more) run a larger or automatic block as 256.
-inline int block_256(const Tuning &t) { return (t.block == 0 || t.block > 256) ? 256 : t.block; }
+inline int block_512(const Tuning &t) { return t.block ? t.block : 512; }
 
 // Propagation.
 hipError_t launch_fwd(const FwdDesc &d, const Tuning &t, int form, bool tan, hipStream_t s);
-hipError_t launch_fwd_batched(const FwdDesc *descs_dev, const WorkItem *items_dev, int32_t n_items,
-                              uint32_t *head_dev, const Tuning &t, int form, bool tan, int n_wg,
+// descs sorted by their step counts, longest first; ends[e]: tiles of 64 opl
+// orbits in descs[0..e].  n_wg = 0 clears the counters only.
+hipError_t launch_fwd_batched(const FwdDesc *descs_dev, const int64_t *ends_dev, int32_t n_descs,
+                              unsigned long long *head_dev, const Tuning &t, int form, bool tan, int n_wg,
                               hipStream_t s);
 int persistent_blocks_per_cu(int form, bool tan, const Tuning &t);
 hipError_t launch_gen_ic(const FwdDesc &d, double *ic, double *w0, hipStream_t s);
