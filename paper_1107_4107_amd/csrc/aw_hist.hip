@@ -15,6 +15,8 @@
 //   5. merge   : one workgroup per tile of several chunks adds their partial
 //                tiles in chunk order and writes the tile out -- no global
 //                atomics anywhere.
+// Few items go another way, in one launch instead of six: one workgroup per
+// tile reads every item's bin and keeps its own (k_hist_small).
 // Counts are exact and independent of scheduling; the order of the float
 // additions inside a chunk is not, so sums can differ in the last bits.
 #include <hip/hip_runtime.h>
@@ -462,6 +464,56 @@ __global__ __launch_bounds__(TILE_BINS) void k_tile_merge(const uint32_t *__rest
   write_bin(g, t, k, cc, sk, mode, norm, accumulate, counts_out, f_out);
 }
 
+// Few items: one workgroup per tile reads all N bins (N / 1024 coalesced loads
+// per lane, from the L2 after the first reader) and accumulates those of its
+// own tile in LDS.  Bound by launch and load latency while the items spread
+// over many tiles (32000 items and 512 x 512 bins with the keys 18.5 us, 34.4
+// sorted), by the LDS adds of one CU where a tile holds most of them (65536
+// items in 64 x 64 bins 27.6 us, 38.2 sorted; all within 1/50 of either
+// width 42.6, 67.5).
+__global__ __launch_bounds__(ACC_BLOCK) void k_hist_small(int64_t N, const uint32_t *__restrict__ bins,
+                                                           const double *__restrict__ vals, TileGeom g, int32_t mode,
+                                                           double norm, int32_t accumulate,
+                                                           uint32_t *__restrict__ counts_out,
+                                                           double *__restrict__ f_out,
+                                                           uint64_t *__restrict__ dropped_out) {
+  __shared__ uint32_t c[TILE_BINS];
+  __shared__ double s[TILE_BINS];
+  __shared__ uint32_t drop;
+  const int t = blockIdx.x, tid = threadIdx.x;
+  c[tid] = 0u;
+  s[tid] = 0.0;
+  if (tid == 0) drop = 0u;
+  __syncthreads();
+  const uint32_t W = (uint32_t)g.W, tx = (uint32_t)(t % g.tiles_x), j0 = (uint32_t)(t / g.tiles_x) * TILE_H;
+  const uint32_t first = j0 * W, span = ((uint32_t)g.H - j0 < TILE_H ? (uint32_t)g.H - j0 : TILE_H) * W;
+  const bool count_drops = t == 0 && dropped_out != nullptr;
+  uint32_t my_drop = 0;
+  auto add = [&](int64_t n, uint32_t bin) {
+    if (count_drops && bin == BIN_DROP) ++my_drop;
+    const uint32_t d = bin - first;   // BIN_DROP stays above every span
+    if (d >= span) return;
+    const uint32_t j = d / W, i = d - j * W;
+    if (i / TILE_W != tx) return;
+    const uint32_t k = j * TILE_W + i % TILE_W;
+    atomicAdd(&c[k], 1u);
+    if (vals) atomicAdd(&s[k], vals[n]);
+  };
+  int64_t n = tid;
+  for (; n + 7 * ACC_BLOCK < N; n += 8 * ACC_BLOCK) {  // eight loads in flight per lane
+    uint32_t b[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) b[k] = bins[n + k * ACC_BLOCK];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) add(n + k * ACC_BLOCK, b[k]);
+  }
+  for (; n < N; n += ACC_BLOCK) add(n, bins[n]);
+  if (my_drop) atomicAdd(&drop, my_drop);
+  __syncthreads();
+  write_bin(g, t, tid, c[tid], s[tid], mode, norm, accumulate, counts_out, f_out);
+  if (count_drops && tid == 0) *dropped_out = drop;
+}
+
 hipError_t launch_hist_bins(int64_t N, const double *a, const double *b, double lo0, double hi0, double lo1,
                             double hi1, int W, int H, int closed, uint32_t *bins, hipStream_t s) {
   if (N <= 0) return hipSuccess;
@@ -494,24 +546,22 @@ hipError_t launch_hist_reduce(int64_t N, const uint32_t *bins, const double *val
                               const HistScratch &w, int mode, double norm, uint32_t *counts_out,
                               double *f_out, uint64_t *dropped_out, hipStream_t s, int accumulate) {
   TileGeom g{p.W, p.H, p.tiles_x, p.n_tiles};
-  const unsigned tile_lds = (unsigned)(sizeof(uint32_t) * ((size_t)p.n_tiles + 1));  // <= 32 KB + 4 B
-  if (N > 0) {
-    hipLaunchKernelGGL(k_tile_count, dim3((unsigned)p.G), dim3(HIST_BLOCK), tile_lds, s, N, bins, g, p.G,
-                       w.block_counts, w.block_dropped);
-  } else {
-    hipError_t e = launch_zero_u32(w.block_counts, p.n_tiles * p.G, s);
-    if (e != hipSuccess) return e;
-    e = launch_zero_u32(w.block_dropped, p.G, s);
-    if (e != hipSuccess) return e;
+  if (hist_small(N, p.n_tiles)) {
+    hipLaunchKernelGGL(k_hist_small, dim3((unsigned)p.n_tiles), dim3(ACC_BLOCK), 0, s, N, bins, vals, g, mode, norm,
+                       accumulate, counts_out, f_out, dropped_out);
+    return hipGetLastError();
   }
+  const unsigned tile_lds = (unsigned)(sizeof(uint32_t) * ((size_t)p.n_tiles + 1));  // <= 32 KB + 4 B
+  hipLaunchKernelGGL(k_tile_count, dim3((unsigned)p.G), dim3(HIST_BLOCK), tile_lds, s, N, bins, g, p.G,
+                     w.block_counts, w.block_dropped);
   hipLaunchKernelGGL(k_tile_scan_rows, dim3((unsigned)p.n_tiles), dim3(SCAN_BLOCK), 0, s, w.block_counts, p.G,
                      w.tile_total);
   hipLaunchKernelGGL(k_tile_scan_tiles, dim3(1), dim3(1024), 0, s, w.tile_total, p.n_tiles, w.block_dropped, p.G,
                      (uint32_t)p.chunk, w.tile_start, w.chunk_first, w.part_first, w.chunk_tile, dropped_out);
-  if (N > 0 && vals && p.n_tiles <= STAGE_MAX_TILES)
+  if (vals && p.n_tiles <= STAGE_MAX_TILES)
     hipLaunchKernelGGL(k_tile_scatter_staged, dim3((unsigned)p.G), dim3(STAGE_BLOCK), 0, s, N, bins, vals, g, p.G,
                        w.block_counts, w.tile_start, w.sorted_local, vals ? w.sorted_val : nullptr);
-  else if (N > 0)
+  else
     hipLaunchKernelGGL(k_tile_scatter, dim3((unsigned)p.G), dim3(HIST_BLOCK), tile_lds, s, N, bins, vals, g, p.G,
                        w.block_counts, w.tile_start, w.sorted_local, vals ? w.sorted_val : nullptr);
   double *psums = vals ? w.part_sums : nullptr;

@@ -19,6 +19,17 @@ constexpr int STAGE_MAX_TILES = 1024;       // images up to this many tiles scat
 constexpr int STAGE_ITEMS = 4096;           // items per LDS staging round
 constexpr int STAGE_BLOCK = 1024;
 
+// Whether N items into T tiles are binned by one workgroup per tile that reads
+// them all (k_hist_small) instead of being sorted by tile first (six launches).
+// Measured with the binning of the keys and values: 32000 items into 512 x 512
+// bins 18.5 us against 34.4 sorted, 65536 into 512 x 512 19.4 / 34.7, into
+// 1024 x 512 26.9 / 36.0, into 64 x 64 27.6 / 38.2; past the line 98304 into
+// 1024 x 512 36.9 / 36.0, into 64 x 64 39.6 / 37.4, 65536 into 900 x 900 (841
+// tiles) 41.4 / 39.5.
+constexpr int64_t HIST_SMALL_N = 65536;
+constexpr int64_t HIST_SMALL_READS = HIST_SMALL_N * 512;
+constexpr bool hist_small(int64_t N, int64_t T) { return N <= HIST_SMALL_N && N * T <= HIST_SMALL_READS; }
+
 // The accumulation splits every tile's sorted range into chunks of at most
 // acc_chunk(N, T) items, one workgroup each; a tile of several chunks leaves a
 // partial tile per chunk, which a second kernel adds up in chunk order.  The
