@@ -686,7 +686,7 @@ hipError_t reduce_image(const ImageCall &c, char *base, int e, const aw_image_sp
   const HistScratch w = hist_scratch_at(base, c.lay, c.vals, p.n_tiles);
   const int mode = c.vals ? 1 : 2;
   const double norm = 1.0 / ((double)d.N * ((d.khi0 - d.klo0) / spec->W) * ((d.khi1 - d.klo1) / spec->H));
-  return launch_hist_reduce(d.N, d.bins, d.vals, p, w, mode, norm, counts ? counts[e] : nullptr, image[e], nullptr,
+  return launch_hist_reduce(d.N, nullptr, d.bins, d.vals, p, w, mode, norm, counts ? counts[e] : nullptr, image[e], nullptr,
                             s);
 }
 
@@ -950,8 +950,8 @@ aw_status aw_window_density(const aw_ensemble *ens, const double *ic_dev, double
     d.k_begin = k_begin + k * window_steps;
     d.k_end = d.k_begin + window_steps;
     if ((st = launch_one(d, t, ens->map_form, tangent_on(*ens), s)) != AW_OK) return st;
-    if ((e = launch_hist_reduce(d.N, d.bins, nullptr, p, w, 2, 0.0, counts_accum_dev, nullptr, nullptr, s, 1)) !=
-        hipSuccess)
+    if ((e = launch_hist_reduce(d.N, nullptr, d.bins, nullptr, p, w, 2, 0.0, counts_accum_dev, nullptr, nullptr, s,
+                                1)) != hipSuccess)
       return hip_fail(e, "window histogram");
   }
   return AW_OK;
@@ -981,9 +981,9 @@ static aw_status hist2d_run(char *base, const Layout &l, const HistPlan &p, int6
   const HistScratch w = hist_scratch_at(base, l, v_dev != nullptr, p.n_tiles);
   uint32_t *bins = (uint32_t *)(base + l.bins);
   hipError_t e;
-  if ((e = launch_hist_bins(N, a_dev, b_dev, lo0, hi0, lo1, hi1, W, H, closed_upper, bins, s)) != hipSuccess)
-    return hip_fail(e, "histogram bins");
-  if ((e = launch_hist_reduce(N, bins, v_dev, p, w, 0, 1.0, counts_dev, sums_dev, dropped_dev, s)) != hipSuccess)
+  const HistKeys keys{a_dev, b_dev, lo0, hi0, lo1, hi1, closed_upper};
+  if ((e = launch_hist_reduce(N, &keys, bins, v_dev, p, w, 0, 1.0, counts_dev, sums_dev, dropped_dev, s)) !=
+      hipSuccess)
     return hip_fail(e, "histogram reduction");
   return AW_OK;
 }

@@ -13,21 +13,22 @@ constexpr int TILE_BINS = TILE_W * TILE_H;
 constexpr int HIST_BLOCK = 256;
 constexpr int HIST_ITEMS_PER_BLOCK = 8192;  // items per block in count/scatter
 constexpr int ACC_BLOCK = 1024;             // lanes per tile in the accumulation
+constexpr int ACC_WINDOW = 16384;           // items whose runs are found at a time
 constexpr int SCAN_BLOCK = 256;             // lanes per tile row in the scan
 constexpr int MAX_TILES = 8192;
-constexpr int STAGE_MAX_TILES = 1024;       // images up to this many tiles scatter through LDS
-constexpr int STAGE_ITEMS = 4096;           // items per LDS staging round
-constexpr int STAGE_BLOCK = 1024;
+constexpr int SEG_MAX_TILES = 1024;         // images up to this many tiles are sorted in segments
+constexpr int SEG_ITEMS = 4096;             // items per segment
+constexpr int SEG_BLOCK = 512;              // lanes per segment
 
 // Whether N items into T tiles are binned by one workgroup per tile that reads
-// them all (k_hist_small) instead of being sorted by tile first (six launches).
-// Measured with the binning of the keys and values: 32000 items into 512 x 512
-// bins 18.5 us against 34.4 sorted, 65536 into 512 x 512 19.4 / 34.7, into
-// 1024 x 512 26.9 / 36.0, into 64 x 64 27.6 / 38.2; past the line 98304 into
-// 1024 x 512 36.9 / 36.0, into 64 x 64 39.6 / 37.4, 65536 into 900 x 900 (841
-// tiles) 41.4 / 39.5.
+// them all (k_hist_small) instead of being sorted by tile first.  Measured with
+// the binning of the keys and values, one workgroup per tile against segments:
+// 32000 items into 900 x 900 bins (841 tiles) 26 us / 33, 65536 into 512 x 512
+// 19.4 / 21, into 1024 x 512 (512 tiles) 27 / 25, into 64 x 64 27.6 / 27 (18.2 /
+// 21 without values), crowded 43 / 57; past the line 98304 into 64 x 64 39.6 /
+// 27, into 512 x 512 25.9 / 21, 65536 into 900 x 900 41 / 33.
 constexpr int64_t HIST_SMALL_N = 65536;
-constexpr int64_t HIST_SMALL_READS = HIST_SMALL_N * 512;
+constexpr int64_t HIST_SMALL_READS = HIST_SMALL_N * 448;
 constexpr bool hist_small(int64_t N, int64_t T) { return N <= HIST_SMALL_N && N * T <= HIST_SMALL_READS; }
 
 // The accumulation splits every tile's sorted range into chunks of at most

@@ -50,6 +50,11 @@ struct HistPlan {
   int64_t chunk = 0;       // items per accumulation chunk
   int64_t max_chunks = 0;  // accumulation workgroups launched: n_tiles + ceil(N / chunk)
 };
+struct HistKeys {
+  const double *a = nullptr, *b = nullptr;
+  double lo0 = 0, hi0 = 0, lo1 = 0, hi1 = 0;
+  int32_t closed = 0;  // the upper edges belong to the last bins
+};
 struct HistScratch {
   uint32_t *block_counts = nullptr;
   uint32_t *block_dropped = nullptr;
@@ -64,11 +69,10 @@ struct HistScratch {
   double *sorted_val = nullptr;
 };
 HistPlan hist_plan(int64_t N, int W, int H);
-hipError_t launch_hist_bins(int64_t N, const double *a, const double *b, double lo0, double hi0, double lo1,
-                            double hi1, int W, int H, int closed, uint32_t *bins, hipStream_t s);
 hipError_t launch_vdir_keys(int64_t N, const double *V, double *phi, double *mu, hipStream_t s);
-// accumulate != 0: counts are added to counts_out instead of written.
-hipError_t launch_hist_reduce(int64_t N, const uint32_t *bins, const double *vals, const HistPlan &p,
+// Items by their bins, or by a caller's keys if keys != nullptr: bins is then
+// scratch.  accumulate != 0: counts are added to counts_out instead of written.
+hipError_t launch_hist_reduce(int64_t N, const HistKeys *keys, uint32_t *bins, const double *vals, const HistPlan &p,
                               const HistScratch &w, int mode, double norm, uint32_t *counts_out,
                               double *f_out, uint64_t *dropped_out, hipStream_t s, int accumulate = 0);
 
