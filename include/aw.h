@@ -162,12 +162,11 @@ typedef struct {
  * {1, 2}; unroll in {1, 2}; the window-test and time-window propagation run
  * one orbit per lane, not unrolled.
  * renorm_every in {1, 2, 4, 8, 16}.  persistent_wgs: workgroups of the batched
- * persistent launch (0 = auto).  lanes_per_orbit in {0, 1, 2}: tangent-free
- * launches that end before n_steps (aw_map_ensemble_steps) or bin time windows
- * (aw_window_density), without AW_F_WINDOW, can run one orbit on two lanes (u
- * and p_u on one, v and p_v on the other, in the rotated frame); 0 does so
- * when one lane per orbit would leave SIMDs without a wave (fewer than
- * 64 x 4 x CUs orbits).  Results are bitwise the same either way. */
+ * persistent launch (0 = auto).  lanes_per_orbit in {0, 1, 2}: without
+ * AW_F_WINDOW and outside the batched launch an orbit can run on two lanes (u,
+ * p_u and their tangent on one, v's on the other, in the rotated frame); 0 does
+ * so while every wave then has a SIMD of its own (at most 32 x 4 x CUs orbits).
+ * Results are bitwise the same either way. */
 typedef struct {
   int32_t block;
   int32_t orbits_per_lane;

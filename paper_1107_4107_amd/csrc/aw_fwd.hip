@@ -316,6 +316,45 @@ __device__ __forceinline__ void finish_orbits(const FwdDesc &d, Orbit (&o)[OPL],
   }
 }
 
+// Orbit m at step k_begin in the scaled frame: its initial state, or the
+// carry as the loop left it.
+template <bool TAN, bool FILT>
+__device__ __forceinline__ void start_orbit(const FwdDesc &d, int64_t m, Orbit &o, bool &left) {
+  left = false;
+  if (d.k_begin == 0) {
+    double s[6];
+    gen_ic(d, m, s);
+    o.x = s[0]; o.y = s[1]; o.z = s[2];
+    o.px = s[3]; o.py = s[4]; o.pz = s[5];
+    o.p0x = s[3]; o.p0y = s[4]; o.p0z = s[5];
+    o.jsum = 0.0;
+    o.kexp = 0;
+    if (TAN) {
+      double w[6];
+      gen_w0(d.seed_tan, m, w);
+      o.dx = w[0]; o.dy = w[1]; o.dz = w[2];
+      o.dpx = w[3]; o.dpy = w[4]; o.dpz = w[5];
+    } else {
+      o.dx = o.dy = o.dz = o.dpx = o.dpy = o.dpz = 0.0;
+    }
+    to_node(o);
+    if (FILT) left = !in_window(o.px, o.py, o.pz, d);
+  } else {
+    const double *c = d.carry;
+    const int64_t N = d.N;
+    const int flags = (int)c[21 * N + m];
+    o.x = c[0 * N + m]; o.y = c[1 * N + m]; o.z = c[2 * N + m];
+    o.px = c[3 * N + m]; o.py = c[4 * N + m]; o.pz = c[5 * N + m];
+    o.dx = c[6 * N + m]; o.dy = c[7 * N + m]; o.dz = c[8 * N + m];
+    o.dpx = c[9 * N + m]; o.dpy = c[10 * N + m]; o.dpz = c[11 * N + m];
+    o.p0x = c[15 * N + m]; o.p0y = c[16 * N + m]; o.p0z = c[17 * N + m];
+    o.jsum = c[18 * N + m];
+    o.kexp = (int)c[19 * N + m];
+    if (FILT) left = (flags & CARRY_LEFT) != 0;
+    if (!(flags & CARRY_NODES)) carry_to_nodes(o);
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Run one wave's tile of 64 OPL orbits, (tile OPL + j) 64 + lane for j < OPL,
 // over global steps [k_begin, k_end).  FILT: test the window after every step.
@@ -337,40 +376,7 @@ __device__ __forceinline__ void run_orbits(const FwdDesc &d, int64_t tile, const
   bool left[OPL];
 #pragma unroll
   for (int j = 0; j < OPL; ++j) {
-    left[j] = false;
-    if (d.k_begin == 0) {
-      double s[6];
-      gen_ic(d, n[j], s);
-      o[j].x = s[0]; o[j].y = s[1]; o[j].z = s[2];
-      o[j].px = s[3]; o[j].py = s[4]; o[j].pz = s[5];
-      o[j].p0x = s[3]; o[j].p0y = s[4]; o[j].p0z = s[5];
-      o[j].jsum = 0.0;
-      o[j].kexp = 0;
-      if (TAN) {
-        double w[6];
-        gen_w0(d.seed_tan, n[j], w);
-        o[j].dx = w[0]; o[j].dy = w[1]; o[j].dz = w[2];
-        o[j].dpx = w[3]; o[j].dpy = w[4]; o[j].dpz = w[5];
-      } else {
-        o[j].dx = o[j].dy = o[j].dz = o[j].dpx = o[j].dpy = o[j].dpz = 0.0;
-      }
-      to_node(o[j]);
-      if (FILT) left[j] = !in_window(o[j].px, o[j].py, o[j].pz, d);
-    } else {
-      // The carry holds the scaled rotated state as the loop left it.
-      const double *c = d.carry;
-      const int64_t N = d.N, m = n[j];
-      const int flags = (int)c[21 * N + m];
-      o[j].x = c[0 * N + m]; o[j].y = c[1 * N + m]; o[j].z = c[2 * N + m];
-      o[j].px = c[3 * N + m]; o[j].py = c[4 * N + m]; o[j].pz = c[5 * N + m];
-      o[j].dx = c[6 * N + m]; o[j].dy = c[7 * N + m]; o[j].dz = c[8 * N + m];
-      o[j].dpx = c[9 * N + m]; o[j].dpy = c[10 * N + m]; o[j].dpz = c[11 * N + m];
-      o[j].p0x = c[15 * N + m]; o[j].p0y = c[16 * N + m]; o[j].p0z = c[17 * N + m];
-      o[j].jsum = c[18 * N + m];
-      o[j].kexp = (int)c[19 * N + m];
-      if (FILT) left[j] = (flags & CARRY_LEFT) != 0;
-      if (!(flags & CARRY_NODES)) carry_to_nodes(o[j]);
-    }
+    start_orbit<TAN, FILT>(d, n[j], o[j], left[j]);
   }
 
   // Positions at the start of this launch (time-window velocity; scaled frame).
@@ -457,35 +463,45 @@ __global__ __launch_bounds__(512, two_blocks(TAN, OPL) ? 4 : 2) void k_fwd(FwdDe
 }
 
 // ---------------------------------------------------------------------------
-// Two lanes per orbit, for tangent-free ensembles too small to give every
-// SIMD a wave at one lane per orbit (Fig. 4's 3.2e4 orbits make 500 waves for
-// 1024 SIMDs).  In the rotated frame the force does not couple u and v, so
-// lane 2m of a pair holds u and p_u and lane 2m + 1 holds v and p_v, and both
-// hold z and p_z.  A kick takes one table sine and cosine of the lane's own
-// coordinate and the z factors, swaps the cosine with the partner lane
-// (cs = cos u + cos v is the same sum in both lanes: IEEE addition commutes),
-// and advances the lane's own momentum and p_z; a drift advances the lane's
-// coordinate and z.  Every value is formed and rounded as in run_orbits, so
-// the states, carries and window bins are bitwise those of one lane per
-// orbit.  Intermediate and time-window launches only: the final epilogue and
-// the window test run one lane per orbit.
+// Two lanes per orbit, for ensembles too small to give every SIMD a wave at one
+// lane per orbit (Fig. 4's 3.2e4 orbits make 500 waves for 1024 SIMDs).  In the
+// scaled frame neither the force nor its Jacobian couples u and v, so lane 2m of
+// a pair holds u, p_u and their tangent, lane 2m + 1 holds v's, and both hold z's.
+// A kick takes one table sine and cosine of the lane's own coordinate and the z
+// factors, swaps the cosine with the partner lane (cs = cos u + cos v is the same
+// sum in both lanes: IEEE addition commutes), and advances the lane's own momenta
+// and p_z; a drift advances the lane's coordinate and z.  The one sum that is
+// rounded differently by order, sin u du + sin v dv, is formed in the even lane
+// and handed to the odd one.  Every value is formed and rounded as in
+// run_orbits, so the states, carries, outputs and bins are bitwise those of one
+// lane per orbit.  The window test runs one lane per orbit.
+// A lone wave is bound by its own issue and by the chain of its kicks, ten
+// dependent operations and a table read each.  An S6 step is 454 VALU instructions
+// instead of 563 with the tangent, 307 instead of 415 without: 4096 orbits over
+// 200 steps take 197 us instead of 235, and 134 instead of 184.
 // ---------------------------------------------------------------------------
-// Lanes 2m and 2m + 1 exchange v (DPP quad_perm [1, 0, 3, 2] on both halves).
-// Every lane of the wave takes part: lanes past the ensemble's end repeat a
-// valid orbit.
-__device__ __forceinline__ double swap_pair(double v) {
-  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), 0xB1, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0xB1, 0xF, 0xF, false);
+// Lanes 2m and 2m + 1 exchange v (DPP quad_perm [1, 0, 3, 2]), or both take lane
+// 2m's (quad_perm [0, 0, 2, 2]).  Every lane of the wave takes part: lanes past
+// the ensemble's end repeat a valid orbit.
+constexpr int DPP_SWAP = 0xB1, DPP_EVEN = 0xA0;
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_pair(double v) {
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, false);
   return __hiloint2double(hi, lo);
 }
 
 struct HalfOrbit {
-  double w, pw;    // own rotated coordinate (u or v, in nodes) and its momentum
-  double z, pz;    // 2 z in nodes, sqrt 2 p_z
+  double w, pw;          // own coordinate (u or v, in nodes) and its momentum
+  double z, pz;          // 2 z in nodes, sqrt 2 p_z
+  double dw, dpw, dz, dpz;  // their tangent
   double p0w, p0z;
-  double jsum;     // meaningful in the pair's even lane
+  double jsum;           // meaningful in the pair's even lane
+  int kexp;
 };
 
+template <bool TAN>
 __device__ __forceinline__ void pair_kick(HalfOrbit &h, double a, double b, const double2 *__restrict__ tab) {
   NodeSC sc[2];
   const double ang[2] = {h.w, h.z};
@@ -493,123 +509,126 @@ __device__ __forceinline__ void pair_kick(HalfOrbit &h, double a, double b, cons
   const NodeSC W = sc[0], Z = sc[1];
   const double e1 = __builtin_fma(a, Z.c, a);
   const double e2 = b * Z.s;
-  const double cs = W.c + swap_pair(W.c);
+  const double cs = W.c + dpp_pair<DPP_SWAP>(W.c);
+  if (TAN) {
+    const double f = e1 * h.dw, q = e2 * h.dz;
+    const double g = dpp_pair<DPP_EVEN>(__builtin_fma(W.s, h.dw, dpp_pair<DPP_SWAP>(W.s * h.dw)));
+    const double mz = cs * __builtin_fma(2.0, e1, -2.0 * a);
+    h.dpw = __builtin_fma(W.c, f, __builtin_fma(-W.s, q, h.dpw));
+    h.dpz = __builtin_fma(mz, h.dz, __builtin_fma(-e2, g, h.dpz));
+  }
   h.pw = __builtin_fma(e1, W.s, h.pw);
   h.pz = __builtin_fma(e2, cs, h.pz);
 }
 
-__device__ __forceinline__ void pair_drift(HalfOrbit &h, double wu, double wz) {
+template <bool TAN>
+__device__ __forceinline__ void pair_drift(HalfOrbit &h, double wu, double wz, double t) {
   h.w = __builtin_fma(wu, h.pw, h.w);
   h.z = __builtin_fma(wz, h.pz, h.z);
+  if (TAN) {
+    h.dw = __builtin_fma(t, h.dpw, h.dw);
+    h.dz = __builtin_fma(t, h.dpz, h.dz);
+  }
 }
 
-template <int FORM>
+template <int FORM, bool TAN>
 __device__ __forceinline__ void pair_step(HalfOrbit &h, const StepWeights &d, const double2 *__restrict__ tab) {
   using F = FormPattern<FORM>;
   constexpr int NK = F::NK;
+  auto drift = [&](int q) { pair_drift<TAN>(h, d.dnode[q], d.dnodez[q], d.drift[q]); };
+  auto kick = [&](int q) { pair_kick<TAN>(h, d.ka[q], d.kb[q], tab); };
   if constexpr (F::LEAD) {
 #pragma unroll
     for (int i = 0; i < NK; ++i) {
-      pair_drift(h, d.dnode[F::drift_idx[i]], d.dnodez[F::drift_idx[i]]);
-      pair_kick(h, d.ka[F::kick_idx[i]], d.kb[F::kick_idx[i]], tab);
+      drift(F::drift_idx[i]);
+      kick(F::kick_idx[i]);
     }
-    pair_drift(h, d.dnode[F::drift_idx[NK]], d.dnodez[F::drift_idx[NK]]);
+    drift(F::drift_idx[NK]);
   } else {
-    pair_kick(h, d.ka[0], d.kb[0], tab);
-    pair_drift(h, d.dnode[0], d.dnodez[0]);
+    kick(0);
+    drift(0);
   }
 }
 
-template <int FORM, bool WINV>
-__global__ __launch_bounds__(512, 2) void k_fwd_pair(FwdDesc d, int64_t full_blocks) {
+// renorm_node's scale, its sum in the same order in the even lane.
+__device__ __forceinline__ void pair_renorm(HalfOrbit &h) {
+  const double dv = dpp_pair<DPP_SWAP>(h.dw), dpv = dpp_pair<DPP_SWAP>(h.dpw);
+  double a = h.dw * h.dw;
+  a = __builtin_fma(dv, dv, a);
+  a = __builtin_fma(h.dz, h.dz, a);
+  a = __builtin_fma(h.dpw, h.dpw, a);
+  a = __builtin_fma(dpv, dpv, a);
+  a = __builtin_fma(h.dpz, h.dpz, a);
+  const int s = __builtin_amdgcn_mov_dpp((__builtin_amdgcn_frexp_exp(a) - 1) >> 1, DPP_EVEN, 0xF, 0xF, false);
+  h.dw = __builtin_amdgcn_ldexp(h.dw, -s);
+  h.dz = __builtin_amdgcn_ldexp(h.dz, -s);
+  h.dpw = __builtin_amdgcn_ldexp(h.dpw, -s);
+  h.dpz = __builtin_amdgcn_ldexp(h.dpz, -s);
+  h.kexp += s;
+}
+
+template <int FORM, bool TAN, bool WINV>
+__global__ __launch_bounds__(512, 2) void k_fwd_pair(FwdDesc, int64_t full_blocks) {
   __shared__ double2 s_tab[AW_TAB_N];
   load_sincos_table(s_tab);
+  const FwdDesc &d = launched_desc();
   const int64_t tile = tile_of_wave(full_blocks);   // of 32 orbits
   if (tile * 32 >= d.N) return;
-  const int64_t m0 = tile * 32 + ((int)__lane_id() >> 1);
-  const bool act = m0 < d.N;
-  const int64_t m = act ? m0 : d.N - 1;   // past the end: repeat a valid orbit, never stored
+  const int64_t m = tile * 32 + ((int)__lane_id() >> 1);
   const bool odd = (threadIdx.x & 1u) != 0;
-  const int64_t N = d.N;
+  const int64_t n[1] = {m < d.N ? m : d.N - 1};     // past the end: repeat a valid orbit, never stored
+  const bool act[1] = {m < d.N && !odd};            // the even lane stores the orbit
+  Orbit o[1];
+  bool left[1];
+  start_orbit<TAN, false>(d, n[0], o[0], left[0]);
+  const double xs[1] = {o[0].x}, ys[1] = {o[0].y}, zs[1] = {o[0].z};
   HalfOrbit h;
-  if (d.k_begin == 0) {
-#pragma clang fp contract(off)
-    double s[6];
-    gen_ic(d, m, s);
-    h.w = to_nodes(odd ? s[0] - s[1] : s[0] + s[1]);
-    h.pw = odd ? s[3] - s[4] : s[3] + s[4];
-    h.z = to_nodes(2.0 * s[2]);
-    h.pz = times_sqrt2(s[5]);
-    h.p0w = h.pw;
-    h.p0z = h.pz;
-    h.jsum = 0.0;
-  } else {
-    const double *c = d.carry;
-    const int64_t r = odd ? 1 : 0;
-    h.w = c[(0 + r) * N + m];
-    h.pw = c[(3 + r) * N + m];
-    h.z = c[2 * N + m];
-    h.pz = c[5 * N + m];
-    h.p0w = c[(15 + r) * N + m];
-    h.p0z = c[17 * N + m];
-    h.jsum = c[18 * N + m];
-    if (!((int)c[21 * N + m] & CARRY_NODES)) {
-      h.w = to_nodes(h.w);
-      h.z = to_nodes(2.0 * h.z);
-      h.pz = times_sqrt2(h.pz);
-      h.p0z = times_sqrt2(h.p0z);
-    }
-  }
-  const double ws = h.w, zs = h.z;
+  h.w = odd ? o[0].y : o[0].x;
+  h.pw = odd ? o[0].py : o[0].px;
+  h.z = o[0].z;
+  h.pz = o[0].pz;
+  h.dw = odd ? o[0].dy : o[0].dx;
+  h.dpw = odd ? o[0].dpy : o[0].dpx;
+  h.dz = o[0].dz;
+  h.dpz = o[0].dpz;
+  h.p0w = odd ? o[0].p0y : o[0].p0x;
+  h.p0z = o[0].p0z;
+  h.jsum = o[0].jsum;
+  h.kexp = o[0].kexp;
   const StepWeights sw = d.w;
+  const int64_t k0 = d.k_begin, k1 = d.k_end, mask = d.renorm_mask;
 #pragma nounroll
-  for (int64_t k = d.k_begin; k < d.k_end; ++k) {
-    pair_step<FORM>(h, sw, s_tab);
+  for (int64_t k = k0; k < k1; ++k) {
+    pair_step<FORM, TAN>(h, sw, s_tab);
     // J as run_orbits accumulates it, in the even lane: the u, v and z squares
     // in that order.
     const double e = h.pw - h.p0w;
-    const double ep = swap_pair(e);
+    const double ep = dpp_pair<DPP_SWAP>(e);
     const double ez = h.pz - h.p0z;
     h.jsum = __builtin_fma(e, e, h.jsum);
     h.jsum = __builtin_fma(ep, ep, h.jsum);
     h.jsum = __builtin_fma(ez, ez, h.jsum);
+    if (TAN && ((k + 1) & mask) == 0) pair_renorm(h);
   }
-  const double dw = h.w - ws;
-  const double dwp = swap_pair(dw);   // the partner's displacement
-  if (!act) return;
-  double *c = d.carry;
-  if (odd) {
-    c[1 * N + m] = h.w;
-    c[4 * N + m] = h.pw;
-    c[16 * N + m] = h.p0w;
-    return;
-  }
-  if (WINV) {
-#pragma clang fp contract(off)
-    double phi, mu;
-    const double du = dw * AW_RAD_PER_NODE, dv = dwp * AW_RAD_PER_NODE;
-    const double dz = (h.z - zs) * (0.5 * AW_RAD_PER_NODE);
-    vdir_key(0.5 * (du + dv) / d.wdt, 0.5 * (du - dv) / d.wdt, dz / d.wdt, phi, mu);
-    d.bins[m] = bin_of(phi, mu, d.klo0, d.khi0, d.klo1, d.khi1, d.W, d.H, true);
-  }
-  c[0 * N + m] = h.w;
-  c[2 * N + m] = h.z;
-  c[3 * N + m] = h.pw;
-  c[5 * N + m] = h.pz;
-  c[15 * N + m] = h.p0w;
-  c[17 * N + m] = h.p0z;
-  c[18 * N + m] = h.jsum;
-  c[20 * N + m] = (double)d.k_end;
-  if (d.k_begin == 0) {
-    // what a first launch of run_orbits writes for a tangent-free orbit
-    double s0[6];
-    gen_ic(d, m, s0);
-#pragma unroll
-    for (int r = 6; r < 12; ++r) c[r * N + m] = 0.0;
-    c[12 * N + m] = s0[0]; c[13 * N + m] = s0[1]; c[14 * N + m] = s0[2];
-    c[19 * N + m] = 0.0;
-  }
-  c[21 * N + m] = (double)CARRY_NODES;   // no window test here
+  // The whole orbit again, as the even lane stores it.
+  o[0].x = h.w;
+  o[0].y = dpp_pair<DPP_SWAP>(h.w);
+  o[0].z = h.z;
+  o[0].px = h.pw;
+  o[0].py = dpp_pair<DPP_SWAP>(h.pw);
+  o[0].pz = h.pz;
+  o[0].dx = h.dw;
+  o[0].dy = dpp_pair<DPP_SWAP>(h.dw);
+  o[0].dz = h.dz;
+  o[0].dpx = h.dpw;
+  o[0].dpy = dpp_pair<DPP_SWAP>(h.dpw);
+  o[0].dpz = h.dpz;
+  o[0].p0x = h.p0w;
+  o[0].p0y = dpp_pair<DPP_SWAP>(h.p0w);
+  o[0].p0z = h.p0z;
+  o[0].jsum = h.jsum;
+  o[0].kexp = h.kexp;
+  finish_orbits<TAN, 1, WINV>(reread(d), o, n, act, left, xs, ys, zs, k0, k1);
 }
 
 // Persistent batched propagation: every wave takes the next tile of 64 OPL
@@ -713,22 +732,24 @@ static TileGrid tile_grid(int64_t n_tiles, int lanes, bool two_of_512) {
   return {full, (unsigned)(full + tail)};
 }
 
-// Two lanes per orbit: tangent-free intermediate or time-window launches
-// without the window test, when asked for (lanes_per_orbit 2) or, by
-// default, when one lane per orbit would leave SIMDs without a wave.
-static bool use_pair(const FwdDesc &d, const Tuning &t, bool tan) {
-  if (tan || d.filter || !(d.window_v || d.k_end < d.T) || d.N <= 0) return false;
+// Two lanes per orbit: without the window test, when asked for
+// (lanes_per_orbit 2) or, by default, while every pair's wave has a SIMD of its
+// own.  200 S6 steps in us, one lane and two: 32768 orbits 238 and 211 (188 and
+// 148 without the tangent); past that two waves share a SIMD, 33000 orbits 234
+// and 333 (187 and 237).
+static bool use_pair(const FwdDesc &d, const Tuning &t) {
+  if (d.filter || d.N <= 0) return false;
   if (t.lpo) return t.lpo == 2;
-  return d.N < (int64_t)n_cus() * 4 * 64;
+  return d.N <= (int64_t)n_cus() * 4 * 32;
 }
 
 template <int FORM, bool TAN>
 static hipError_t fwd_dispatch_opl(const FwdDesc &d, const Tuning &t, hipStream_t s) {
   if (d.N <= 0) return hipSuccess;
-  if (use_pair(d, t, TAN)) {
+  if (use_pair(d, t)) {
     const TileGrid g = tile_grid((d.N + 31) / 32, 512, false);
-    if (d.window_v) hipLaunchKernelGGL((k_fwd_pair<FORM, true>), dim3(g.blocks), dim3(512), 0, s, d, g.full_blocks);
-    else hipLaunchKernelGGL((k_fwd_pair<FORM, false>), dim3(g.blocks), dim3(512), 0, s, d, g.full_blocks);
+    if (d.window_v) hipLaunchKernelGGL((k_fwd_pair<FORM, TAN, true>), dim3(g.blocks), dim3(512), 0, s, d, g.full_blocks);
+    else hipLaunchKernelGGL((k_fwd_pair<FORM, TAN, false>), dim3(g.blocks), dim3(512), 0, s, d, g.full_blocks);
     return hipGetLastError();
   }
   // The window test and the time-window velocity run with one orbit per lane
