@@ -156,9 +156,9 @@ typedef struct {
  * {0, 64, 128, 256, 512}: the kernels hold a 64 KB sine/cosine table per
  * block, so blocks of 512 lanes are needed for a full CU.  The propagation runs
  * every wave on a tile of its own; 0 picks blocks of 512 there, with as many
- * waves at work as there are tiles.  The adjoints run one orbit per lane of a
- * block; 0 picks 512 when the ensemble gives every CU at least one such block,
- * else the largest of 256, 128 and 64 that still does.  orbits_per_lane in
+ * waves at work as there are tiles.  The adjoints run one orbit per lane or pair
+ * of lanes of a block; 0 picks 256 there while no CU gets a second such block,
+ * else 512.  orbits_per_lane in
  * {1, 2}; unroll in {1, 2}; the window-test and time-window propagation run
  * one orbit per lane, not unrolled.
  * renorm_every in {1, 2, 4, 8, 16}.  persistent_wgs: workgroups of the batched

@@ -27,12 +27,12 @@
 // exponent is recomputed in the reverse sweep from the stored pre-rescale
 // tangent, so it matches the forward pass exactly.
 //
-// Forward kernel: one lane per orbit runs the map with its tangent, stores
+// Forward kernel: one lane per orbit, or two for few orbits, runs the map with its tangent, stores
 // (s, w) at the start of every segment of `ckpt` steps and writes L.  In the
 // last segments, as many as the workspace has room for, it also keeps (s, w)
 // at the end of every ADJ_SUB-th step and of the segment's last step (before
 // any rescale).
-// Backward kernel: one lane per orbit walks the segments from the last; a
+// Backward kernel: it walks the segments from the last; a
 // segment whose states were not kept it recomputes from its checkpoint, keeping
 // the same ones, then it sweeps the steps backwards, undoing each stage by its exact
 // inverse (drift: X -= t P, dX -= t dP; kick: P -= the kick's increment,
@@ -216,14 +216,6 @@ __device__ __forceinline__ double tan_sum2(const Orbit &o) {
   return __builtin_fma(o.dpz, o.dpz, a);
 }
 
-// dL/dw_T in the scaled frame: w_T over the sum of its squares, scaled by the
-// upstream gradient gl.
-__device__ __forceinline__ void end_condition(const Orbit &o, Adjoint2 &a, double gl) {
-  const double c = gl / tan_sum2(o);
-  a.dxb = c * o.dx; a.dyb = c * o.dy; a.dzb = c * o.dz;
-  a.dpxb = c * o.dpx; a.dpyb = c * o.dpy; a.dpzb = c * o.dpz;
-}
-
 // The initial-state gradient, back from the scaled frame (d/dx = d/du + d/dv,
 // d/dy = d/du - d/dv, d/dz = sqrt 2 d/d(sqrt 2 z); momenta alike).
 __device__ __forceinline__ void store_grad2(const FtleDesc &d, int64_t n, const Adjoint2 &a) {
@@ -237,227 +229,367 @@ __device__ __forceinline__ void store_grad2(const FtleDesc &d, int64_t n, const 
   d.geps[n] = a.eb;
 }
 
-// Power-of-two exponent the forward rescale applies to this tangent.
-__device__ __forceinline__ int rescale_exponent(const Orbit &o) {
-  Orbit t = o;
-  t.kexp = 0;
-  renorm_node(t);
-  return t.kexp;
-}
+// One orbit's state, tangent and adjoint as the kernels below hold them: on one
+// lane, or on the two lanes of a pair (HalfOrbit; the adjoint is split the same
+// way, and the even lane's eb is the orbit's).  The sums over u and v and what they
+// enter (zb, dzb, dp_z, eb) are formed in the even lane as rev_kick2 forms them and
+// handed to the odd one, so both ways give the same bits.
+// Bound by VALU issue: a step back is 903 VALU instructions on two lanes (162 of
+// them the hand-overs) and 1024 on one, a step forward 449 and 559; 16384 orbits
+// over 200 steps take 600 us and 679, 4096 orbits 584 and 665.
+struct OneLane {
+  Orbit o;
+  Adjoint2 a{0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  double n0;  // |w_0|^2
 
-template <int FORM>
+  static __device__ __forceinline__ int64_t orbit() { return (int64_t)blockIdx.x * blockDim.x + threadIdx.x; }
+  __device__ __forceinline__ void begin() {
+    o.p0x = o.p0y = o.p0z = 0.0;
+    o.jsum = 0.0;
+    o.kexp = 0;
+  }
+  __device__ __forceinline__ void start(const FtleDesc &d, int64_t n) {
+    const int64_t N = d.N;
+    begin();
+    o.x = d.ic[0 * N + n]; o.y = d.ic[1 * N + n]; o.z = d.ic[2 * N + n];
+    o.px = d.ic[3 * N + n]; o.py = d.ic[4 * N + n]; o.pz = d.ic[5 * N + n];
+    o.dx = d.w0[0 * N + n]; o.dy = d.w0[1 * N + n]; o.dz = d.w0[2 * N + n];
+    o.dpx = d.w0[3 * N + n]; o.dpy = d.w0[4 * N + n]; o.dpz = d.w0[5 * N + n];
+    n0 = tan_sum2(o);   // before the frame
+    to_node(o);
+  }
+  __device__ __forceinline__ void load(const double *p, int64_t N, int64_t n) { load12(p, N, n, o); }
+  __device__ __forceinline__ void store(double *p, int64_t N, int64_t n) const { store12(p, N, n, o); }
+  template <int FORM>
+  __device__ __forceinline__ void fwd(const FtleDesc &d, const double2 *__restrict__ tab) { tan_step<FORM>(o, d, tab); }
+  __device__ __forceinline__ double sum2() const { return tan_sum2(o); }
+  // The power-of-two exponent of the forward rescale of this tangent, and w <- 2^-k w.
+  __device__ __forceinline__ int exponent() const {
+    Orbit t = o;
+    t.kexp = 0;
+    renorm_node(t);
+    return t.kexp;
+  }
+  __device__ __forceinline__ int rescale() {
+    const int k0 = o.kexp;
+    renorm_node(o);
+    return o.kexp - k0;
+  }
+  __device__ __forceinline__ void unscale(int k) {
+    o.dx = __builtin_amdgcn_ldexp(o.dx, k);
+    o.dy = __builtin_amdgcn_ldexp(o.dy, k);
+    o.dz = __builtin_amdgcn_ldexp(o.dz, k);
+    o.dpx = __builtin_amdgcn_ldexp(o.dpx, k);
+    o.dpy = __builtin_amdgcn_ldexp(o.dpy, k);
+    o.dpz = __builtin_amdgcn_ldexp(o.dpz, k);
+  }
+  __device__ __forceinline__ void rescale_adjoint(int k) {
+    a.dxb = __builtin_amdgcn_ldexp(a.dxb, -k);
+    a.dyb = __builtin_amdgcn_ldexp(a.dyb, -k);
+    a.dzb = __builtin_amdgcn_ldexp(a.dzb, -k);
+    a.dpxb = __builtin_amdgcn_ldexp(a.dpxb, -k);
+    a.dpyb = __builtin_amdgcn_ldexp(a.dpyb, -k);
+    a.dpzb = __builtin_amdgcn_ldexp(a.dpzb, -k);
+  }
+  __device__ __forceinline__ bool writes() const { return true; }
+  __device__ __forceinline__ int kexp() const { return o.kexp; }
+  // dL/dw_T in the scaled frame: w_T over the sum of its squares, scaled by the
+  // upstream gradient gl.
+  __device__ __forceinline__ void end_condition(double gl) {
+    const double c = gl / sum2();
+    a.dxb = c * o.dx; a.dyb = c * o.dy; a.dzb = c * o.dz;
+    a.dpxb = c * o.dpx; a.dpyb = c * o.dpy; a.dpzb = c * o.dpz;
+  }
+  template <int FORM, bool EPS0>
+  __device__ __forceinline__ void rev(const FtleDesc &d, const double2 *__restrict__ tab) {
+    rev_tan_step<FORM, EPS0>(o, a, d, tab);
+  }
+  template <bool EPS0>
+  __device__ __forceinline__ void finish(const FtleDesc &d, int64_t n) {
+    if (!EPS0) a.eb /= d.eps;   // the kicks collected eps epsbar
+    store_grad2(d, n, a);
+  }
+};
+
+struct TwoLanes {
+  HalfOrbit h;
+  double wb = 0.0, zb = 0.0, pwb = 0.0, pzb = 0.0;      // state adjoint
+  double dwb = 0.0, dzb = 0.0, dpwb = 0.0, dpzb = 0.0;  // tangent adjoint
+  double eb = 0.0, n0;
+  int odd;
+
+  static __device__ __forceinline__ int64_t orbit() {
+    return ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 1;
+  }
+  __device__ __forceinline__ void begin() {
+    odd = (int)(threadIdx.x & 1u);
+    h.p0w = h.p0z = h.jsum = 0.0;
+    h.kexp = 0;
+  }
+  __device__ __forceinline__ void start(const FtleDesc &d, int64_t n) {
+    OneLane whole;
+    whole.start(d, n);
+    begin();
+    n0 = whole.n0;
+    h.w = odd ? whole.o.y : whole.o.x;
+    h.pw = odd ? whole.o.py : whole.o.px;
+    h.dw = odd ? whole.o.dy : whole.o.dx;
+    h.dpw = odd ? whole.o.dpy : whole.o.dpx;
+    h.z = whole.o.z; h.pz = whole.o.pz;
+    h.dz = whole.o.dz; h.dpz = whole.o.dpz;
+  }
+  // Both lanes store z's rows, so that a lane reads back what it wrote itself.
+  __device__ __forceinline__ void load(const double *p, int64_t N, int64_t n) {
+    h.w = p[(0 + odd) * N + n]; h.z = p[2 * N + n];
+    h.pw = p[(3 + odd) * N + n]; h.pz = p[5 * N + n];
+    h.dw = p[(6 + odd) * N + n]; h.dz = p[8 * N + n];
+    h.dpw = p[(9 + odd) * N + n]; h.dpz = p[11 * N + n];
+  }
+  __device__ __forceinline__ void store(double *p, int64_t N, int64_t n) const {
+    p[(0 + odd) * N + n] = h.w; p[2 * N + n] = h.z;
+    p[(3 + odd) * N + n] = h.pw; p[5 * N + n] = h.pz;
+    p[(6 + odd) * N + n] = h.dw; p[8 * N + n] = h.dz;
+    p[(9 + odd) * N + n] = h.dpw; p[11 * N + n] = h.dpz;
+  }
+  template <int FORM>
+  __device__ __forceinline__ void fwd(const FtleDesc &d, const double2 *__restrict__ tab) {
+    pair_step<FORM, true>(h, d.w, tab);
+  }
+  __device__ __forceinline__ double sum2() const { return pair_tan_sum2(h); }
+  __device__ __forceinline__ int exponent() const { return pair_rescale_exponent(h); }
+  __device__ __forceinline__ int rescale() {
+    const int k = exponent();
+    pair_rescale(h, k);
+    return k;
+  }
+  __device__ __forceinline__ void unscale(int k) { pair_rescale(h, -k); }
+  __device__ __forceinline__ void rescale_adjoint(int k) {
+    dwb = __builtin_amdgcn_ldexp(dwb, -k);
+    dzb = __builtin_amdgcn_ldexp(dzb, -k);
+    dpwb = __builtin_amdgcn_ldexp(dpwb, -k);
+    dpzb = __builtin_amdgcn_ldexp(dpzb, -k);
+  }
+  __device__ __forceinline__ bool writes() const { return !odd; }
+  __device__ __forceinline__ int kexp() const { return h.kexp; }
+  __device__ __forceinline__ void end_condition(double gl) {
+    const double c = gl / sum2();
+    dwb = c * h.dw; dzb = c * h.dz;
+    dpwb = c * h.dpw; dpzb = c * h.dpz;
+  }
+  __device__ __forceinline__ void drift(double wu, double wz, double t) {
+    h.w = __builtin_fma(-wu, h.pw, h.w);
+    h.z = __builtin_fma(-wz, h.pz, h.z);
+    h.dw = __builtin_fma(-t, h.dpw, h.dw);
+    h.dz = __builtin_fma(-t, h.dpz, h.dz);
+    pwb = __builtin_fma(t, wb, pwb);
+    pzb = __builtin_fma(t, zb, pzb);
+    dpwb = __builtin_fma(t, dwb, dpwb);
+    dpzb = __builtin_fma(t, dzb, dpzb);
+  }
+  // rev_kick2's sums over u and v; right in the even lane.
+  static __device__ __forceinline__ double both(double f, double x) {
+    return __builtin_fma(f, x, dpp_pair<DPP_SWAP>(f * x));
+  }
+  template <bool EPS0>
+  __device__ __forceinline__ void kick(double ka, double kb, double kt, double ktb, const double2 *__restrict__ tab) {
+    NodeSC sc[2];
+    const double ang[2] = {h.w, h.z};
+    sincos_nodes<2, true>(ang, sc, tab);
+    const NodeSC W = sc[0], Z = sc[1];
+    const double e1 = __builtin_fma(ka, Z.c, ka);
+    const double e2 = kb * Z.s;
+    const double g = __builtin_fma(2.0, e1, -2.0 * ka);
+    const double cs = W.c + dpp_pair<DPP_SWAP>(W.c);
+    const double mzz = cs * g;
+
+    const double aww = dpwb * h.dw, azz = dpzb * h.dz;
+    const double awz = __builtin_fma(dpwb, h.dz, dpzb * h.dw);
+    const double q = both(W.s, pwb), kc = both(W.c, aww), ks = both(W.s, awz);
+    const double A = __builtin_fma(cs, pzb, -ks);
+    const double csz = cs * azz;
+    const double qk = q + kc;
+    if constexpr (EPS0) {
+      const double f1 = __builtin_fma(kt, Z.c, kt), f2 = ktb * Z.s, gf = __builtin_fma(2.0, f1, -2.0 * kt);
+      eb = __builtin_fma(f1, qk, eb);
+      eb = __builtin_fma(f2, A, eb);
+      eb = __builtin_fma(gf, csz, eb);
+    } else {
+      eb = __builtin_fma(e1, qk, eb);
+      eb = __builtin_fma(e2, A, eb);
+      eb = __builtin_fma(g, csz, eb);
+    }
+
+    const double hb = __builtin_fma(e2, pzb, g * azz);
+    wb = __builtin_fma(W.c, __builtin_fma(-e2, awz, e1 * pwb), __builtin_fma(-W.s, __builtin_fma(e1, aww, hb), wb));
+    zb = dpp_pair<DPP_EVEN>(__builtin_fma(g, A, __builtin_fma(-e2, __builtin_fma(2.0, csz, qk), zb)));
+
+    const double hd = e2 * dpzb;
+    dwb = __builtin_fma(W.c, e1 * dpwb, __builtin_fma(-W.s, hd, dwb));
+    dzb = dpp_pair<DPP_EVEN>(__builtin_fma(mzz, dpzb, __builtin_fma(-e2, both(W.s, dpwb), dzb)));
+
+    const double r = e2 * h.dz;
+    h.dpw = __builtin_fma(-W.c, e1 * h.dw, __builtin_fma(W.s, r, h.dpw));
+    h.dpz = dpp_pair<DPP_EVEN>(__builtin_fma(-mzz, h.dz, __builtin_fma(e2, both(W.s, h.dw), h.dpz)));
+    h.pw = __builtin_fma(-e1, W.s, h.pw);
+    h.pz = __builtin_fma(-e2, cs, h.pz);
+  }
+  template <int FORM, bool EPS0>
+  __device__ __forceinline__ void rev(const FtleDesc &d, const double2 *__restrict__ tab) {
+    using F = FormPattern<FORM>;
+    constexpr int NK = F::NK;
+    auto undrift = [&](int q) { drift(d.w.dnode[q], d.w.dnodez[q], d.w.drift[q]); };
+    auto unkick = [&](int q) { kick<EPS0>(d.w.ka[q], d.w.kb[q], d.kt[q], d.ktb[q], tab); };
+    if constexpr (F::LEAD) {
+      undrift(F::drift_idx[NK]);
+#pragma unroll
+      for (int i = NK - 1; i >= 0; --i) {
+        unkick(F::kick_idx[i]);
+        undrift(F::drift_idx[i]);
+      }
+    } else {
+      undrift(0);
+      unkick(0);
+    }
+  }
+  template <bool EPS0>
+  __device__ __forceinline__ void finish(const FtleDesc &d, int64_t n) {
+    if (!EPS0) eb /= d.eps;   // the kicks collected eps epsbar
+    Adjoint2 a{};
+    a.xb = wb; a.yb = dpp_pair<DPP_SWAP>(wb); a.zb = zb;
+    a.pxb = pwb; a.pyb = dpp_pair<DPP_SWAP>(pwb); a.pzb = pzb;
+    a.eb = eb;
+    if (!odd) store_grad2(d, n, a);
+  }
+};
+
+template <int FORM, class LANES>
 __global__ __launch_bounds__(512) void k_ftle_fwd(FtleDesc d) {
   __shared__ double2 s_tab[AW_TAB_N];
   load_sincos_table(s_tab);
-  const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t n = LANES::orbit();
   if (n >= d.N) return;
   const int64_t N = d.N;
-  Orbit o;
-  o.x = d.ic[0 * N + n]; o.y = d.ic[1 * N + n]; o.z = d.ic[2 * N + n];
-  o.px = d.ic[3 * N + n]; o.py = d.ic[4 * N + n]; o.pz = d.ic[5 * N + n];
-  o.dx = d.w0[0 * N + n]; o.dy = d.w0[1 * N + n]; o.dz = d.w0[2 * N + n];
-  o.dpx = d.w0[3 * N + n]; o.dpy = d.w0[4 * N + n]; o.dpz = d.w0[5 * N + n];
-  o.p0x = o.px; o.p0y = o.py; o.p0z = o.pz;
-  o.jsum = 0.0;
-  o.kexp = 0;
-  const double n0 = tan_sum2(o);   // |w_0|^2, before the frame
-  to_node(o);
+  LANES l;
+  l.start(d, n);
   for (int64_t s = 0; s < d.n_seg; ++s) {
-    store12(d.ckpts + s * 12 * N, N, n, o);
+    l.store(d.ckpts + s * 12 * N, N, n);
     const int64_t g0 = s * d.ckpt;
     const int64_t g1 = g0 + d.ckpt < d.T ? g0 + d.ckpt : d.T;
     const bool keep = s >= d.keep_from;
     double *steps = d.steps + adj_steps_at(d, s) * 12 * N;
     for (int64_t g = g0; g < g1; ++g) {
-      tan_step<FORM>(o, d, s_tab);
-      if (keep && adj_kept(g, g1)) store12(steps + adj_slot(g, g0) * 12 * N, N, n, o);
+      l.template fwd<FORM>(d, s_tab);
+      if (keep && adj_kept(g, g1)) l.store(steps + adj_slot(g, g0) * 12 * N, N, n);
       if (((g + 1) & RESCALE_MASK) == 0) {
-        const int k0 = o.kexp;
-        renorm_node(o);
-        d.exps[((g + 1) / (RESCALE_MASK + 1) - 1) * N + n] = (int16_t)(o.kexp - k0);
+        const int k = l.rescale();
+        if (l.writes()) d.exps[((g + 1) / (RESCALE_MASK + 1) - 1) * N + n] = (int16_t)k;
       }
     }
   }
-  store12(d.ckpts + d.n_seg * 12 * N, N, n, o);   // the final state (after any last rescale)
+  l.store(d.ckpts + d.n_seg * 12 * N, N, n);   // the final state (after any last rescale)
   if (d.L) {
-    const double n2 = 0.5 * tan_sum2(o);
+    const double n2 = 0.5 * l.sum2();
     const int e = __builtin_amdgcn_frexp_exp(n2);
     const double mant = __builtin_amdgcn_frexp_mant(n2);
-    d.L[n] = 0.5 * ((double)(2 * o.kexp + e) * LN2_D + log(mant)) - 0.5 * log(n0);
+    if (l.writes()) d.L[n] = 0.5 * ((double)(2 * l.kexp() + e) * LN2_D + log(mant)) - 0.5 * log(l.n0);
   }
 }
 
-template <int FORM, bool EPS0>
+template <int FORM, bool EPS0, class LANES>
 __global__ __launch_bounds__(512) void k_ftle_bwd(FtleDesc d) {
   __shared__ double2 s_tab[AW_TAB_N];
   load_sincos_table(s_tab);
-  const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t n = LANES::orbit();
   if (n >= d.N) return;
   const int64_t N = d.N;
   const double gl = d.gL ? d.gL[n] : 1.0;
-  Adjoint2 a{0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  Orbit o;
-  o.p0x = o.p0y = o.p0z = 0.0;
-  o.jsum = 0.0;
-  o.kexp = 0;
+  LANES l;
+  l.begin();
   for (int64_t s = d.n_seg - 1; s >= 0; --s) {
     const int64_t g0 = s * d.ckpt;
     const int64_t g1 = g0 + d.ckpt < d.T ? g0 + d.ckpt : d.T;
     double *steps = d.steps + adj_steps_at(d, s) * 12 * N;
     if (s < d.keep_from) {  // else the forward pass has kept the step states already
-      load12(d.ckpts + s * 12 * N, N, n, o);
+      l.load(d.ckpts + s * 12 * N, N, n);
       for (int64_t g = g0; g < g1; ++g) {
-        tan_step<FORM>(o, d, s_tab);
-        if (adj_kept(g, g1)) store12(steps + adj_slot(g, g0) * 12 * N, N, n, o);
-        if (((g + 1) & RESCALE_MASK) == 0) renorm_node(o);
+        l.template fwd<FORM>(d, s_tab);
+        if (adj_kept(g, g1)) l.store(steps + adj_slot(g, g0) * 12 * N, N, n);
+        if (((g + 1) & RESCALE_MASK) == 0) l.rescale();
       }
     }
     for (int64_t g = g1 - 1; g >= g0; --g) {
       // end of step g, before any rescale: kept (every rescale step is kept,
       // since ADJ_SUB divides 8), or rebuilt by the inverse of step g + 1
-      if (adj_kept(g, g1)) load12(steps + adj_slot(g, g0) * 12 * N, N, n, o);
-      if (g == d.T - 1) {
-        // dL/dw_T = w_T / |w_T|^2 (scaled by the upstream gradient).
-        end_condition(o, a, gl);
-      } else if (((g + 1) & RESCALE_MASK) == 0) {
-        const int k = rescale_exponent(o);
-        a.dxb = __builtin_amdgcn_ldexp(a.dxb, -k);
-        a.dyb = __builtin_amdgcn_ldexp(a.dyb, -k);
-        a.dzb = __builtin_amdgcn_ldexp(a.dzb, -k);
-        a.dpxb = __builtin_amdgcn_ldexp(a.dpxb, -k);
-        a.dpyb = __builtin_amdgcn_ldexp(a.dpyb, -k);
-        a.dpzb = __builtin_amdgcn_ldexp(a.dpzb, -k);
-      }
-      rev_tan_step<FORM, EPS0>(o, a, d, s_tab);
+      if (adj_kept(g, g1)) l.load(steps + adj_slot(g, g0) * 12 * N, N, n);
+      if (g == d.T - 1) l.end_condition(gl);  // dL/dw_T = w_T / |w_T|^2 (scaled by the upstream gradient)
+      else if (((g + 1) & RESCALE_MASK) == 0) l.rescale_adjoint(l.exponent());
+      l.template rev<FORM, EPS0>(d, s_tab);
     }
   }
-  if (!EPS0) a.eb /= d.eps;   // the kicks collected eps epsbar
-  store_grad2(d, n, a);
+  l.template finish<EPS0>(d, n);
 }
 
-template <int FORM, bool EPS0>
+template <int FORM, bool EPS0, class LANES>
 __global__ __launch_bounds__(512) void k_ftle_bwd_rev(FtleDesc d) {
   __shared__ double2 s_tab[AW_TAB_N];
   load_sincos_table(s_tab);
-  const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t n = LANES::orbit();
   if (n >= d.N) return;
   const int64_t N = d.N;
   const double gl = d.gL ? d.gL[n] : 1.0;
-  Adjoint2 a{0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  Orbit o;
-  o.p0x = o.p0y = o.p0z = 0.0;
-  o.jsum = 0.0;
-  o.kexp = 0;
+  LANES l;
+  l.begin();
   for (int64_t s = d.n_seg - 1; s >= 0; --s) {
     const int64_t g0 = s * d.ckpt;
     const int64_t g1 = g0 + d.ckpt < d.T ? g0 + d.ckpt : d.T;
     // Exact state at the end of step g1 - 1, after any rescale there.
-    load12(d.ckpts + (s + 1) * 12 * N, N, n, o);
+    l.load(d.ckpts + (s + 1) * 12 * N, N, n);
     for (int64_t g = g1 - 1; g >= g0; --g) {
-      // o: the state at the end of step g, after any rescale that followed it.
-      if (g == d.T - 1) {
-        end_condition(o, a, gl);
-      }
+      // here: the state at the end of step g, after any rescale that followed it
+      if (g == d.T - 1) l.end_condition(gl);
       if (((g + 1) & RESCALE_MASK) == 0) {
         // the forward set w_post = 2^-k w_pre: restore w_pre, and wbar_pre = 2^-k wbar_post
         const int k = d.exps[((g + 1) / (RESCALE_MASK + 1) - 1) * N + n];
-        o.dx = __builtin_amdgcn_ldexp(o.dx, k);
-        o.dy = __builtin_amdgcn_ldexp(o.dy, k);
-        o.dz = __builtin_amdgcn_ldexp(o.dz, k);
-        o.dpx = __builtin_amdgcn_ldexp(o.dpx, k);
-        o.dpy = __builtin_amdgcn_ldexp(o.dpy, k);
-        o.dpz = __builtin_amdgcn_ldexp(o.dpz, k);
-        a.dxb = __builtin_amdgcn_ldexp(a.dxb, -k);
-        a.dyb = __builtin_amdgcn_ldexp(a.dyb, -k);
-        a.dzb = __builtin_amdgcn_ldexp(a.dzb, -k);
-        a.dpxb = __builtin_amdgcn_ldexp(a.dpxb, -k);
-        a.dpyb = __builtin_amdgcn_ldexp(a.dpyb, -k);
-        a.dpzb = __builtin_amdgcn_ldexp(a.dpzb, -k);
+        l.unscale(k);
+        l.rescale_adjoint(k);
       }
-      rev_tan_step<FORM, EPS0>(o, a, d, s_tab);   // o: the state at the start of step g
+      l.template rev<FORM, EPS0>(d, s_tab);   // the state at the start of step g
     }
   }
-  if (!EPS0) a.eb /= d.eps;   // the kicks collected eps epsbar
-  store_grad2(d, n, a);
+  l.template finish<EPS0>(d, n);
+}
+
+template <bool EPS0>
+hipError_t launch_bwd(const FtleDesc &d, bool rev, int form, const Tuning &t, hipStream_t s) {
+  return for_form(form, [&](auto f) {
+    constexpr int F = decltype(f)::value;
+    const bool two = two_lanes(t, d.N);
+    if (two && rev) launch_lanes(k_ftle_bwd_rev<F, EPS0, TwoLanes>, 2 * d.N, d, t, s);
+    else if (two) launch_lanes(k_ftle_bwd<F, EPS0, TwoLanes>, 2 * d.N, d, t, s);
+    else if (rev) launch_lanes(k_ftle_bwd_rev<F, EPS0, OneLane>, d.N, d, t, s);
+    else launch_lanes(k_ftle_bwd<F, EPS0, OneLane>, d.N, d, t, s);
+  });
 }
 
 }  // namespace
 
-hipError_t launch_ftle_backward_reversible(const FtleDesc &d, int form, const Tuning &t, hipStream_t s) {
-  if (d.N <= 0) return hipSuccess;
-  const bool e0 = d.eps == 0.0;
-  const int tb = block_for(t, d.N);
-  const unsigned blocks = (unsigned)((d.N + tb - 1) / tb);
-  switch (form) {
-  case 1:
-    if (e0) hipLaunchKernelGGL(HIP_KERNEL_NAME(k_ftle_bwd_rev<1, true>), dim3(blocks), dim3(tb), 0, s, d);
-    else hipLaunchKernelGGL(HIP_KERNEL_NAME(k_ftle_bwd_rev<1, false>), dim3(blocks), dim3(tb), 0, s, d);
-    break;
-  case 2:
-    if (e0) hipLaunchKernelGGL(HIP_KERNEL_NAME(k_ftle_bwd_rev<2, true>), dim3(blocks), dim3(tb), 0, s, d);
-    else hipLaunchKernelGGL(HIP_KERNEL_NAME(k_ftle_bwd_rev<2, false>), dim3(blocks), dim3(tb), 0, s, d);
-    break;
-  case 4:
-    if (e0) hipLaunchKernelGGL(HIP_KERNEL_NAME(k_ftle_bwd_rev<4, true>), dim3(blocks), dim3(tb), 0, s, d);
-    else hipLaunchKernelGGL(HIP_KERNEL_NAME(k_ftle_bwd_rev<4, false>), dim3(blocks), dim3(tb), 0, s, d);
-    break;
-  case 6:
-    if (e0) hipLaunchKernelGGL(HIP_KERNEL_NAME(k_ftle_bwd_rev<6, true>), dim3(blocks), dim3(tb), 0, s, d);
-    else hipLaunchKernelGGL(HIP_KERNEL_NAME(k_ftle_bwd_rev<6, false>), dim3(blocks), dim3(tb), 0, s, d);
-    break;
-  case 7:
-    if (e0) hipLaunchKernelGGL(HIP_KERNEL_NAME(k_ftle_bwd_rev<7, true>), dim3(blocks), dim3(tb), 0, s, d);
-    else hipLaunchKernelGGL(HIP_KERNEL_NAME(k_ftle_bwd_rev<7, false>), dim3(blocks), dim3(tb), 0, s, d);
-    break;
-  default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
 hipError_t launch_ftle_forward(const FtleDesc &d, int form, const Tuning &t, hipStream_t s) {
   if (d.N <= 0) return hipSuccess;
-  const int tb = block_for(t, d.N);
-  const unsigned blocks = (unsigned)((d.N + tb - 1) / tb);
-  switch (form) {
-  case 1: hipLaunchKernelGGL(k_ftle_fwd<1>, dim3(blocks), dim3(tb), 0, s, d); break;
-  case 2: hipLaunchKernelGGL(k_ftle_fwd<2>, dim3(blocks), dim3(tb), 0, s, d); break;
-  case 4: hipLaunchKernelGGL(k_ftle_fwd<4>, dim3(blocks), dim3(tb), 0, s, d); break;
-  case 6: hipLaunchKernelGGL(k_ftle_fwd<6>, dim3(blocks), dim3(tb), 0, s, d); break;
-  case 7: hipLaunchKernelGGL(k_ftle_fwd<7>, dim3(blocks), dim3(tb), 0, s, d); break;
-  default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
+  return for_form(form, [&](auto f) {
+    constexpr int F = decltype(f)::value;
+    if (two_lanes(t, d.N)) launch_lanes(k_ftle_fwd<F, TwoLanes>, 2 * d.N, d, t, s);
+    else launch_lanes(k_ftle_fwd<F, OneLane>, d.N, d, t, s);
+  });
+}
+
+hipError_t launch_ftle_backward_reversible(const FtleDesc &d, int form, const Tuning &t, hipStream_t s) {
+  if (d.N <= 0) return hipSuccess;
+  return d.eps == 0.0 ? launch_bwd<true>(d, true, form, t, s) : launch_bwd<false>(d, true, form, t, s);
 }
 
 hipError_t launch_ftle_backward(const FtleDesc &d, int form, const Tuning &t, hipStream_t s) {
   if (d.N <= 0) return hipSuccess;
-  const bool e0 = d.eps == 0.0;
-  const int tb = block_for(t, d.N);
-  const unsigned blocks = (unsigned)((d.N + tb - 1) / tb);
-  switch (form) {
-  case 1:
-    if (e0) hipLaunchKernelGGL(HIP_KERNEL_NAME(k_ftle_bwd<1, true>), dim3(blocks), dim3(tb), 0, s, d);
-    else hipLaunchKernelGGL(HIP_KERNEL_NAME(k_ftle_bwd<1, false>), dim3(blocks), dim3(tb), 0, s, d);
-    break;
-  case 2:
-    if (e0) hipLaunchKernelGGL(HIP_KERNEL_NAME(k_ftle_bwd<2, true>), dim3(blocks), dim3(tb), 0, s, d);
-    else hipLaunchKernelGGL(HIP_KERNEL_NAME(k_ftle_bwd<2, false>), dim3(blocks), dim3(tb), 0, s, d);
-    break;
-  case 4:
-    if (e0) hipLaunchKernelGGL(HIP_KERNEL_NAME(k_ftle_bwd<4, true>), dim3(blocks), dim3(tb), 0, s, d);
-    else hipLaunchKernelGGL(HIP_KERNEL_NAME(k_ftle_bwd<4, false>), dim3(blocks), dim3(tb), 0, s, d);
-    break;
-  case 6:
-    if (e0) hipLaunchKernelGGL(HIP_KERNEL_NAME(k_ftle_bwd<6, true>), dim3(blocks), dim3(tb), 0, s, d);
-    else hipLaunchKernelGGL(HIP_KERNEL_NAME(k_ftle_bwd<6, false>), dim3(blocks), dim3(tb), 0, s, d);
-    break;
-  case 7:
-    if (e0) hipLaunchKernelGGL(HIP_KERNEL_NAME(k_ftle_bwd<7, true>), dim3(blocks), dim3(tb), 0, s, d);
-    else hipLaunchKernelGGL(HIP_KERNEL_NAME(k_ftle_bwd<7, false>), dim3(blocks), dim3(tb), 0, s, d);
-    break;
-  default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
+  return d.eps == 0.0 ? launch_bwd<true>(d, false, form, t, s) : launch_bwd<false>(d, false, form, t, s);
 }
 
 }  // namespace aw

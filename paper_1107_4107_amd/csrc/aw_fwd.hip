@@ -463,110 +463,14 @@ __global__ __launch_bounds__(512, two_blocks(TAN, OPL) ? 4 : 2) void k_fwd(FwdDe
 }
 
 // ---------------------------------------------------------------------------
-// Two lanes per orbit, for ensembles too small to give every SIMD a wave at one
-// lane per orbit (Fig. 4's 3.2e4 orbits make 500 waves for 1024 SIMDs).  In the
-// scaled frame neither the force nor its Jacobian couples u and v, so lane 2m of
-// a pair holds u, p_u and their tangent, lane 2m + 1 holds v's, and both hold z's.
-// A kick takes one table sine and cosine of the lane's own coordinate and the z
-// factors, swaps the cosine with the partner lane (cs = cos u + cos v is the same
-// sum in both lanes: IEEE addition commutes), and advances the lane's own momenta
-// and p_z; a drift advances the lane's coordinate and z.  The one sum that is
-// rounded differently by order, sin u du + sin v dv, is formed in the even lane
-// and handed to the odd one.  Every value is formed and rounded as in
-// run_orbits, so the states, carries, outputs and bins are bitwise those of one
-// lane per orbit.  The window test runs one lane per orbit.
+// Two lanes per orbit (pair_step), for ensembles too small to give every SIMD a
+// wave at one lane per orbit (Fig. 4's 3.2e4 orbits make 500 waves for 1024
+// SIMDs).  The window test runs one lane per orbit.
 // A lone wave is bound by its own issue and by the chain of its kicks, ten
 // dependent operations and a table read each.  An S6 step is 454 VALU instructions
 // instead of 563 with the tangent, 307 instead of 415 without: 4096 orbits over
 // 200 steps take 197 us instead of 235, and 134 instead of 184.
 // ---------------------------------------------------------------------------
-// Lanes 2m and 2m + 1 exchange v (DPP quad_perm [1, 0, 3, 2]), or both take lane
-// 2m's (quad_perm [0, 0, 2, 2]).  Every lane of the wave takes part: lanes past
-// the ensemble's end repeat a valid orbit.
-constexpr int DPP_SWAP = 0xB1, DPP_EVEN = 0xA0;
-
-template <int CTRL>
-__device__ __forceinline__ double dpp_pair(double v) {
-  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, false);
-  return __hiloint2double(hi, lo);
-}
-
-struct HalfOrbit {
-  double w, pw;          // own coordinate (u or v, in nodes) and its momentum
-  double z, pz;          // 2 z in nodes, sqrt 2 p_z
-  double dw, dpw, dz, dpz;  // their tangent
-  double p0w, p0z;
-  double jsum;           // meaningful in the pair's even lane
-  int kexp;
-};
-
-template <bool TAN>
-__device__ __forceinline__ void pair_kick(HalfOrbit &h, double a, double b, const double2 *__restrict__ tab) {
-  NodeSC sc[2];
-  const double ang[2] = {h.w, h.z};
-  sincos_nodes<2, true>(ang, sc, tab);
-  const NodeSC W = sc[0], Z = sc[1];
-  const double e1 = __builtin_fma(a, Z.c, a);
-  const double e2 = b * Z.s;
-  const double cs = W.c + dpp_pair<DPP_SWAP>(W.c);
-  if (TAN) {
-    const double f = e1 * h.dw, q = e2 * h.dz;
-    const double g = dpp_pair<DPP_EVEN>(__builtin_fma(W.s, h.dw, dpp_pair<DPP_SWAP>(W.s * h.dw)));
-    const double mz = cs * __builtin_fma(2.0, e1, -2.0 * a);
-    h.dpw = __builtin_fma(W.c, f, __builtin_fma(-W.s, q, h.dpw));
-    h.dpz = __builtin_fma(mz, h.dz, __builtin_fma(-e2, g, h.dpz));
-  }
-  h.pw = __builtin_fma(e1, W.s, h.pw);
-  h.pz = __builtin_fma(e2, cs, h.pz);
-}
-
-template <bool TAN>
-__device__ __forceinline__ void pair_drift(HalfOrbit &h, double wu, double wz, double t) {
-  h.w = __builtin_fma(wu, h.pw, h.w);
-  h.z = __builtin_fma(wz, h.pz, h.z);
-  if (TAN) {
-    h.dw = __builtin_fma(t, h.dpw, h.dw);
-    h.dz = __builtin_fma(t, h.dpz, h.dz);
-  }
-}
-
-template <int FORM, bool TAN>
-__device__ __forceinline__ void pair_step(HalfOrbit &h, const StepWeights &d, const double2 *__restrict__ tab) {
-  using F = FormPattern<FORM>;
-  constexpr int NK = F::NK;
-  auto drift = [&](int q) { pair_drift<TAN>(h, d.dnode[q], d.dnodez[q], d.drift[q]); };
-  auto kick = [&](int q) { pair_kick<TAN>(h, d.ka[q], d.kb[q], tab); };
-  if constexpr (F::LEAD) {
-#pragma unroll
-    for (int i = 0; i < NK; ++i) {
-      drift(F::drift_idx[i]);
-      kick(F::kick_idx[i]);
-    }
-    drift(F::drift_idx[NK]);
-  } else {
-    kick(0);
-    drift(0);
-  }
-}
-
-// renorm_node's scale, its sum in the same order in the even lane.
-__device__ __forceinline__ void pair_renorm(HalfOrbit &h) {
-  const double dv = dpp_pair<DPP_SWAP>(h.dw), dpv = dpp_pair<DPP_SWAP>(h.dpw);
-  double a = h.dw * h.dw;
-  a = __builtin_fma(dv, dv, a);
-  a = __builtin_fma(h.dz, h.dz, a);
-  a = __builtin_fma(h.dpw, h.dpw, a);
-  a = __builtin_fma(dpv, dpv, a);
-  a = __builtin_fma(h.dpz, h.dpz, a);
-  const int s = __builtin_amdgcn_mov_dpp((__builtin_amdgcn_frexp_exp(a) - 1) >> 1, DPP_EVEN, 0xF, 0xF, false);
-  h.dw = __builtin_amdgcn_ldexp(h.dw, -s);
-  h.dz = __builtin_amdgcn_ldexp(h.dz, -s);
-  h.dpw = __builtin_amdgcn_ldexp(h.dpw, -s);
-  h.dpz = __builtin_amdgcn_ldexp(h.dpz, -s);
-  h.kexp += s;
-}
-
 template <int FORM, bool TAN, bool WINV>
 __global__ __launch_bounds__(512, 2) void k_fwd_pair(FwdDesc, int64_t full_blocks) {
   __shared__ double2 s_tab[AW_TAB_N];
@@ -600,15 +504,8 @@ __global__ __launch_bounds__(512, 2) void k_fwd_pair(FwdDesc, int64_t full_block
 #pragma nounroll
   for (int64_t k = k0; k < k1; ++k) {
     pair_step<FORM, TAN>(h, sw, s_tab);
-    // J as run_orbits accumulates it, in the even lane: the u, v and z squares
-    // in that order.
-    const double e = h.pw - h.p0w;
-    const double ep = dpp_pair<DPP_SWAP>(e);
-    const double ez = h.pz - h.p0z;
-    h.jsum = __builtin_fma(e, e, h.jsum);
-    h.jsum = __builtin_fma(ep, ep, h.jsum);
-    h.jsum = __builtin_fma(ez, ez, h.jsum);
-    if (TAN && ((k + 1) & mask) == 0) pair_renorm(h);
+    pair_accum_j(h);
+    if (TAN && ((k + 1) & mask) == 0) pair_rescale(h, pair_rescale_exponent(h));
   }
   // The whole orbit again, as the even lane stores it.
   o[0].x = h.w;
@@ -705,12 +602,13 @@ int n_cus() {
   return ncu;
 }
 
+bool two_lanes(const Tuning &t, int64_t n) {
+  return n > 0 && (t.lpo ? t.lpo == 2 : n <= (int64_t)n_cus() * 4 * 32);
+}
+
 int block_for(const Tuning &t, int64_t n) {
   if (t.block) return t.block;
-  const int ncu = n_cus();
-  int b = 512;
-  while (b > 64 && (int64_t)b * ncu > n) b >>= 1;
-  return b;
+  return n <= (int64_t)n_cus() * 256 ? 256 : 512;
 }
 
 // The grid for n_tiles tiles, one per wave, in blocks of `lanes` lanes: whole
@@ -732,16 +630,7 @@ static TileGrid tile_grid(int64_t n_tiles, int lanes, bool two_of_512) {
   return {full, (unsigned)(full + tail)};
 }
 
-// Two lanes per orbit: without the window test, when asked for
-// (lanes_per_orbit 2) or, by default, while every pair's wave has a SIMD of its
-// own.  200 S6 steps in us, one lane and two: 32768 orbits 238 and 211 (188 and
-// 148 without the tangent); past that two waves share a SIMD, 33000 orbits 234
-// and 333 (187 and 237).
-static bool use_pair(const FwdDesc &d, const Tuning &t) {
-  if (d.filter || d.N <= 0) return false;
-  if (t.lpo) return t.lpo == 2;
-  return d.N <= (int64_t)n_cus() * 4 * 32;
-}
+static bool use_pair(const FwdDesc &d, const Tuning &t) { return !d.filter && two_lanes(t, d.N); }
 
 template <int FORM, bool TAN>
 static hipError_t fwd_dispatch_opl(const FwdDesc &d, const Tuning &t, hipStream_t s) {

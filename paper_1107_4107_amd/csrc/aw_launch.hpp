@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "aw_internal.hpp"
 
 namespace aw {
@@ -15,18 +17,27 @@ struct Tuning {
   int unroll = 1;
   int renorm = 8;
   int pwgs = 0;
-  int lpo = 0;    // lanes per orbit of tangent-free intermediate launches: 0 auto, 1 or 2
+  int lpo = 0;    // lanes per orbit: 0 auto (two_lanes), 1 or 2
 };
 
 int n_cus();  // compute units of the current device
 
-// Lanes per block of the adjoint kernels for n orbits.  A block set in the
-// tuning is used as is.  Automatic: 512 when every CU gets at least one block
-// of 512 (a block holds the 64 KB sine/cosine table, so two blocks share a CU,
-// and it takes two of 512 lanes to fill it at four waves per SIMD); below that
-// the largest of 256 and 128 that still gives every CU a block, else 64, so
-// that small ensembles spread over as much of the chip as they can.  No
-// result depends on the block.
+// Whether n orbits run on two lanes each: when asked for (lanes_per_orbit 2) or,
+// by default, while every pair's wave has a SIMD of its own.  200 S6 steps in us,
+// one lane and two: 32768 orbits 238 and 211 (188 and 148 without the tangent);
+// past that two waves share a SIMD, 33000 orbits 234 and 333 (187 and 237).  The
+// gradient of J, 16384 orbits 464 and 378, 32761 466 and 404, 33000 458 and 594;
+// of L, 16384 679 and 600, 32761 691 and 656, 33000 682 and 988.
+bool two_lanes(const Tuning &t, int64_t n);
+
+// Lanes per block of the adjoint kernels for n lanes in all.  A block set in the
+// tuning is used as is.  Automatic: 256, one wave per SIMD of a CU, while every
+// CU holds at most one such block, else 512 (a block holds the 64 KB sine/cosine
+// table, so two blocks share a CU, and it takes two of 512 lanes to fill it at
+// four waves per SIMD).  Smaller blocks would spread over more CUs but share
+// SIMDs when two land on one CU: the gradient of J for 40000 orbits over 200
+// steps takes 472 us in blocks of 256 and took 780 in blocks of 128, for 257 orbits
+// 511 and 524 in blocks of 64.  No result depends on the block.
 int block_for(const Tuning &t, int64_t n);
 
 inline int block_512(const Tuning &t) { return t.block ? t.block : 512; }
@@ -76,7 +87,27 @@ hipError_t launch_hist_reduce(int64_t N, const HistKeys *keys, uint32_t *bins, c
                               const HistScratch &w, int mode, double norm, uint32_t *counts_out,
                               double *f_out, uint64_t *dropped_out, hipStream_t s, int accumulate = 0);
 
-// Adjoint.
+// Adjoint kernels: `lanes` lanes in blocks of block_for, and the call f(form) with
+// the map form as a compile-time constant.
+template <class D>
+void launch_lanes(void (*kernel)(D), int64_t lanes, const D &d, const Tuning &t, hipStream_t s) {
+  const int tb = block_for(t, lanes);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)((lanes + tb - 1) / tb)), dim3((unsigned)tb), 0, s, d);
+}
+
+template <class Fn>
+hipError_t for_form(int form, Fn &&f) {
+  switch (form) {
+  case 1: f(std::integral_constant<int, 1>{}); break;
+  case 2: f(std::integral_constant<int, 2>{}); break;
+  case 4: f(std::integral_constant<int, 4>{}); break;
+  case 6: f(std::integral_constant<int, 6>{}); break;
+  case 7: f(std::integral_constant<int, 7>{}); break;
+  default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
 hipError_t launch_adj_forward(const AdjDesc &d, int form, const Tuning &t, hipStream_t s);
 hipError_t launch_adj_backward(const AdjDesc &d, int form, const Tuning &t, hipStream_t s);
 hipError_t launch_adj_backward_reversible(const AdjDesc &d, int form, const Tuning &t, hipStream_t s);
