@@ -534,7 +534,8 @@ aw_status upload_tables(StreamScratch &sc, const Layout &l, const BatchTables &b
 // the area at `base`.  timed: record it for aw_timing_read.
 aw_status launch_batched_tables(const BatchTables &b, const Layout &l, char *base, const Tuning &t, int form, bool tan,
                                 hipStream_t s, bool timed) {
-  const int64_t nw = block_512(t) >> 6;
+  // As many blocks as their first four waves, one per SIMD, have tiles for.
+  const int64_t nw = std::min<int64_t>(block_512(t) >> 6, 4);
   const int nwg = (int)std::min<int64_t>(persistent_wgs(form, tan, t), (b.tiles() + nw - 1) / nw);
   auto launch = [&] {
     return launch_fwd_batched((const FwdDesc *)(base + l.descs), (const int64_t *)(base + l.ends),

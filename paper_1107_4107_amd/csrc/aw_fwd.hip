@@ -528,12 +528,17 @@ __global__ __launch_bounds__(512, 2) void k_fwd_pair(FwdDesc, int64_t full_block
   finish_orbits<TAN, 1, WINV>(reread(d), o, n, act, left, xs, ys, zs, k0, k1);
 }
 
-// Persistent batched propagation: every wave takes the next tile of 64 OPL
-// orbits from a device counter until the tiles of all ensembles, the longest
+// Persistent batched propagation: every wave starts on a tile of 64 OPL orbits of
+// its own, the first waves of all blocks before their second ones, and then takes
+// the next tile from a device counter until the tiles of all ensembles, the longest
 // runs first, are done.  descs[e] are sorted by their step counts, and
 // ends[e] is the number of tiles of descs[0..e]; the tile's ensemble is found
 // by bisection.  Waves share nothing but the table: a tile of the longest run
-// keeps one wave and not the whole block from the next tile.
+// keeps one wave and not the whole block from the next tile.  With the first tiles
+// from the counter too the first blocks' waves took them all, two to a SIMD, and
+// every take cost 11 ns on the one counter: 18 slices of up to 39 x 39 orbits over up to
+// 579 steps took 1228 us and take 706, two of up to 300 x 300 over 900 steps of the
+// standard map 83 and 59.
 // Two orbits per lane take about 266 VGPRs; held to 256 (two waves per SIMD
 // instead of one, the spills outside the step loop) the batch runs a fifth
 // faster.
@@ -544,13 +549,9 @@ __global__ __launch_bounds__(512, (TAN || OPL > 1) ? 2 : 4) void k_fwd_persist(c
                                                                                unsigned long long *head) {
   __shared__ double2 s_tab[AW_TAB_N];
   load_sincos_table(s_tab);
-  const int64_t n_tiles = ends[n_descs - 1];
-  for (;;) {
-    unsigned long long t0 = 0;
-    if (__lane_id() == 0) t0 = atomicAdd(head, 1ull);
-    const int64_t t = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(t0 >> 32)) << 32) |
-                                (uint32_t)__builtin_amdgcn_readfirstlane((int)t0));
-    if (t >= n_tiles) break;
+  const int64_t n_tiles = ends[n_descs - 1], n_waves = (int64_t)gridDim.x * (blockDim.x >> 6);
+  int64_t t = (int64_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) * gridDim.x + blockIdx.x;
+  while (t < n_tiles) {
     int32_t lo = 0, hi = n_descs - 1;   // the first e with ends[e] > t
     while (lo < hi) {
       const int32_t mid = (lo + hi) >> 1;
@@ -559,6 +560,11 @@ __global__ __launch_bounds__(512, (TAN || OPL > 1) ? 2 : 4) void k_fwd_persist(c
     }
     const int32_t e = __builtin_amdgcn_readfirstlane(lo);
     run_orbits<FORM, TAN, OPL, 1>(descs[e], t - (e > 0 ? ends[e - 1] : 0), s_tab);
+    if (n_tiles <= n_waves) break;
+    unsigned long long t0 = 0;
+    if (__lane_id() == 0) t0 = atomicAdd(head, 1ull);
+    t = n_waves + (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(t0 >> 32)) << 32) |
+                            (uint32_t)__builtin_amdgcn_readfirstlane((int)t0));
   }
 }
 
