@@ -757,9 +757,12 @@ __global__ __launch_bounds__(ACC_BLOCK) void k_segment_accum(int64_t N, int32_t 
   const int64_t o = ((int64_t)slot0 + q) * TILE_BINS + tid;
   part_counts[o] = c[tid];
   if (have_vals) part_sums[o] = s[tid];
-  // One lane's fence covers the workgroup's stores, which the barrier orders
-  // before it, and its acquire the loads after the next barrier: a fence on
-  // every wave writes the L2 back 16 times.
+  // Every wave waits until its own stores have reached the L2: the barrier waits
+  // for LDS operations only, and the release below for the stores of its own
+  // wave.  Then one lane's release writes the L2 back for the whole workgroup,
+  // and its acquire covers the loads after the next barrier (a fence on every
+  // wave would write the L2 back 16 times).
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (tid == 0) found[0] = __hip_atomic_fetch_add(&tile_done[t], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
