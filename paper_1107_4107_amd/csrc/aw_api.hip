@@ -442,15 +442,13 @@ FwdDesc make_desc(const aw_ensemble &e, const double *ic, const Tuning &t) {
   d.filter = (e.flags & AW_F_WINDOW) ? 1 : 0;
   if (d.filter) {
     const double w = e.window[1] - e.window[0];
-    // 2 p_x = p_u + p_v, 2 p_y = p_u - p_v
-    const double e0x = std::cos(e.window[0]), e0y = std::sin(e.window[0]);
-    const double e1x = std::cos(e.window[1]), e1y = std::sin(e.window[1]);
-    d.c0u = e0x - e0y;
-    d.c0v = -(e0x + e0y);
-    d.c1u = e1y - e1x;
-    d.c1v = e1y + e1x;
-    d.mu2_lo = e.window[2] * std::fabs(e.window[2]);
-    d.mu2_hi = e.window[3] * std::fabs(e.window[3]);
+    d.e0x = std::cos(e.window[0]);
+    d.e0y = std::sin(e.window[0]);
+    d.e1x = std::cos(e.window[1]);
+    d.e1y = std::sin(e.window[1]);
+    // See in_window: what lies on an edge stays on its inner side.
+    d.mu2_lo = e.window[2] * std::fabs(e.window[2]) * (e.window[2] > 0.0 ? 1.0 - 0x1p-48 : 1.0 + 0x1p-48);
+    d.mu2_hi = e.window[3] * std::fabs(e.window[3]) * (e.window[3] > 0.0 ? 1.0 + 0x1p-48 : 1.0 - 0x1p-48);
     d.win_phi = (e.window[0] == -M_PI && e.window[1] == M_PI) ? 0 : (w <= M_PI ? 1 : 2);
     d.win_mu = (e.window[2] == -1.0 && e.window[3] == 1.0) ? 0 : 1;
   }

@@ -133,22 +133,40 @@ __device__ __forceinline__ void vdir_key(double vx, double vy, double vz, double
 constexpr double LN2 = 0x1.62e42fefa39efp-1;
 
 // Is the direction of P inside the closed window phi in [phi_lo, phi_hi],
-// mu = pz/|P| in [mu_lo, mu_hi]?  On the scaled momenta (p_u, p_v, sqrt 2 p_z),
-// whose squares add up to 2 |P|^2.  The phi test uses half-plane (cross
+// mu = pz/|P| in [mu_lo, mu_hi]?  The phi test uses half-plane (cross
 // product) tests against the edge directions e0, e1 instead of atan2: for a
 // window of width w <= pi, phi is inside iff e0 x d >= 0 and d x e1 >= 0; for
-// w > pi, iff d is not strictly inside the complementary sector.  The mu test
-// compares p |p| against mu |mu| times the sum of squares, which needs no
-// square root: the whole test is 10 FP64 instructions where the rotated-back
-// momentum, its norm and their products took about 100.
+// w > pi, iff d is not strictly inside the complementary sector.
+__device__ __forceinline__ bool in_phi(double px, double py, const FwdDesc &d) {
+#pragma clang fp contract(off)
+  if (d.win_phi == 0) return true;
+  const double c0 = d.e0x * py - d.e0y * px;   // e0 x d
+  const double c1 = px * d.e1y - py * d.e1x;   // d x e1
+  return d.win_phi == 1 ? (c0 >= 0.0 && c1 >= 0.0) : !(c0 < 0.0 && c1 < 0.0);
+}
+
+// The initial momentum, as it was given.
+__device__ __forceinline__ bool in_window0(double px, double py, double pz, const FwdDesc &d) {
+#pragma clang fp contract(off)
+  bool ok = in_phi(px, py, d);
+  if (d.win_mu != 0) {
+    const double r = sqrt(px * px + py * py + pz * pz);
+    ok = ok && pz >= d.win[2] * r && pz <= d.win[3] * r;
+  }
+  return ok;
+}
+
+// After a step, on the scaled momenta (p_u, p_v, sqrt 2 p_z), whose squares add
+// up to 2 |P|^2; the phi test takes 2 P.  The mu test compares p |p| against
+// mu |mu| times the sum of squares, which needs no square root: the whole test
+// is 14 FP64 instructions where the rotated-back momentum, its norm and their
+// products took about 100.  The squares of a momentum that lies on an edge, or
+// within the rounding of in_window0, come out up to 17 half-ulps beyond it;
+// the edges' squares are moved out by 32, so that a momentum which does not
+// change stays in.
 __device__ __forceinline__ bool in_window(double pu, double pv, double pz, const FwdDesc &d) {
 #pragma clang fp contract(off)
-  bool ok = true;
-  if (d.win_phi != 0) {
-    const double c0 = __builtin_fma(pu, d.c0u, pv * d.c0v);   // 2 e0 x d
-    const double c1 = __builtin_fma(pu, d.c1u, pv * d.c1v);   // 2 d x e1
-    ok = d.win_phi == 1 ? (c0 >= 0.0 && c1 >= 0.0) : !(c0 < 0.0 && c1 < 0.0);
-  }
+  bool ok = in_phi(pu + pv, pu - pv, d);
   if (d.win_mu != 0) {
     const double r2 = __builtin_fma(pu, pu, __builtin_fma(pv, pv, pz * pz));
     const double q = pz * fabs(pz);
@@ -337,8 +355,8 @@ __device__ __forceinline__ void start_orbit(const FwdDesc &d, int64_t m, Orbit &
     } else {
       o.dx = o.dy = o.dz = o.dpx = o.dpy = o.dpz = 0.0;
     }
+    if (FILT) left = !in_window0(s[3], s[4], s[5], d);
     to_node(o);
-    if (FILT) left = !in_window(o.px, o.py, o.pz, d);
   } else {
     const double *c = d.carry;
     const int64_t N = d.N;

@@ -87,9 +87,9 @@ struct FwdDesc {
   // fixed-energy (SPHERE) initial conditions and the stay-in-window test
   double energy;
   double win[4];          // phi_lo, phi_hi, mu_lo, mu_hi
-  double c0u, c0v;        // 2 e0 x d = c0u p_u + c0v p_v, e0 = (cos phi_lo, sin phi_lo)
-  double c1u, c1v;        // 2 d x e1 = c1u p_u + c1v p_v, e1 = (cos phi_hi, sin phi_hi)
-  double mu2_lo, mu2_hi;  // mu |mu| of the window's mu_lo, mu_hi
+  double e0x, e0y;        // (cos phi_lo, sin phi_lo)
+  double e1x, e1y;        // (cos phi_hi, sin phi_hi)
+  double mu2_lo, mu2_hi;  // mu |mu| of the window's mu_lo, mu_hi, each moved out by 2^-48 of itself
   int32_t win_phi;        // 0: every phi; 1: sector of width <= pi; 2: complement of a sector < pi
   int32_t win_mu;         // 0: every mu; 1: test mu_lo <= pz/|P| <= mu_hi
   int32_t filter;         // test the window after every step
