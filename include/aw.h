@@ -166,7 +166,11 @@ typedef struct {
  * AW_F_WINDOW and outside the batched launch an orbit can run on two lanes (u,
  * p_u and their tangent on one, v's on the other, in the rotated frame); 0 does
  * so while every wave then has a SIMD of its own (at most 32 x 4 x CUs orbits).
- * Results are bitwise the same either way. */
+ * The propagation's two-lane kernel has one shape: 0 keeps one lane per orbit
+ * where a block, orbits_per_lane 2 or unroll 2 is asked for, except in
+ * tangent-free launches that end before n_steps (aw_map_ensemble_steps) or bin
+ * time windows (aw_window_density), whose choice depends on the number of orbits
+ * alone; 2 ignores those three fields.  Results are bitwise the same either way. */
 typedef struct {
   int32_t block;
   int32_t orbits_per_lane;

@@ -383,7 +383,7 @@ template <bool EPS0>
 hipError_t launch_bwd(const AdjDesc &d, bool rev, int form, const Tuning &t, hipStream_t s) {
   return for_form(form, [&](auto f) {
     constexpr int F = decltype(f)::value;
-    const bool two = two_lanes(t, d.N);
+    const bool two = two_lanes(t, d.N, n_cus());
     if (two && rev) launch_lanes(k_adj_bwd_rev<F, EPS0, TwoLanes>, 2 * d.N, d, t, s);
     else if (two) launch_lanes(k_adj_bwd<F, EPS0, TwoLanes>, 2 * d.N, d, t, s);
     else if (rev) launch_lanes(k_adj_bwd_rev<F, EPS0, OneLane>, d.N, d, t, s);
@@ -397,7 +397,7 @@ hipError_t launch_adj_forward(const AdjDesc &d, int form, const Tuning &t, hipSt
   if (d.N <= 0) return hipSuccess;
   return for_form(form, [&](auto f) {
     constexpr int F = decltype(f)::value;
-    if (two_lanes(t, d.N)) launch_lanes(k_adj_fwd<F, TwoLanes>, 2 * d.N, d, t, s);
+    if (two_lanes(t, d.N, n_cus())) launch_lanes(k_adj_fwd<F, TwoLanes>, 2 * d.N, d, t, s);
     else launch_lanes(k_adj_fwd<F, OneLane>, d.N, d, t, s);
   });
 }

@@ -563,7 +563,7 @@ template <bool EPS0>
 hipError_t launch_bwd(const FtleDesc &d, bool rev, int form, const Tuning &t, hipStream_t s) {
   return for_form(form, [&](auto f) {
     constexpr int F = decltype(f)::value;
-    const bool two = two_lanes(t, d.N);
+    const bool two = two_lanes(t, d.N, n_cus());
     if (two && rev) launch_lanes(k_ftle_bwd_rev<F, EPS0, TwoLanes>, 2 * d.N, d, t, s);
     else if (two) launch_lanes(k_ftle_bwd<F, EPS0, TwoLanes>, 2 * d.N, d, t, s);
     else if (rev) launch_lanes(k_ftle_bwd_rev<F, EPS0, OneLane>, d.N, d, t, s);
@@ -577,7 +577,7 @@ hipError_t launch_ftle_forward(const FtleDesc &d, int form, const Tuning &t, hip
   if (d.N <= 0) return hipSuccess;
   return for_form(form, [&](auto f) {
     constexpr int F = decltype(f)::value;
-    if (two_lanes(t, d.N)) launch_lanes(k_ftle_fwd<F, TwoLanes>, 2 * d.N, d, t, s);
+    if (two_lanes(t, d.N, n_cus())) launch_lanes(k_ftle_fwd<F, TwoLanes>, 2 * d.N, d, t, s);
     else launch_lanes(k_ftle_fwd<F, OneLane>, d.N, d, t, s);
   });
 }

@@ -626,10 +626,6 @@ int n_cus() {
   return ncu;
 }
 
-bool two_lanes(const Tuning &t, int64_t n) {
-  return n > 0 && (t.lpo ? t.lpo == 2 : n <= (int64_t)n_cus() * 4 * 32);
-}
-
 int block_for(const Tuning &t, int64_t n) {
   if (t.block) return t.block;
   return n <= (int64_t)n_cus() * 256 ? 256 : 512;
@@ -654,12 +650,14 @@ static TileGrid tile_grid(int64_t n_tiles, int lanes, bool two_of_512) {
   return {full, (unsigned)(full + tail)};
 }
 
-static bool use_pair(const FwdDesc &d, const Tuning &t) { return !d.filter && two_lanes(t, d.N); }
+static bool use_pair(const FwdDesc &d, const Tuning &t, bool tan) {
+  return !d.filter && fwd_two_lanes(t, d.N, !tan && (d.window_v || d.k_end < d.T), n_cus());
+}
 
 template <int FORM, bool TAN>
 static hipError_t fwd_dispatch_opl(const FwdDesc &d, const Tuning &t, hipStream_t s) {
   if (d.N <= 0) return hipSuccess;
-  if (use_pair(d, t)) {
+  if (use_pair(d, t, TAN)) {
     const TileGrid g = tile_grid((d.N + 31) / 32, 512, false);
     if (d.window_v) hipLaunchKernelGGL((k_fwd_pair<FORM, TAN, true>), dim3(g.blocks), dim3(512), 0, s, d, g.full_blocks);
     else hipLaunchKernelGGL((k_fwd_pair<FORM, TAN, false>), dim3(g.blocks), dim3(512), 0, s, d, g.full_blocks);

@@ -17,7 +17,7 @@ struct Tuning {
   int unroll = 1;
   int renorm = 8;
   int pwgs = 0;
-  int lpo = 0;    // lanes per orbit: 0 auto (two_lanes), 1 or 2
+  int lpo = 0;    // lanes per orbit: 0 auto (two_lanes, fwd_two_lanes), 1 or 2
 };
 
 int n_cus();  // compute units of the current device
@@ -28,7 +28,19 @@ int n_cus();  // compute units of the current device
 // past that two waves share a SIMD, 33000 orbits 234 and 333 (187 and 237).  The
 // gradient of J, 16384 orbits 464 and 378, 32761 466 and 404, 33000 458 and 594;
 // of L, 16384 679 and 600, 32761 691 and 656, 33000 682 and 988.
-bool two_lanes(const Tuning &t, int64_t n);
+inline bool two_lanes(const Tuning &t, int64_t n, int64_t cus) {
+  return n > 0 && (t.lpo ? t.lpo == 2 : n <= cus * 4 * 32);
+}
+
+// The same for the propagation without the window test.  The pair kernel has one
+// shape, so by default it does not take the place of a block, a number of orbits
+// per lane or an unrolling that the caller asked for -- but for part, a
+// tangent-free launch that ends before n_steps or bins a time window, whose
+// automatic choice has always been made from n alone.
+inline bool fwd_two_lanes(const Tuning &t, int64_t n, bool part, int64_t cus) {
+  const bool shaped = t.block != 0 || t.opl != 1 || t.unroll != 1;
+  return two_lanes(t, n, cus) && (t.lpo == 2 || part || !shaped);
+}
 
 // Lanes per block of the adjoint kernels for n lanes in all.  A block set in the
 // tuning is used as is.  Automatic: 256, one wave per SIMD of a CU, while every
