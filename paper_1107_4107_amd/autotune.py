@@ -4,10 +4,11 @@ Times short probes of an ensemble (the same descriptor with a reduced number
 of steps) under every candidate (block, orbits per lane, unroll) with the
 library's HIP-event kernel timing, keeps the fastest, and caches the choice in
 a JSON file keyed by device, library build, single launch or batch, map form,
-tangent flag and ensemble-size bucket.  A batch runs as one persistent launch,
-which takes blocks of at most 256 lanes and does not unroll, so a batch is
-tuned over block and orbits per lane only.  Results are bitwise independent
-of the choice, so tuning never changes numbers, only speed.
+tangent flag and ensemble-size bucket.  Block 0 is the library's own choice:
+for a single ensemble of few orbits it runs two lanes per orbit, which no
+explicit block does.  A batch runs as one persistent launch, which does not
+unroll, so a batch is tuned over block and orbits per lane only.  Results are
+bitwise independent of the choice, so tuning never changes numbers, only speed.
 """
 from __future__ import annotations
 
@@ -24,11 +25,10 @@ import torch
 from . import Ensemble, Tuning, _abi, map_ensembles, timing_enable, timing_read
 
 DEFAULT_CACHE = os.path.join(os.path.expanduser("~"), ".cache", "arnoldweb_tuning.json")
-CANDIDATES: Tuple[Tuple[int, int, int], ...] = tuple(
+CANDIDATES: Tuple[Tuple[int, int, int], ...] = ((0, 1, 1),) + tuple(
     (b, o, u) for b in (64, 128, 256, 512) for o in (1, 2) for u in (1, 2))
-# The persistent launch of a batch: blocks above 256 lanes run as 256, and the
-# step loop is not unrolled.
-BATCH_CANDIDATES: Tuple[Tuple[int, int, int], ...] = tuple((b, o, 1) for b in (64, 128, 256) for o in (1, 2))
+# The persistent launch of a batch does not unroll the step loop; its block 0 is 512.
+BATCH_CANDIDATES: Tuple[Tuple[int, int, int], ...] = tuple((b, o, 1) for b in (64, 128, 256, 512) for o in (1, 2))
 
 _LIB_ID = None
 

@@ -46,3 +46,12 @@ int main() {
                    check=True, capture_output=True)
     out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
     assert out.returncode == 0 and out.stdout.strip() == "ok", out.stdout
+
+
+def test_the_autotuner_can_choose_the_default():
+    """The default shape is among the candidates: the automatic block for a
+    single ensemble, the block it stands for (512) for a batch."""
+    from paper_1107_4107_amd import Tuning, autotune
+    t = Tuning()
+    assert (t.block, t.orbits_per_lane, t.unroll) in autotune.CANDIDATES
+    assert (512, t.orbits_per_lane, 1) in autotune.BATCH_CANDIDATES
