@@ -336,12 +336,21 @@ def grad_workspace_bytes(ens: Ensemble, ckpt_every: int, reversible: bool = Fals
 
 
 # An adjoint call that allocates its own workspace gives it room for the step
-# states of every segment, so that nothing is recomputed, up to this size (1.4%
-# of the card's memory); beyond it the last segments that fit are kept.
+# states of every segment, so that nothing is recomputed, up to this size in all
+# (1.4% of the card's memory) and a quarter of the memory that is free; beyond
+# it the last segments that fit are kept.  The keep_bytes argument of the calls
+# replaces both limits.
 KEEP_BYTES = 4 << 30
+# Room below this is taken without a look at the free memory.
+KEEP_UNASKED_BYTES = 64 << 20
 
 
-def _adjoint_workspace(ens: Ensemble, ckpt_every: int, need: int, rows: int, reversible: bool, dev) -> torch.Tensor:
+def _free_bytes(dev) -> int:
+    return torch.cuda.mem_get_info(dev)[0]
+
+
+def _adjoint_workspace(ens: Ensemble, ckpt_every: int, need: int, rows: int, reversible: bool, dev,
+                       keep_bytes: Optional[int] = None) -> torch.Tensor:
     """A workspace of at least `need` bytes; rows: doubles per orbit and state."""
     N, T = ens.size, int(ens.n_steps)
     ck = min(int(ckpt_every), T)
@@ -350,7 +359,11 @@ def _adjoint_workspace(ens: Ensemble, ckpt_every: int, need: int, rows: int, rev
     if not reversible and n_seg > 1 and N > 0:
         exps = 2 * N * (T // 8) if rows == 12 else 0
         seg = need - exps - 8 * rows * N * (n_seg + 1)      # the step states of one segment
-        want += seg * max(0, min(n_seg - 1, (KEEP_BYTES - need) // seg))
+        room = KEEP_BYTES - need if keep_bytes is None else int(keep_bytes)
+        extra = seg * max(0, min(n_seg - 1, room // seg))
+        if keep_bytes is None and extra > KEEP_UNASKED_BYTES and not torch.cuda.is_current_stream_capturing():
+            extra = min(extra, seg * max(0, (_free_bytes(dev) // 4 - need) // seg))
+        want += extra
     if want > need:
         try:
             return torch.empty((want,), dtype=torch.uint8, device=dev)
@@ -361,10 +374,16 @@ def _adjoint_workspace(ens: Ensemble, ckpt_every: int, need: int, rows: int, rev
 
 def indicator_grad(ens: Ensemble, ic: torch.Tensor, grad_J: Optional[torch.Tensor] = None,
                    ckpt_every: int = 100, tuning: Optional[Tuning] = None,
-                   workspace: Optional[torch.Tensor] = None, reversible: bool = False):
+                   workspace: Optional[torch.Tensor] = None, reversible: bool = False,
+                   keep_bytes: Optional[int] = None):
     """Adjoint gradient of J.  Returns (J[N], grad_ic[6, N], grad_eps[N]).
     reversible=True sweeps each segment back by inverting the steps instead
-    of recomputing and storing them (aw_indicator_grad_reversible)."""
+    of recomputing and storing them (aw_indicator_grad_reversible).
+    Without a workspace the call allocates grad_workspace_bytes() and, to save
+    the recompute, up to keep_bytes more for the step states of further
+    segments (default: as many as fit KEEP_BYTES in all and a quarter of the
+    free memory; 0: none, ckpt_every alone sets the memory).  The result does
+    not depend on it."""
     if ens.ic_kind != "explicit":
         raise ValueError("indicator_grad needs an explicit ensemble")
     N = ens.size
@@ -373,7 +392,7 @@ def indicator_grad(ens: Ensemble, ic: torch.Tensor, grad_J: Optional[torch.Tenso
         _dev_f64(grad_J, (N,), "grad_J")
     nb = grad_workspace_bytes(ens, ckpt_every, reversible)
     if workspace is None or workspace.numel() * workspace.element_size() < nb:
-        workspace = _adjoint_workspace(ens, ckpt_every, nb, 6, reversible, ic.device)
+        workspace = _adjoint_workspace(ens, ckpt_every, nb, 6, reversible, ic.device, keep_bytes)
     J = torch.empty((N,), dtype=torch.float64, device=ic.device)
     gic = torch.empty((6, N), dtype=torch.float64, device=ic.device)
     geps = torch.empty((N,), dtype=torch.float64, device=ic.device)
@@ -386,11 +405,12 @@ def indicator_grad(ens: Ensemble, ic: torch.Tensor, grad_J: Optional[torch.Tenso
 class IndicatorJ(torch.autograd.Function):
     """J_n = (1/T) sum_k |P_k - P_0|^2 per orbit, differentiable in the initial
     state ic[N, 6] and in eps (a 0-d float64 tensor); the backward pass runs the
-    checkpointed adjoint kernels (reversible=True: the store-free sweep)."""
+    checkpointed adjoint kernels (reversible=True: the store-free sweep) in a
+    workspace of its own (keep_bytes as for indicator_grad)."""
 
     @staticmethod
     def forward(ctx, ic, eps, n_steps: int, h: float = H_PAPER, map_form: str = "s6", ckpt_every: int = 100,
-                reversible: bool = False):
+                reversible: bool = False, keep_bytes: Optional[int] = None):
         if ic.dim() != 2 or ic.shape[1] != 6:
             raise ValueError("ic must be [N, 6]")
         soa = ic.detach().t().contiguous()
@@ -401,6 +421,7 @@ class IndicatorJ(torch.autograd.Function):
         ctx.ens = e
         ctx.ckpt = ckpt_every
         ctx.reversible = reversible
+        ctx.keep_bytes = keep_bytes
         ctx.eps_shape = eps.shape if isinstance(eps, torch.Tensor) else None
         return res.orbit_out[OUT_J].clone()
 
@@ -408,11 +429,11 @@ class IndicatorJ(torch.autograd.Function):
     def backward(ctx, gJ):
         (soa,) = ctx.saved_tensors
         _, gic, geps = indicator_grad(ctx.ens, soa, gJ.contiguous().to(torch.float64), ctx.ckpt,
-                                      reversible=ctx.reversible)
+                                      reversible=ctx.reversible, keep_bytes=ctx.keep_bytes)
         g_eps = geps.sum()
         if ctx.eps_shape is not None:
             g_eps = g_eps.reshape(ctx.eps_shape)
-        return gic.t().contiguous(), g_eps, None, None, None, None, None
+        return gic.t().contiguous(), g_eps, None, None, None, None, None, None
 
 
 def ftle_grad_workspace_bytes(ens: Ensemble, ckpt_every: int, reversible: bool = False) -> int:
@@ -424,11 +445,13 @@ def ftle_grad_workspace_bytes(ens: Ensemble, ckpt_every: int, reversible: bool =
 
 def ftle_grad(ens: Ensemble, ic: torch.Tensor, w0: Optional[torch.Tensor] = None,
               grad_L: Optional[torch.Tensor] = None, ckpt_every: int = 100, tuning: Optional[Tuning] = None,
-              workspace: Optional[torch.Tensor] = None, reversible: bool = False):
+              workspace: Optional[torch.Tensor] = None, reversible: bool = False,
+              keep_bytes: Optional[int] = None):
     """Second-order adjoint gradient of the tangent growth L = ln(|w_T|/|w_0|).
     w0 defaults to the ensemble's seeded tangent start (the one map_ensemble
     uses).  reversible=True sweeps each segment back by inverting the steps
-    (aw_ftle_grad_reversible).  Returns (L[N], grad_ic[6, N], grad_eps[N])."""
+    (aw_ftle_grad_reversible).  keep_bytes: as for indicator_grad, beyond
+    ftle_grad_workspace_bytes().  Returns (L[N], grad_ic[6, N], grad_eps[N])."""
     if ens.ic_kind != "explicit":
         raise ValueError("ftle_grad needs an explicit ensemble")
     N = ens.size
@@ -440,7 +463,7 @@ def ftle_grad(ens: Ensemble, ic: torch.Tensor, w0: Optional[torch.Tensor] = None
         _dev_f64(grad_L, (N,), "grad_L")
     nb = ftle_grad_workspace_bytes(ens, ckpt_every, reversible)
     if workspace is None or workspace.numel() * workspace.element_size() < nb:
-        workspace = _adjoint_workspace(ens, ckpt_every, nb, 12, reversible, ic.device)
+        workspace = _adjoint_workspace(ens, ckpt_every, nb, 12, reversible, ic.device, keep_bytes)
     L = torch.empty((N,), dtype=torch.float64, device=ic.device)
     gic = torch.empty((6, N), dtype=torch.float64, device=ic.device)
     geps = torch.empty((N,), dtype=torch.float64, device=ic.device)
@@ -455,11 +478,12 @@ class IndicatorL(torch.autograd.Function):
     lambda = L/(T h) and chi = L/ln(1 + T h)), from the seeded tangent start,
     differentiable in the initial state ic[N, 6] and in eps (a 0-d float64
     tensor); the backward pass runs the second-order adjoint kernels
-    (reversible=True: the store-free sweep)."""
+    (reversible=True: the store-free sweep) in a workspace of its own (keep_bytes
+    as for indicator_grad)."""
 
     @staticmethod
     def forward(ctx, ic, eps, n_steps: int, h: float = H_PAPER, map_form: str = "s6", ckpt_every: int = 100,
-                seed_tangent: int = 0, reversible: bool = False):
+                seed_tangent: int = 0, reversible: bool = False, keep_bytes: Optional[int] = None):
         if ic.dim() != 2 or ic.shape[1] != 6:
             raise ValueError("ic must be [N, 6]")
         soa = ic.detach().t().contiguous()
@@ -470,6 +494,7 @@ class IndicatorL(torch.autograd.Function):
         ctx.ens = e
         ctx.ckpt = ckpt_every
         ctx.reversible = reversible
+        ctx.keep_bytes = keep_bytes
         ctx.eps_shape = eps.shape if isinstance(eps, torch.Tensor) else None
         return res.orbit_out[OUT_L].clone()
 
@@ -477,11 +502,11 @@ class IndicatorL(torch.autograd.Function):
     def backward(ctx, gL):
         (soa,) = ctx.saved_tensors
         _, gic, geps = ftle_grad(ctx.ens, soa, grad_L=gL.contiguous().to(torch.float64), ckpt_every=ctx.ckpt,
-                                 reversible=ctx.reversible)
+                                 reversible=ctx.reversible, keep_bytes=ctx.keep_bytes)
         g_eps = geps.sum()
         if ctx.eps_shape is not None:
             g_eps = g_eps.reshape(ctx.eps_shape)
-        return gic.t().contiguous(), g_eps, None, None, None, None, None, None
+        return gic.t().contiguous(), g_eps, None, None, None, None, None, None, None
 
 
 class Graph:
