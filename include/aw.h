@@ -447,10 +447,11 @@ void aw_graph_destroy(aw_graph *g);
 aw_status aw_timing_enable(int32_t on);
 aw_status aw_timing_read(double *ms, int64_t *launches);
 
-/* FP64 operations of a map step in the rotated frame, for the roofline: counts
- * of fma, mul and add/sub (per orbit-step, excluding the per-orbit
- * prologue/epilogue); flops = 2 fma + mul + add.  The count of the unscaled
- * form; the kernels' scaled units take fewer operations for the same step. */
+/* FP64 operations credited to a map step: counts of fma, mul and add/sub (per
+ * orbit-step, excluding the per-orbit prologue/epilogue); flops = 2 fma + mul +
+ * add.  A fixed unit for comparing kernels, the count of the step in the
+ * unscaled rotated frame; the kernels' scaled units take fewer operations for
+ * the same step, so it is no measure of how busy the FP64 units are. */
 aw_status aw_step_op_counts(int32_t map_form, int32_t tangent, int64_t *fma, int64_t *mul,
                             int64_t *add);
 

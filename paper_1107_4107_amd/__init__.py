@@ -554,8 +554,8 @@ def timing_read():
 
 
 def step_op_counts(map_form: str = "s6", tangent: bool = True):
-    """FP64 (fma, mul, add) operations of a map step, the unit of the roofline
-    (the unscaled rotated form; the kernels take fewer)."""
+    """FP64 (fma, mul, add) operations credited to a map step: a fixed unit (the
+    unscaled rotated form), not what the kernels execute, which is fewer."""
     f, m, a = ctypes.c_int64(), ctypes.c_int64(), ctypes.c_int64()
     _abi.check(_lib().aw_step_op_counts(FORMS[map_form], int(tangent), ctypes.byref(f), ctypes.byref(m),
                                         ctypes.byref(a)))

@@ -742,8 +742,8 @@ hipError_t launch_zero_u32(uint32_t *p, int32_t n, hipStream_t s) {
   return hipGetLastError();
 }
 
-// FP64 operations per map step in the unscaled rotated frame, the unit of the
-// roofline (amortised renormalisation excluded): a sincos takes 8 FMA, 4 MUL
+// FP64 operations per map step in the unscaled rotated frame, a fixed unit of
+// work (amortised renormalisation excluded): a sincos takes 8 FMA, 4 MUL
 // and 1 ADD, the z factors 9, 3 and 1, the rest of a kick 3, 2 and 1 and with
 // the tangent 8 FMA and 6 MUL more; a drift 3 FMA, 6 with the tangent; the J
 // accumulator 3 FMA and 4 ADD.  kick_node and drift_node take fewer.
