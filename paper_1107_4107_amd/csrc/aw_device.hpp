@@ -67,7 +67,7 @@ __device__ __forceinline__ double flip(double v, uint32_t sgn) {
 // shears,
 //   c1 = C - t S,  s = S + w c1,  c = c1 - t s,
 // t = tan(r pi/4096) and w = sin(r pi/2048), one coefficient each beyond the
-// leading one.  7 FMA, 3 MUL, 3 ADD in place of the radian form's 8, 4 and 1
+// leading one.  5 FMA, 3 MUL, 3 ADD in place of the radian form's 8, 4 and 1
 // plus the products that a doubled angle needed, and no reduction constants.
 // Error over random arguments: sin at most 1.12e-16 (rms 3.8e-17), cos 1.66e-16
 // (4.8e-17); the radian form's are 1.63e-16 (4.3e-17) and 1.64e-16 (4.6e-17).
@@ -89,16 +89,25 @@ __device__ __forceinline__ uint32_t node_offset(double t) {
   return a;
 }
 
-// The table entry e turned by r nodes, |r| <= 1/2.
-__device__ __forceinline__ NodeSC turn_node(double2 e, double r) {
-  const double u = r * r;
-  const double w = r * __builtin_fma(AW_NODE_W[1], u, AW_NODE_W[0]);
-  const double t = r * __builtin_fma(AW_NODE_T[1], u, AW_NODE_T[0]);
-  const double c1 = __builtin_fma(-t, e.x, e.y);
-  NodeSC o;
-  o.s = __builtin_fma(w, c1, e.x);
-  o.c = __builtin_fma(-t, o.s, c1);
-  return o;
+// The table entries e turned by rem(k) nodes, at most 1/2: remainders and
+// coefficients, then the shears of all angles in step.
+template <int K, class Rem>
+__device__ __forceinline__ void turn_nodes(const double2 (&e)[K], Rem &&rem, NodeSC (&o)[K]) {
+  double r[K], w[K], t[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    r[k] = rem(k);
+    const double u = r[k] * r[k];
+    w[k] = r[k] * __builtin_fma(AW_NODE_W[1], u, AW_NODE_W[0]);
+    t[k] = r[k] * __builtin_fma(AW_NODE_T[1], u, AW_NODE_T[0]);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int k = 0; k < K; ++k) o[k].c = __builtin_fma(-t[k], e[k].x, e[k].y);
+#pragma unroll
+  for (int k = 0; k < K; ++k) o[k].s = __builtin_fma(w[k], o[k].c, e[k].x);
+#pragma unroll
+  for (int k = 0; k < K; ++k) o[k].c = __builtin_fma(-t[k], o[k].s, o[k].c);
 }
 
 // The sines and cosines of K angles, in three phases that the instruction
@@ -114,7 +123,7 @@ __device__ __forceinline__ NodeSC turn_node(double2 e, double r) {
 // the tangent).  Without the tangent the padding costs as much as it gains.
 template <int K, bool ALIGN = false>
 __device__ __forceinline__ void sincos_nodes(const double (&a)[K], NodeSC (&o)[K], const double2 *__restrict__ tab) {
-  double m[K], r[K], w[K], t[K];
+  double m[K];
   double2 e[K];
 #pragma unroll
   for (int k = 0; k < K; ++k) m[k] = a[k] + AW_ROUND_MAGIC;
@@ -122,20 +131,7 @@ __device__ __forceinline__ void sincos_nodes(const double (&a)[K], NodeSC (&o)[K
   for (int k = 0; k < K; ++k) e[k] = *(const double2 *)((const char *)tab + node_offset(m[k]));
   __builtin_amdgcn_sched_barrier(0);
   if (ALIGN) asm volatile(".p2align 3");
-#pragma unroll
-  for (int k = 0; k < K; ++k) {
-    r[k] = a[k] - (m[k] - AW_ROUND_MAGIC);
-    const double u = r[k] * r[k];
-    w[k] = r[k] * __builtin_fma(AW_NODE_W[1], u, AW_NODE_W[0]);
-    t[k] = r[k] * __builtin_fma(AW_NODE_T[1], u, AW_NODE_T[0]);
-  }
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int k = 0; k < K; ++k) o[k].c = __builtin_fma(-t[k], e[k].x, e[k].y);
-#pragma unroll
-  for (int k = 0; k < K; ++k) o[k].s = __builtin_fma(w[k], o[k].c, e[k].x);
-#pragma unroll
-  for (int k = 0; k < K; ++k) o[k].c = __builtin_fma(-t[k], o[k].s, o[k].c);
+  turn_nodes<K>(e, [&](int k) { return a[k] - (m[k] - AW_ROUND_MAGIC); }, o);
 }
 
 // x times a constant held in two parts, rounded once (to within 2^-100).

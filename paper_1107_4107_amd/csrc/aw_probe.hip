@@ -51,11 +51,11 @@ __global__ __launch_bounds__(BLOCK) void k_fma_chains(double m, double c, int64_
   }
 }
 
-// The step loops' table lookup and rotation for an argument in radians (a
-// two-part reduction by pi/2048 in front; the kernels' own angles are in
-// nodes), cos x sin x and cos^2 x from the doubled angle as the kick forms its
-// z factors, and the polynomial form of the initial conditions, one argument
-// per lane; and the kernels' node-unit form itself.
+// The step loops' rotation of a table entry (turn_nodes) behind a reduction that
+// is this probe's own: arguments in radians, a two-part reduction by pi/2048 in
+// front, and from the doubled angle cos x sin x and cos^2 x; the polynomial form
+// of the initial conditions, one argument per lane; and the step loops' own
+// reduction and rotation of K angles in nodes, as they call it.
 __device__ __forceinline__ double radian_reduce(double x, uint32_t& lo) {
   const double m = __builtin_fma(x, AW_NODES_PER_RAD[0], AW_ROUND_MAGIC);
   const double q = m - AW_ROUND_MAGIC;
@@ -74,15 +74,19 @@ __global__ __launch_bounds__(BLOCK) void k_sincos(const double* __restrict__ x, 
   if (form == 0) {
     uint32_t lo;
     const double r = radian_reduce(x[i], lo);
-    const aw::NodeSC v = aw::turn_node(tab[lo & (AW_TAB_N - 1)], r * AW_NODES_PER_RAD[0]);
-    s[i] = v.s;
-    c[i] = v.c;
+    const double2 e[1] = {tab[lo & (AW_TAB_N - 1)]};
+    aw::NodeSC v[1];
+    aw::turn_nodes<1>(e, [&](int) { return r * AW_NODES_PER_RAD[0]; }, v);
+    s[i] = v[0].s;
+    c[i] = v[0].c;
   } else if (form == 2) {
     uint32_t lo;
     const double r = radian_reduce(x[i], lo);
-    const aw::NodeSC v = aw::turn_node(tab[(2 * lo) & (AW_TAB_N - 1)], (r + r) * AW_NODES_PER_RAD[0]);
-    s[i] = 0.5 * v.s;
-    c[i] = __builtin_fma(0.5, v.c, 0.5);
+    const double2 e[1] = {tab[(2 * lo) & (AW_TAB_N - 1)]};
+    aw::NodeSC v[1];
+    aw::turn_nodes<1>(e, [&](int) { return (r + r) * AW_NODES_PER_RAD[0]; }, v);
+    s[i] = 0.5 * v[0].s;
+    c[i] = __builtin_fma(0.5, v[0].c, 0.5);
   } else {
     double sv, cv;
     aw::sincos_full(x[i], sv, cv);
@@ -91,17 +95,26 @@ __global__ __launch_bounds__(BLOCK) void k_sincos(const double* __restrict__ x, 
   }
 }
 
+// K arguments per lane, K lane to K lane + K - 1; past the end a lane repeats the
+// last one, never stored.
+template <int K, bool ALIGN>
 __global__ __launch_bounds__(BLOCK) void k_sincos_node(const double* __restrict__ a, double* __restrict__ s,
                                                        double* __restrict__ c, int64_t n) {
   __shared__ double2 tab[AW_TAB_N];
   aw::load_sincos_table(tab);
-  const int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
+  const int64_t i = ((int64_t)blockIdx.x * BLOCK + threadIdx.x) * K;
   if (i >= n) return;
-  const double x[1] = {a[i]};
-  aw::NodeSC r[1];
-  aw::sincos_nodes<1>(x, r, tab);
-  s[i] = r[0].s;
-  c[i] = r[0].c;
+  double x[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) x[k] = a[i + k < n ? i + k : n - 1];
+  aw::NodeSC r[K];
+  aw::sincos_nodes<K, ALIGN>(x, r, tab);
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    if (i + k >= n) continue;
+    s[i + k] = r[k].s;
+    c[i + k] = r[k].c;
+  }
 }
 
 int fail(hipError_t e, const char* what) {
@@ -177,12 +190,11 @@ extern "C" int awp_fma_peak(int32_t waves_per_simd, int64_t trips, double* out) 
 }
 
 // Writes s_dev[i], c_dev[i] = sin, cos of x_dev[i] (device arrays of n
-// doubles) as the kernels compute them: form 0 = the table and rotation of the
-// step loops, 1 = the polynomial routine of the initial conditions and
-// the energy; form 2 writes the kick's z factors instead, s = cos x sin x and
-// c = cos^2 x, from the table at the doubled angle.  Enqueued on `stream`
-// (NULL = default).  Returns 0, 1 on a HIP error (printed), 2 on bad
-// arguments.
+// doubles): form 0 = the step loops' table and rotation behind the probe's own
+// reduction in radians, 1 = the polynomial routine of the initial conditions and
+// the energy; form 2 writes s = cos x sin x and c = cos^2 x, from the same table
+// and rotation at the doubled angle.  Enqueued on `stream` (NULL = default).
+// Returns 0, 1 on a HIP error (printed), 2 on bad arguments.
 extern "C" int awp_sincos(const double* x_dev, double* s_dev, double* c_dev, int64_t n, int32_t form,
                           void* stream) {
   if (n < 0 || form < 0 || form > 2) return 2;
@@ -196,15 +208,29 @@ extern "C" int awp_sincos(const double* x_dev, double* s_dev, double* c_dev, int
   return e == hipSuccess ? 0 : fail(e, "sincos probe");
 }
 
-// The node-unit sine and cosine of the propagation kernels: s_dev[i],
-// c_dev[i] = sin, cos of a_dev[i] pi/2048.  Arguments and results as awp_sincos.
-extern "C" int awp_sincos_node(const double* a_dev, double* s_dev, double* c_dev, int64_t n, void* stream) {
-  if (n < 0) return 2;
+// The node-unit sine and cosine of the propagation and adjoint kernels, the
+// function their kicks call: s_dev[i], c_dev[i] = sin, cos of a_dev[i] pi/2048.
+// `angles` at a time and aligned as in a kick of one lane per orbit (3, with the
+// tangent aligned), of two lanes (2, aligned), or one at a time.  Arguments and
+// results as awp_sincos.
+extern "C" int awp_sincos_nodes(const double* a_dev, double* s_dev, double* c_dev, int64_t n, int32_t angles,
+                                int32_t aligned, void* stream) {
+  if (n < 0 || angles < 1 || angles > 3 || (aligned ? angles == 1 : angles == 2)) return 2;
   if (n == 0) return 0;
   if (!a_dev || !s_dev || !c_dev) return 2;
-  const int64_t blocks = (n + BLOCK - 1) / BLOCK;
+  const int64_t lanes = (n + angles - 1) / angles, blocks = (lanes + BLOCK - 1) / BLOCK;
   if (blocks > INT32_MAX) return 2;
-  hipLaunchKernelGGL(k_sincos_node, dim3((unsigned)blocks), dim3(BLOCK), 0, (hipStream_t)stream, a_dev, s_dev, c_dev, n);
+  const dim3 grid((unsigned)blocks), block(BLOCK);
+  const hipStream_t st = (hipStream_t)stream;
+  if (angles == 1) hipLaunchKernelGGL((k_sincos_node<1, false>), grid, block, 0, st, a_dev, s_dev, c_dev, n);
+  else if (angles == 2) hipLaunchKernelGGL((k_sincos_node<2, true>), grid, block, 0, st, a_dev, s_dev, c_dev, n);
+  else if (aligned) hipLaunchKernelGGL((k_sincos_node<3, true>), grid, block, 0, st, a_dev, s_dev, c_dev, n);
+  else hipLaunchKernelGGL((k_sincos_node<3, false>), grid, block, 0, st, a_dev, s_dev, c_dev, n);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? 0 : fail(e, "node sincos probe");
+}
+
+// The same, one angle at a time.
+extern "C" int awp_sincos_node(const double* a_dev, double* s_dev, double* c_dev, int64_t n, void* stream) {
+  return awp_sincos_nodes(a_dev, s_dev, c_dev, n, 1, 0, stream);
 }
