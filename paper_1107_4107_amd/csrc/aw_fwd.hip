@@ -1,7 +1,7 @@
 // aw_fwd.hip -- ensemble propagation kernels (gfx950, FP64).
 //
 // One orbit per lane (or two, interleaved, for instruction-level
-// parallelism; or, for small tangent-free ensembles, one orbit on two lanes);
+// parallelism; or, for small ensembles, one orbit on two lanes);
 // the state, the tangent vector and the accumulators stay in
 // VGPRs for the whole run; initial conditions are generated in registers from
 // the ensemble descriptor, so the only HBM traffic is the coalesced
@@ -559,7 +559,12 @@ __global__ __launch_bounds__(512, 2) void k_fwd_pair(FwdDesc, int64_t full_block
 // standard map 83 and 59.
 // Two orbits per lane take about 266 VGPRs; held to 256 (two waves per SIMD
 // instead of one, the spills outside the step loop) the batch runs a fifth
-// faster.
+// faster.  One orbit per lane without the tangent is held to 128, four waves per
+// SIMD, and spills 72 VGPRs per tile, outside the step loop: two slices of 1024 x
+// 1024 over 200 and 100 steps of the standard map take 595 us (613 at 256 VGPRs,
+// without spills; 650 in blocks of 256 lanes that pulled tiles of 256), 200 slices
+// of 40 x 40 152 (159; 197), 16 of up to 256 x 256 over up to 900 S6 steps 3.71 ms
+// (3.40; 3.92).
 template <int FORM, bool TAN, int OPL>
 __global__ __launch_bounds__(512, (TAN || OPL > 1) ? 2 : 4) void k_fwd_persist(const FwdDesc *__restrict__ descs,
                                                                                const int64_t *__restrict__ ends,

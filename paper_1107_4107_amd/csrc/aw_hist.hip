@@ -436,9 +436,11 @@ __global__ __launch_bounds__(ACC_BLOCK) void k_hist_small(int64_t N, const uint3
 // another block's counts.  The accumulation gathers a tile's runs from all
 // segments.  Against the sort by tile over the whole range, this drops the
 // bins' write and two reads of them, the two scans and their launches.
-// Bound by HBM: 72 MB of keys and values read and 30 MB written in 17 us (22
-// with the launch).  3000001 items into 512 x 512 bins, all launches: 67 us
-// sorted over the whole range, 42 in segments; into 64 x 64 78 / 55, into
+// Bound by memory: 72 MB of keys and values read and 30 MB written in 24.3 us
+// with the launch where the inputs are new (4.2 TB/s; a large copy reaches 5.0),
+// in 21.9 where repeated calls leave them in the Infinity Cache.  3000001 items
+// into 512 x 512 bins, all launches, inputs new / repeated: 72 / 68 us sorted over
+// the whole range, 44 / 42 in segments; repeated, into 64 x 64 78 / 55, into
 // 1024 x 512 72 / 49; all within 1/50 of either width of 512 x 512 84 / 62; 98304
 // items into 512 x 512 34 / 21.  Blocks of 512 lanes: three per CU hold 3e6
 // items at once; 6144 items on 1024 lanes took 28 us in place of 22.
